@@ -198,7 +198,8 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   int st = decode_mfma_supported(a) ? launch_decode_mfma(a)
            : decode_gla_supported(a) ? launch_decode_gla(a)
            : mla_mfma_supported(a)  ? launch_mla_mfma(a)
-                                    : launch_decode_generic(a);
+           : decode_f32_supported(a) ? launch_decode_f32(a)
+                                     : launch_decode_generic(a);
   if (st != MLRA_OK) return st;
   if (a.t_main.on() && !main_fast) (void)hipEventRecord(a.t_main.stop, a.stream);
   if (a.t_epi.on() && !epi_fast) (void)hipEventRecord(a.t_epi.start, a.stream);

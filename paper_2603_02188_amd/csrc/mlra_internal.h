@@ -124,6 +124,8 @@ int launch_absorb_q_generic(int batch, int h, int d_h, int n_blocks, int groups,
                             const void* w_uk, void* q_abs, int dtype, hipStream_t stream, float fold = 1.f,
                             const void* q_rope = nullptr, void* q_rope_out = nullptr, int d_r = 0);
 int launch_decode_generic(const DecodeArgs& a);
+bool decode_f32_supported(const DecodeArgs& a);   // fp32 matrix instructions, any dtype and dims up to its registers
+int launch_decode_f32(const DecodeArgs& a);
 // seq_lens_out[s * q_len + j] = max(0, seq_lens[s] - (q_len - 1 - j)); page_table_out row s * q_len + j = row s
 int launch_expand_queries(const int32_t* seq_lens, const int32_t* page_table, int batch, int q_len, int max_pages,
                           int32_t* seq_lens_out, int32_t* page_table_out, hipStream_t stream);

@@ -1,0 +1,96 @@
+"""The kernels on the fp32 matrix instructions (absorb, decode, merge + up-projection of every shape outside the bf16
+fast paths) at the edges of their tiles, against the fp64 oracle.  Bars as for the other parity tests:
+max|gpu - ref| / max|ref| <= 1e-5 (fp32 storage) and 1e-2 (bf16 storage)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mlra_oracle as orc
+from paper_2603_02188_amd import binding as mlra
+from paper_2603_02188_amd import inputs as gen
+
+from gpu_util import device_cache, device_queries_weights, host, max_rel_err, oracle_views
+
+pytestmark = pytest.mark.gpu
+
+TOL = {"bf16": 1e-2, "f32": 1e-5}
+
+
+def _shifted(t):
+    """The same values one element past an aligned address."""
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    buf[1:] = t.reshape(-1)
+    return buf[1:].view(t.shape)
+
+
+def _run(wl, lens, shift=False, folded=False, out_dtype=torch.float32):
+    print(f"[case] {wl.name} B={wl.batch} NB={wl.n_blocks} d_cb={wl.d_cb} d_r={wl.d_r} h={wl.h} d_h={wl.d_h} "
+          f"{wl.dtype} page={wl.page_size} groups={wl.groups} shift={shift} folded={folded} lens={list(lens)}", flush=True)
+    inp = gen.make_decode_inputs(wl, poison=True, seq_lens=np.array(lens, dtype=np.int32))
+    cache = device_cache(inp)
+    tensors = device_queries_weights(inp)
+    if shift:
+        cache = mlra.Cache(_shifted(cache.latent), _shifted(cache.rope), cache.page_table, cache.seq_lens)
+        tensors = [_shifted(t) for t in tensors]
+    q_nope, q_rope, w_uk, w_uv = tensors
+    two, scale = wl.groups == 2, wl.tau
+    if folded:
+        q_abs, q_rope = (mlra.mlra2_absorb_q_folded if two else mlra.mlra_absorb_q_folded)(q_nope, w_uk, q_rope, wl.tau)
+        scale = mlra.SCALE_FOLDED
+    else:
+        q_abs = (mlra.mlra2_absorb_q if two else mlra.mlra_absorb_q)(q_nope, w_uk)
+    lse = torch.full((wl.batch, wl.n_blocks, wl.h // wl.groups), float("nan"), device="cuda")
+    out = (mlra.mlra2_decode_attn if two else mlra.mlra_decode_attn)(cache, q_abs, q_rope, w_uv, scale, 0.5,
+                                                                     out_dtype=out_dtype, lse=lse)
+    torch.cuda.synchronize()
+    v = oracle_views(inp)
+    args = (v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"], v["q_rope"], v["w_uk"],
+            v["w_uv"], wl.tau)
+    ref = orc.mlra2_decode_batch(*args, 0.5) if two else orc.mlra_decode_batch(*args, 0.5)
+    err = max_rel_err(host(out), ref)
+    print(f"       max rel err {err:.3e}", flush=True)
+    assert err <= (1e-2 if out_dtype == torch.bfloat16 else TOL[wl.dtype])
+    lse = host(lse)
+    for s, n in enumerate(lens):
+        assert np.all(np.isneginf(lse[s])) if n == 0 else np.all(np.isfinite(lse[s]))
+
+
+def _wl(**kw):
+    return gen.WORKLOADS["C1"].scaled(**{**dict(name="f32-kernels", shuffle_pages=True, spare_frac=0.2), **kw})
+
+
+LENS = [0, 1, 63, 64, 65, 129, 300, 511]
+
+
+# heads: one tile, its edges, 2 and 4 tiles per workgroup and a remainder; dims: the edges of each register size (96 / 64,
+# 192 / 128, 320 / 256 channels), beyond the last one (the plain kernel), odd ones (element loads), one channel
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,d_cb,d_r,d_h,nb", [
+    (1, 64, 32, 64, 1), (16, 64, 32, 65, 2), (17, 60, 36, 24, 2), (33, 61, 3, 63, 1), (8, 65, 32, 64, 2),
+    (64, 128, 64, 128, 1), (65, 96, 32, 128, 1), (20, 127, 65, 66, 1), (130, 68, 24, 40, 2), (33, 129, 64, 64, 1),
+    (64, 256, 64, 64, 1), (17, 253, 67, 30, 1), (5, 260, 64, 64, 1), (3, 1, 2, 6, 80), (6, 7, 2, 130, 90)])
+def test_dims_and_heads(dtype, h, d_cb, d_r, d_h, nb):
+    _run(_wl(batch=len(LENS), n_min=0, n_max=511, h=h, d_cb=d_cb, d_r=d_r, d_h=d_h, n_blocks=nb, dtype=dtype), LENS)
+
+
+# batches around the 16 sequences of an MFMA tile; enough chunks that a piece's chunks are shared by several threads
+@pytest.mark.parametrize("batch,n,page", [(1, 9000, 64), (2, 3001, 48), (15, 130, 16), (16, 64, 64), (17, 200, 64), (33, 70, 32)])
+def test_batches_and_chunks(batch, n, page):
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(1, n + 1, size=batch)
+    lens[0] = n
+    for folded in (False, True):
+        _run(_wl(batch=batch, n_min=1, n_max=n, page_size=page, h=12), lens.tolist(), folded=folded)
+    _run(_wl(batch=batch, n_min=1, n_max=n, page_size=page, h=12, dtype="bf16"), lens.tolist(), out_dtype=torch.bfloat16)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("h,d_cb,d_r,d_h", [(8, 64, 32, 64), (40, 128, 64, 128), (16, 256, 64, 64)])
+def test_bases_that_are_not_aligned_for_wide_loads(dtype, h, d_cb, d_r, d_h):
+    _run(_wl(batch=3, n_min=1, n_max=400, h=h, d_cb=d_cb, d_r=d_r, d_h=d_h, n_blocks=2, dtype=dtype), [400, 1, 77],
+         shift=True, folded=True)
+
+
+def test_head_groups():
+    _run(_wl(batch=3, n_min=1, n_max=600, h=36, groups=2), [600, 1, 65])
+    _run(_wl(batch=3, n_min=1, n_max=600, h=36, groups=2, dtype="bf16"), [600, 0, 65], folded=True)
