@@ -1,12 +1,11 @@
-// Shape-generic kernels of libmlra: cache append, query absorption, a plain (non-MFMA) decode
-// kernel for any dims and for fp32 caches, and the split merge + up-projection epilogue.
+// Shape-generic kernels of libmlra: cache append, query expansion, a plain (non-MFMA) decode kernel for latent blocks
+// wider than the fp32 matrix kernel's registers hold, and the generic GQA decode.
 // All arithmetic is fp32; bf16 appears only as a storage type.
 #include "mlra_internal.h"
 
 namespace mlra {
 
 static constexpr float kLog2e = 1.4426950408889634f;
-static constexpr float kLn2 = 0.6931471805599453f;
 static constexpr float kNegBig = -1.0e30f;  // "no token seen yet" running max (finite: no inf-inf)
 
 __device__ __forceinline__ float wave_max(float v) {
@@ -76,52 +75,6 @@ int launch_expand_queries(const int32_t* seq_lens, const int32_t* page_table, in
                           int32_t* seq_lens_out, int32_t* page_table_out, hipStream_t stream) {
   expand_queries_kernel<<<batch * q_len, 256, 0, stream>>>(seq_lens, page_table, q_len, max_pages, seq_lens_out,
                                                            page_table_out);
-  return check_launch();
-}
-
-// ------------------------------------------------------------------------------------------------
-// mlra_absorb_q, generic form (Step 1, Section 2.1): one workgroup per (head, block, sequence);
-// each wave produces rows c of q~ = W^UK_(b),(i) q with lanes striding the d_h contraction.
-// ------------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void absorb_q_generic_kernel(const T* q_nope, const T* w_uk, T* q_abs, int h, int d_h, int n_blocks,
-                                        int groups, int d_cb, float fold, const T* q_rope, T* q_rope_out, int d_r) {
-  extern __shared__ float qs[];
-  const int head = blockIdx.x, b = blockIdx.y, s = blockIdx.z;
-  if (b == n_blocks) {   // (launched only when the softmax scale is folded in) the RoPE queries of this head
-    for (int id = threadIdx.x; id < groups * d_r; id += blockDim.x) {
-      const size_t off = ((size_t)s * h * groups + (id / d_r) * h + head) * d_r + id % d_r;
-      store_f32(q_rope_out, off, load_f32(q_rope, off) * fold);
-    }
-    return;
-  }
-  const int q_head = (b / (n_blocks / groups)) * h + head;   // Eq. (6): block b serves the heads of its group
-  for (int p = threadIdx.x; p < d_h; p += blockDim.x)
-    qs[p] = load_f32(q_nope, ((size_t)s * h * groups + q_head) * d_h + p);
-  __syncthreads();
-  const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, nwaves = blockDim.x / 64;
-  for (int c = wave; c < d_cb; c += nwaves) {
-    const size_t row = ((size_t)b * d_cb + c) * ((size_t)h * d_h) + (size_t)head * d_h;
-    float acc = 0.f;
-    for (int p = lane; p < d_h; p += 64) acc += load_f32(w_uk, row + p) * qs[p];
-    acc = wave_sum(acc);
-    if (lane == 0) store_f32(q_abs, (((size_t)s * n_blocks + b) * h + head) * d_cb + c, acc * fold);
-  }
-}
-
-int launch_absorb_q_generic(int batch, int h, int d_h, int n_blocks, int groups, int d_cb, const void* q_nope,
-                            const void* w_uk, void* q_abs, int dtype, hipStream_t stream, float fold,
-                            const void* q_rope, void* q_rope_out, int d_r) {
-  dim3 grid(h, n_blocks + (q_rope_out ? 1 : 0), batch);
-  const size_t lds = (size_t)d_h * sizeof(float);
-  if (dtype == MLRA_BF16)
-    absorb_q_generic_kernel<bf16_t><<<grid, 256, lds, stream>>>((const bf16_t*)q_nope, (const bf16_t*)w_uk,
-                                                                (bf16_t*)q_abs, h, d_h, n_blocks, groups, d_cb, fold,
-                                                                (const bf16_t*)q_rope, (bf16_t*)q_rope_out, d_r);
-  else
-    absorb_q_generic_kernel<float><<<grid, 256, lds, stream>>>((const float*)q_nope, (const float*)w_uk,
-                                                               (float*)q_abs, h, d_h, n_blocks, groups, d_cb, fold,
-                                                               (const float*)q_rope, (float*)q_rope_out, d_r);
   return check_launch();
 }
 
@@ -253,72 +206,6 @@ int launch_decode_generic(const DecodeArgs& a) {
         (const float*)a.latent, (const float*)a.rope, a.page_table, a.seq_lens, a.page_size, a.max_pages,
         a.n_blocks, a.d_cb, a.d_r, a.h, (const float*)a.q_abs, (const float*)a.q_rope, scale_log2, a.part_z,
         a.part_ml, a.plan.n_splits, a.plan.chunk_tokens, HG, TT, a.groups);
-  return check_launch();
-}
-
-// ------------------------------------------------------------------------------------------------
-// Split merge + Step 3 + block sum, generic form: one workgroup per (head, sequence).
-//   z_b = sum_s 2^(m_s - m*) z_s / sum_s 2^(m_s - m*) l_s        (log-sum-exp merge of the chunks)
-//   out = out_scale * sum_b z_b W^UV_(b),(i)                       (Step 3 and Eq. (5)'s block sum)
-// ------------------------------------------------------------------------------------------------
-template <typename T, typename TO>
-__global__ __launch_bounds__(256) void merge_upproj_generic_kernel(
-    const float* __restrict__ part_z, const float* __restrict__ part_ml, const int32_t* __restrict__ seq_lens,
-    const T* __restrict__ w_uv, TO* __restrict__ out, float* __restrict__ lse, int h, int d_h, int n_blocks,
-    int d_cb, int n_splits, int chunk, float out_scale, int groups, const T* __restrict__ gate) {
-  extern __shared__ float zs[];  // [bpg*d_cb]
-  // output head blockIdx.x = grp * h + head; its branches are the bpg blocks of group grp (Eq. (6);
-  // one group of all blocks is Eq. (5))
-  const int head = blockIdx.x % h, grp = blockIdx.x / h, s = blockIdx.y;
-  const int bpg = n_blocks / groups, b0 = grp * bpg;
-  const int n = seq_lens[s];
-  const int active = min(n_splits, (n + chunk - 1) / chunk);
-  const int tid = threadIdx.x;
-  for (int bb = 0; bb < bpg; ++bb) {
-    const int b = b0 + bb;
-    const size_t unit0 = ((size_t)s * n_blocks + b) * n_splits;
-    float m_star = kNegBig;
-    for (int k = 0; k < active; ++k) m_star = fmaxf(m_star, part_ml[((unit0 + k) * h + head) * 2]);
-    float L = 0.f;
-    for (int k = 0; k < active; ++k) {
-      const float* ml = part_ml + ((unit0 + k) * h + head) * 2;
-      L += exp2f(ml[0] - m_star) * ml[1];
-    }
-    const float inv = L > 0.f ? 1.f / L : 0.f;
-    for (int c = tid; c < d_cb; c += 256) {
-      float z = 0.f;
-      for (int k = 0; k < active; ++k) {
-        const float w = exp2f(part_ml[((unit0 + k) * h + head) * 2] - m_star);
-        z += w * part_z[((unit0 + k) * h + head) * d_cb + c];
-      }
-      zs[bb * d_cb + c] = z * inv;
-    }
-    if (tid == 0 && lse) lse[((size_t)s * n_blocks + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
-  }
-  __syncthreads();
-  const int d_cg = bpg * d_cb;
-  const size_t ld = (size_t)h * d_h;
-  for (int j = tid; j < d_h; j += 256) {
-    float acc = 0.f;
-    for (int r = 0; r < d_cg; ++r)
-      acc += zs[r] * load_f32(w_uv, ((size_t)b0 * d_cb + r) * ld + (size_t)head * d_h + j);
-    const size_t o = ((size_t)s * h * groups + blockIdx.x) * d_h + j;
-    store_f32(out, o, acc * out_scale * (gate ? load_f32(gate, o) : 1.f));   // gate: Appendix E, O^attn = Attention . G
-  }
-}
-
-int launch_merge_upproj_generic(const DecodeArgs& a) {
-  dim3 grid(a.h * a.groups, a.batch);
-  const size_t lds = (size_t)a.n_blocks / a.groups * a.d_cb * sizeof(float);
-#define MLRA_MERGE(T, TO)                                                                                       \
-  merge_upproj_generic_kernel<T, TO><<<grid, 256, lds, a.stream>>>(                                             \
-      a.part_z, a.part_ml, a.seq_lens, (const T*)a.w_uv, (TO*)a.out, a.lse, a.h, a.d_h, a.n_blocks, a.d_cb,     \
-      a.plan.n_splits, a.plan.chunk_tokens, a.out_scale, a.groups, (const T*)a.gate)
-  if (a.dtype == MLRA_BF16 && a.out_dtype == MLRA_BF16) MLRA_MERGE(bf16_t, bf16_t);
-  else if (a.dtype == MLRA_BF16) MLRA_MERGE(bf16_t, float);
-  else if (a.out_dtype == MLRA_BF16) MLRA_MERGE(float, bf16_t);
-  else MLRA_MERGE(float, float);
-#undef MLRA_MERGE
   return check_launch();
 }
 

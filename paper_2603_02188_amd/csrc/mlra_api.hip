@@ -203,7 +203,7 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   if (st != MLRA_OK) return st;
   if (a.t_main.on() && !main_fast) (void)hipEventRecord(a.t_main.stop, a.stream);
   if (a.t_epi.on() && !epi_fast) (void)hipEventRecord(a.t_epi.start, a.stream);
-  st = epi_fast ? launch_merge_upproj_mfma(a) : launch_merge_upproj_generic(a);
+  st = epi_fast ? launch_merge_upproj_mfma(a) : launch_merge_upproj_f32(a);
   if (a.t_epi.on() && !epi_fast) (void)hipEventRecord(a.t_epi.stop, a.stream);
   if (st == MLRA_OK && timing_on()) ++g_timing_calls;
   return st;
@@ -249,7 +249,7 @@ static int absorb_common(int batch, int h, int d_h, int n_blocks, int groups, in
   if (absorb_q_mfma_supported(d_h, d_cb, dtype) && (!q_rope_out || d_r % 8 == 0))
     return launch_absorb_q_mfma(batch, h / groups, d_h, n_blocks, groups, d_cb, q_nope, w_uk, q_abs,
                                 (hipStream_t)stream, fold, q_rope, q_rope_out, d_r);
-  return launch_absorb_q_generic(batch, h / groups, d_h, n_blocks, groups, d_cb, q_nope, w_uk, q_abs, dtype,
+  return launch_absorb_q_f32(batch, h / groups, d_h, n_blocks, groups, d_cb, q_nope, w_uk, q_abs, dtype,
                                  (hipStream_t)stream, fold, q_rope, q_rope_out, d_r);
 }
 
