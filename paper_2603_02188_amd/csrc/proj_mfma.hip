@@ -5,8 +5,6 @@
 //      contraction over all n_blocks * d_cb latent channels)
 // Both are batched over sequences as the MFMA M dimension so that each weight element is read once
 // per workgroup, and both put the head index on the grid.
-#include <type_traits>
-
 #include "mlra_internal.h"
 
 namespace mlra {
@@ -166,28 +164,33 @@ __global__ __launch_bounds__(256) void absorb_q_mfma_kernel(const bf16_t* __rest
 }
 
 // ------------------------------------------------------------------------------------------------
-// merge + up-projection.  One workgroup per (head, tile of up to 32 sequences).
-//   phase 0: the loads of the first 512 rows of this head's W^UV slice are issued into registers, so
-//            that they are in flight while phase 1 runs (and, when every sequence has a single chunk, the
-//            loads of the rows that the decode kernel already normalised and rounded: see `direct`);
-//   phase 1a: one thread per (sequence, block) turns the chunk partials' (m, l) into normalised merge
-//            weights w_k = 2^(m_k - m*) / L in LDS and writes the log-sum-exp;
-//   phase 1b: merged z = sum_k w_k z_k of the 32 sequences for all R = n_blocks*d_cb latent channels,
-//            rounded to bf16, is built in LDS (row = sequence), four independent items per thread at a
-//            time so that their loads overlap (`direct`: the rows arrive merged, they are only copied);
-//   phase 2: out[seq][j] = sum_r z[seq][r] W^UV[r][head*128 + j]; W^UV goes through LDS 256 rows at a
-//            time and reaches the MFMA B operand through transpose reads; wave w owns output columns
-//            [32 w, 32 w + 32).
+// merge + up-projection.  One workgroup per (head, tile of up to 32 sequences), two of them resident per CU.
+//   phase 0: the first 256 rows of this head's W^UV slice are fetched into registers, so that they are in flight while
+//            phase 1 runs;
+//   phase 1: merged z of the 32 sequences for all R = n_blocks * d_cb latent channels, rounded to bf16, is built in LDS
+//            (row = sequence).  kDirect: every sequence has one chunk and the decode kernel has normalised and rounded
+//            its row, which is only copied.  kRows / kItems: z = sum_k w_k z_k over the chunks, whose partials are
+//            normalised bf16 rows / fp32 Z; a thread takes U items (sequence, 8 channels) at a time and the first
+//            KK chunks of each are in flight while sixteen lanes per (sequence, block) turn the chunks' (m, l) into the
+//            weights w_k = 2^(m_k - m*) (l_k) / L in LDS and write the log-sum-exp;
+//   phase 2: out[seq][j] = sum_r z[seq][r] W^UV[r][head*128 + j]; W^UV goes through LDS 128 rows at a time (the rows
+//            after the next 128 are fetched into the registers that were just stored) and reaches the MFMA B operand
+//            through transpose reads; wave w owns output columns [32 w, 32 w + 32).
+// Bound by latency: a chain of a few round trips to memory per workgroup, which the second workgroup of the CU fills.
+// One kernel for all three forms held the registers of the largest (448), so that a CU had one workgroup.
+// Kernel times, before -> after the forms were split (128 heads, 512 latent channels): 128 sequences with gate and
+// log-sum-exp 41 -> 19 us, 64 sequences 15.6 -> 13.0, 4 sequences of up to 128K in 32 chunk slots 22.4 -> 17.4, one
+// sequence in 12 chunks 11.5 -> 8.9, fp32 partials of 128 sequences in 4 slots 32.9 -> 26.9.
 // ------------------------------------------------------------------------------------------------
-constexpr int kWRowsLds = 256;    // W^UV rows resident in LDS at a time (64 KiB)
-constexpr int kWRowsRegs = 512;   // W^UV rows prefetched into registers at a time (32 loads per thread)
+constexpr int kWRows = 128;       // W^UV rows in LDS at a time (32 KiB); twice as many in registers
+enum MergeMode { kDirect, kRows, kItems };
 
-template <typename TO>
-__global__ __launch_bounds__(256) void merge_upproj_mfma_kernel(
+template <typename TO, int MODE, int U, int KK>
+__global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
     const float* __restrict__ part_z, const float* __restrict__ part_ml, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ w_uv, TO* __restrict__ out, float* __restrict__ lse, int batch, int h, int nb_total,
     int d_cb, int n_splits, int chunk, const int32_t* __restrict__ chunk_tab, float out_scale,
-    const bf16_t* __restrict__ gate, int rows_bf16, int spw) {
+    const bf16_t* __restrict__ gate, int spw) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // blockIdx.z = head group (Eq. (6)); one group of all blocks is Eq. (5).  h: heads per block; this
   // workgroup's head is h * group + head in out, and its branches are blocks [b0, b0 + n_blocks).
@@ -195,247 +198,192 @@ __global__ __launch_bounds__(256) void merge_upproj_mfma_kernel(
   const int R = n_blocks * d_cb;
   const int zpitch = R + 8;                               // bf16 elements per z row (+16 B against conflicts)
   const int units_per_seq = n_blocks * n_splits;
-  unsigned char* wt = smem;                               // [256 rows][256 B], 16-byte chunks swizzled
-  bf16_t* zt = (bf16_t*)(smem + kWRowsLds * 256);         // [32][zpitch]
-  float* wtab = (float*)(smem + kWRowsLds * 256 + (size_t)32 * zpitch * 2);   // [32][units_per_seq]
-  float* ltab = wtab + 32 * units_per_seq;                 // [32][units_per_seq] row sums of the partials
-  int* act = (int*)(ltab + 32 * units_per_seq);           // [32] active chunks per sequence
+  unsigned char* wt = smem;                               // [kWRows][256 B], 16-byte chunks swizzled
+  bf16_t* zt = (bf16_t*)(smem + kWRows * 256);            // [32][zpitch]
+  float* wtab = (float*)(smem + kWRows * 256 + (size_t)32 * zpitch * 2);   // [32][units_per_seq] (not kDirect)
   // spw: sequences per workgroup (32, or fewer for small batches so that more workgroups share the merge;
   // the rest of the 32 MFMA rows is zero padding)
   const int head = blockIdx.x, m0 = blockIdx.y * spw;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, g = lane >> 5, c32 = lane & 31;
   const size_t ldw = (size_t)h * kDh;
-
-  // ---- phase 0: thread t owns 16-byte chunk t % 16 of rows t / 16 + 16 i
-  bf16x8 wreg[kWRowsRegs / 16];
-  const bf16_t* wsrc = w_uv + ((size_t)b0 * d_cb + (tid >> 4)) * ldw + (size_t)head * kDh + (tid & 15) * 8;
-  auto fetch_w = [&](int row0) {
-#pragma unroll
-    for (int i = 0; i < kWRowsRegs / 16; ++i)
-      if (row0 + 16 * i < R) wreg[i] = *(const bf16x8*)(wsrc + (size_t)(row0 + 16 * i) * ldw);
-  };
-  fetch_w(0);
-  // (single-chunk rows, see phase 1b: their loads do not depend on phase 1a, so they go out here as well;
-  // what a sequence without tokens leaves in the workspace is discarded below)
-  constexpr int kZPre = 8;
-  bf16x8 zpre[kZPre];
-  const int items_per_row = R / 8;
   const int n_valid = min(spw, batch - m0);
-  const int n_items = n_valid * items_per_row;
-  // normalised bf16 rows, one chunk per sequence: the rows are final (see phase 1b)
-  const bool direct = rows_bf16 && n_splits == 1;
-  const bool z_early = direct && n_items <= kZPre * 256;
-  if (z_early) {
+  const int items_per_row = R / 8, n_items = n_valid * items_per_row;
+
+  // ---- phase 0: thread t owns 16-byte chunk t % 16 of rows t / 16 + 16 i of each part
+  bf16x8 wreg[2][kWRows / 16];
+  const bf16_t* wsrc = w_uv + ((size_t)b0 * d_cb + (tid >> 4)) * ldw + (size_t)head * kDh + (tid & 15) * 8;
+  auto fetch_w = [&](int part, bf16x8 (&reg)[kWRows / 16]) {
 #pragma unroll
-    for (int u = 0; u < kZPre; ++u) {
-      const int item = min(tid + u * 256, n_items - 1);
-      const int sl = item / items_per_row, r0 = (item % items_per_row) * 8;
-      zpre[u] = *(const bf16x8*)((const bf16_t*)part_z +
-                                 (((size_t)(m0 + sl) * nb_total + b0 + r0 / d_cb) * h + head) * d_cb + r0 % d_cb);
-    }
-  }
+    for (int i = 0; i < kWRows / 16; ++i)
+      if (part * kWRows + 16 * i < R) reg[i] = *(const bf16x8*)(wsrc + (size_t)(part * kWRows + 16 * i) * ldw);
+  };
+  fetch_w(0, wreg[0]);
+  fetch_w(1, wreg[1]);
 
-  // ---- phase 1a: every (sequence, block, chunk) partial's (m, l) goes to LDS with one load per thread,
-  // then one thread per (sequence, block) reduces them
-  for (int t = tid; t < 32 * units_per_seq; t += 256) {
-    const int sl = t / units_per_seq, seq = m0 + sl, k = t % n_splits;
-    float2 ml = make_float2(kNegBig, 0.f);
-    if (sl < n_valid) {
-      // the slot exists in the workspace whether or not its chunk ran: loaded without waiting for the
-      // sequence length (one round trip instead of two), kept only if the chunk is active
-      const float2 got =
-          *(const float2*)(part_ml + ((((size_t)seq * nb_total + b0) * n_splits + t % units_per_seq) * h + head) * 2);
-      const int ch = chunk_tab ? chunk_tab[seq] : chunk;
-      const int active = min(n_splits, (seq_lens[seq] + ch - 1) / ch);
-      if (k < active) ml = got;
-    }
-    wtab[t] = ml.x;
-    ltab[t] = ml.y;
-  }
-  __syncthreads();
-  for (int t = tid; t < 32 * n_blocks; t += 256) {
-    const int sl = t / n_blocks, b = t % n_blocks, seq = m0 + sl;
-    float* wrow = wtab + sl * units_per_seq + b * n_splits;
-    const float* lrow = ltab + sl * units_per_seq + b * n_splits;
-    int active = 0;
-    if (sl < n_valid) {
-      const int ch = chunk_tab ? chunk_tab[seq] : chunk;
-      active = min(n_splits, (seq_lens[seq] + ch - 1) / ch);
-      float m_star = kNegBig;
-      for (int k = 0; k < active; ++k) m_star = fmaxf(m_star, wrow[k]);
-      float L = 0.f;
-      for (int k = 0; k < active; ++k) {
-        const float w = exp2f(wrow[k] - m_star);
-        L += w * lrow[k];
-        // (a partial that arrives normalised, z_k / l_k, carries its row sum in its weight)
-        wrow[k] = rows_bf16 ? w * lrow[k] : w;
-      }
-      const float inv = L > 0.f ? 1.f / L : 0.f;
-      for (int k = 0; k < active; ++k) wrow[k] *= inv;
-      if (lse) lse[((size_t)seq * nb_total + b0 + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
-    }
-    if (b == 0) act[sl] = active;
-  }
-  __syncthreads();
-
-  // ---- phase 1b: item = (valid sequence slot, 8 consecutive latent channels).  A thread takes U items
-  // at a time and KK chunks of each per round trip, U * KK = 16 (32 loads in flight): many chunks (small
-  // batches) go one item per thread with sixteen chunks in flight, one or two chunks eight items per
-  // thread.
+  // ---- phase 1
+  auto active_chunks = [&](int seq) {
+    const int ch = chunk_tab ? chunk_tab[seq] : chunk;
+    return min(n_splits, (seq_lens[seq] + ch - 1) / ch);
+  };
+  bf16x8 zero8;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) zero8[e] = (__bf16)0.0f;
   // rows of sequences past the batch feed MFMA rows that are never stored; they only have to be finite
-  for (int t = n_items + tid; t < 32 * items_per_row; t += 256) {
-    bf16x8 zero;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) zero[e] = (__bf16)0.0f;
-    *(bf16x8*)(zt + (t / items_per_row) * zpitch + (t % items_per_row) * 8) = zero;
-  }
-  const size_t z_stride = (size_t)h * d_cb;
-  auto merge_items = [&](auto u_tag) {
-    constexpr int U = decltype(u_tag)::value, KK = 16 / U;
+  for (int t = n_items + tid; t < 32 * items_per_row; t += 256)
+    *(bf16x8*)(zt + (t / items_per_row) * zpitch + (t % items_per_row) * 8) = zero8;
+  if constexpr (MODE == kDirect) {
+    const bf16_t* zn = (const bf16_t*)part_z;
     for (int base = tid; base < n_items; base += U * 256) {
-      float z[U][8];
-      const float* pz[U];
-      const float* wk[U];
-      int na[U], sl[U], r0[U], kmax = 0;
+      bf16x8 row[U];
+      int n[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int item = min(base + u * 256, n_items - 1), sl = item / items_per_row, r0 = (item % items_per_row) * 8;
+        row[u] = *(const bf16x8*)(zn + (((size_t)(m0 + sl) * nb_total + b0 + r0 / d_cb) * h + head) * d_cb + r0 % d_cb);
+        n[u] = seq_lens[m0 + sl];
+      }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int item = base + u * 256;
-        sl[u] = min(item, n_items - 1) / items_per_row;
-        r0[u] = (min(item, n_items - 1) % items_per_row) * 8;
+        // (what a sequence without tokens leaves in the workspace is discarded)
+        if (item < n_items)
+          *(bf16x8*)(zt + (item / items_per_row) * zpitch + (item % items_per_row) * 8) = n[u] > 0 ? row[u] : zero8;
+      }
+    }
+    if (lse)
+      for (int t = tid; t < n_valid * n_blocks; t += 256) {
+        const int seq = m0 + t / n_blocks, b = b0 + t % n_blocks;
+        const float2 ml = *(const float2*)(part_ml + (((size_t)seq * nb_total + b) * h + head) * 2);
+        lse[((size_t)seq * nb_total + b) * h + head] =
+            seq_lens[seq] > 0 && ml.y > 0.f ? (ml.x + log2f(ml.y)) * kLn2 : -INFINITY;
+      }
+  } else {
+    const size_t z_stride = (size_t)h * d_cb;
+    bool have_weights = false;
+    for (int base0 = 0; base0 < n_items; base0 += U * 256) {
+      const int base = base0 + tid;
+      size_t pz[U];
+      const float* wk[U];
+      int na[U], sl[U], r0[U], kmax = 0;
+      float z[U][8];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int item = min(base + u * 256, n_items - 1);
+        sl[u] = item / items_per_row;
+        r0[u] = (item % items_per_row) * 8;
         const int b = r0[u] / d_cb, c0 = r0[u] % d_cb;
-        na[u] = item < n_items ? act[sl[u]] : 0;
+        na[u] = base + u * 256 < n_items ? active_chunks(m0 + sl[u]) : 0;
         kmax = max(kmax, na[u]);
-        pz[u] = part_z + ((((size_t)(m0 + sl[u]) * nb_total + b0 + b) * n_splits) * h + head) * d_cb + c0;
+        pz[u] = ((((size_t)(m0 + sl[u]) * nb_total + b0 + b) * n_splits) * h + head) * d_cb + c0;
         wk[u] = wtab + sl[u] * units_per_seq + b * n_splits;
 #pragma unroll
         for (int e = 0; e < 8; ++e) z[u][e] = 0.f;
       }
-      for (int k0 = 0; k0 < kmax; k0 += KK) {
-        f32x4 lo[KK][U], hi[KK][U];
-        float w[KK][U];
+      typedef __attribute__((ext_vector_type(MODE == kRows ? 4 : 8))) float raw_t;   // eight channels as stored
+      raw_t raw[KK][U];
+      auto load_chunks = [&](int k0) {
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const int k = k0 + kk;
-            const bool on = k < na[u];
-            const f32x4* src = (const f32x4*)(pz[u] + (on ? k : 0) * z_stride);
-            w[kk][u] = on ? wk[u][k] : 0.f;
-            if (on) { lo[kk][u] = src[0]; hi[kk][u] = src[1]; }
-            else { lo[kk][u] = f32x4{0.f, 0.f, 0.f, 0.f}; hi[kk][u] = lo[kk][u]; }
+            const size_t at = pz[u] + (k0 + kk < na[u] ? k0 + kk : 0) * z_stride;   // (chunk 0's slot always exists)
+            if constexpr (MODE == kRows) raw[kk][u] = *(const raw_t*)((const bf16_t*)part_z + at);
+            else raw[kk][u] = *(const raw_t*)(part_z + at);
+          }
+      };
+      load_chunks(0);
+      if (!have_weights) {     // (uniform) weights of all (sequence, block) pairs, once
+        have_weights = true;
+        // (four pairs of a lane group at a time, so that their loads overlap; chunk l16 of each stays in a register,
+        // and only chunks from 16 on are read twice)
+        const int l16 = lane & 15, n_pairs = n_valid * n_blocks;
+        for (int pair0 = tid >> 4; pair0 < n_pairs; pair0 += 64) {
+          float2 first[4];
+          int active[4];
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int pair = min(pair0 + 16 * i, n_pairs - 1), ps = pair / n_blocks, b = pair - ps * n_blocks;
+            active[i] = active_chunks(m0 + ps);
+            first[i] = *(const float2*)(part_ml + ((((size_t)(m0 + ps) * nb_total + b0 + b) * n_splits +
+                                                    min(l16, n_splits - 1)) * h + head) * 2);
           }
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
+          for (int i = 0; i < 4; ++i) {
+            const int pair = pair0 + 16 * i, ps = pair / n_blocks, b = pair - ps * n_blocks, seq = m0 + ps;
+            if (pair >= n_pairs) break;
+            const float* ml = part_ml + ((((size_t)seq * nb_total + b0 + b) * n_splits) * h + head) * 2;
+            float* wrow = wtab + ps * units_per_seq + b * n_splits;
+            float m_star = l16 < active[i] ? fmaxf(kNegBig, first[i].x) : kNegBig, L = 0.f, w0 = 0.f;
+            for (int k = l16 + 16; k < active[i]; k += 16) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);
 #pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              z[u][e] += w[kk][u] * lo[kk][u][e];
-              z[u][4 + e] += w[kk][u] * hi[kk][u][e];
+            for (int o = 8; o > 0; o >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, o));
+            // (a partial that arrives normalised, z_k / l_k, carries its row sum in its weight)
+            if (l16 < active[i]) {
+              w0 = exp2f(first[i].x - m_star);
+              L = w0 * first[i].y;
+              if (MODE == kRows) w0 = L;
             }
-      }
+            for (int k = l16 + 16; k < active[i]; k += 16) {
+              const float2 got = *(const float2*)(ml + (size_t)k * h * 2);
+              const float w = exp2f(got.x - m_star);
+              L += w * got.y;
+              wrow[k] = MODE == kRows ? w * got.y : w;
+            }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (base + u * 256 < n_items) {
-          bf16x8 packed;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) packed[e] = (__bf16)z[u][e];
-          *(bf16x8*)(zt + sl[u] * zpitch + r0[u]) = packed;
+            for (int o = 8; o > 0; o >>= 1) L += __shfl_xor(L, o);
+            const float inv = L > 0.f ? 1.f / L : 0.f;
+            if (l16 < active[i]) wrow[l16] = w0 * inv;
+            for (int k = l16 + 16; k < active[i]; k += 16) wrow[k] *= inv;
+            if (lse && l16 == 0)
+              lse[((size_t)seq * nb_total + b0 + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
+          }
         }
-      }
-    }
-  };
-  // the same for partials that are normalised bf16 rows (16 bytes per item and chunk)
-  auto merge_rows = [&](auto u_tag) {
-    constexpr int U = decltype(u_tag)::value, KK = 16 / U;
-    const bf16_t* zn = (const bf16_t*)part_z;
-    for (int base = tid; base < n_items; base += U * 256) {
-      float z[U][8];
-      const bf16_t* pz[U];
-      const float* wk[U];
-      int na[U], sl[U], r0[U], kmax = 0;
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int item = base + u * 256;
-        sl[u] = min(item, n_items - 1) / items_per_row;
-        r0[u] = (min(item, n_items - 1) % items_per_row) * 8;
-        const int b = r0[u] / d_cb, c0 = r0[u] % d_cb;
-        na[u] = item < n_items ? act[sl[u]] : 0;
-        kmax = max(kmax, na[u]);
-        pz[u] = zn + ((((size_t)(m0 + sl[u]) * nb_total + b0 + b) * n_splits) * h + head) * d_cb + c0;
-        wk[u] = wtab + sl[u] * units_per_seq + b * n_splits;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z[u][e] = 0.f;
+        __syncthreads();
       }
       for (int k0 = 0; k0 < kmax; k0 += KK) {
-        bf16x8 row[KK][U];
-        float w[KK][U];
+        if (k0 > 0) load_chunks(k0);
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk)
 #pragma unroll
           for (int u = 0; u < U; ++u) {
-            const int k = k0 + kk;
-            const bool on = k < na[u];
-            w[kk][u] = on ? wk[u][k] : 0.f;
-            row[kk][u] = *(const bf16x8*)(pz[u] + (on ? k : 0) * z_stride);   // (chunk 0's slot always exists)
+            const bool on = k0 + kk < na[u];
+            const float w = on ? wk[u][k0 + kk] : 0.f;
+            // (an inactive chunk has weight 0; what its slot holds may be anything, NaN included)
+            if constexpr (MODE == kRows) {
+              const bf16x8 row = __builtin_bit_cast(bf16x8, raw[kk][u]);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) z[u][e] += w != 0.f ? w * (float)row[e] : 0.f;
+            } else {
+#pragma unroll
+              for (int e = 0; e < 8; ++e) z[u][e] += on ? w * raw[kk][u][e] : 0.f;
+            }
           }
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk)
-#pragma unroll
-          for (int u = 0; u < U; ++u)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              // (an inactive chunk has weight 0; what its slot holds may be anything, NaN included)
-              z[u][e] += w[kk][u] != 0.f ? w[kk][u] * (float)row[kk][u][e] : 0.f;
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
+      for (int u = 0; u < U; ++u)
         if (base + u * 256 < n_items) {
           bf16x8 packed;
 #pragma unroll
           for (int e = 0; e < 8; ++e) packed[e] = (__bf16)z[u][e];
           *(bf16x8*)(zt + sl[u] * zpitch + r0[u]) = packed;
         }
-      }
     }
-  };
-  if (z_early) {
-    // one chunk per sequence and the decode kernel wrote z / l as bf16 rows [.][block][head][d_cb]: the
-    // rows fetched at the top go to LDS
-    bf16x8 zero;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) zero[e] = (__bf16)0.0f;
-#pragma unroll
-    for (int u = 0; u < kZPre; ++u) {
-      const int item = tid + u * 256;
-      if (item < n_items) {
-        const int sl = item / items_per_row, r0 = (item % items_per_row) * 8;
-        *(bf16x8*)(zt + sl * zpitch + r0) = act[sl] > 0 ? zpre[u] : zero;
-      }
-    }
-  } else if (direct) {
-    // (the same for more rows than a thread prefetches)
-    const bf16_t* zn = (const bf16_t*)part_z;
-    for (int item = tid; item < n_items; item += 256) {
-      const int sl = item / items_per_row, r0 = (item % items_per_row) * 8;
-      const int b = r0 / d_cb, c0 = r0 % d_cb;
-      bf16x8 v;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (__bf16)0.0f;
-      if (act[sl] > 0) v = *(const bf16x8*)(zn + (((size_t)(m0 + sl) * nb_total + b0 + b) * h + head) * d_cb + c0);
-      *(bf16x8*)(zt + sl * zpitch + r0) = v;
-    }
-  } else if (rows_bf16) {
-    if (n_splits > 8) merge_rows(std::integral_constant<int, 1>{});
-    else if (n_splits > 4) merge_rows(std::integral_constant<int, 2>{});
-    else if (n_splits > 2) merge_rows(std::integral_constant<int, 4>{});
-    else merge_rows(std::integral_constant<int, 8>{});
-  } else if (n_splits > 8) merge_items(std::integral_constant<int, 1>{});
-  else if (n_splits > 4) merge_items(std::integral_constant<int, 2>{});
-  else if (n_splits > 2) merge_items(std::integral_constant<int, 4>{});
-  else merge_items(std::integral_constant<int, 8>{});
+  }
 
   // ---- phase 2 ----
+  // The gate values of this lane's outputs are fetched here, all sixteen at once (rows past the batch repeat the last
+  // one): fetched one by one between the stores at the end, each was a round trip to memory of its own (12 us of 39 on
+  // 128 sequences).
+  const int j = wave * 32 + c32;
+  auto out_at = [&](int r) {             // accumulator register r: offset of its sequence slot in out and gate
+    const int sl = (r >> 2) * 8 + g * 4 + (r & 3), s = m0 + min(sl, n_valid - 1);
+    return ((size_t)s * h * gridDim.z + blockIdx.z * h + head) * kDh + j;
+  };
+  bf16_t gate_v[16];
+  if (gate) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) gate_v[r] = gate[out_at(r)];
+  }
   f32x16 acc = opaque_zero();
   // transpose-read offsets: the 16 lanes of a block fetch 4 consecutive rows x 16 output columns
   unsigned tr_off[2];
@@ -448,45 +396,42 @@ __global__ __launch_bounds__(256) void merge_upproj_mfma_kernel(
       tr_off[half] = row * 256 + ((cc ^ swz(row & 7)) << 4) + ((seg & 1) << 3);
     }
   }
-  for (int pass0 = 0; pass0 < R; pass0 += kWRowsRegs) {
-    if (pass0 > 0) fetch_w(pass0);
+  auto part_step = [&](int part, bf16x8 (&reg)[kWRows / 16]) {
+    const int row_base = part * kWRows;
+    if (row_base >= R) return;                              // (uniform)
+    __syncthreads();   // phase 1 done / previous rows consumed
 #pragma unroll
-    for (int part = 0; part < kWRowsRegs / kWRowsLds; ++part) {
-      const int row_base = pass0 + part * kWRowsLds;
-      if (row_base >= R) break;
-      __syncthreads();   // phase 1 done / previous rows consumed
-#pragma unroll
-      for (int i = 0; i < kWRowsLds / 16; ++i) {
-        const int row = (tid >> 4) + 16 * i, cc = tid & 15;
-        if (row_base + row < R)
-          *(bf16x8*)(wt + row * 256 + ((cc ^ swz(row & 7)) << 4)) = wreg[part * (kWRowsLds / 16) + i];
-      }
-      __syncthreads();
-      const int rows = min(kWRowsLds, R - row_base);
-      auto k_step = [&](int ks) {
-        const bf16x8 a = *(const bf16x8*)(zt + c32 * zpitch + row_base + ks * 16 + g * 8);
-        const short4v lo = lds_tr16(wt + ks * 16 * 256 + tr_off[0]);
-        const short4v hi = lds_tr16(wt + ks * 16 * 256 + tr_off[1]);
-        const bf16x8 bm = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bm, acc, 0, 0, 0);
-      };
-      if (rows == kWRowsLds) {
-        // straight-line, so that the LDS reads of later steps are issued ahead of the MFMAs of earlier ones
-#pragma unroll
-        for (int ks = 0; ks < kWRowsLds / 16; ++ks) k_step(ks);
-      } else {
-        for (int ks = 0; ks < rows / 16; ++ks) k_step(ks);
-      }
+    for (int i = 0; i < kWRows / 16; ++i) {
+      const int row = (tid >> 4) + 16 * i, cc = tid & 15;
+      if (row_base + 16 * i < R) *(bf16x8*)(wt + row * 256 + ((cc ^ swz(row & 7)) << 4)) = reg[i];
     }
+    if (row_base + 2 * kWRows < R) fetch_w(part + 2, reg);
+    __syncthreads();
+    const int rows = min(kWRows, R - row_base);
+    auto k_step = [&](int ks) {
+      const bf16x8 a = *(const bf16x8*)(zt + c32 * zpitch + row_base + ks * 16 + g * 8);
+      const short4v lo = lds_tr16(wt + ks * 16 * 256 + tr_off[0]);
+      const short4v hi = lds_tr16(wt + ks * 16 * 256 + tr_off[1]);
+      const bf16x8 bm = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bm, acc, 0, 0, 0);
+    };
+    if (rows == kWRows) {
+      // straight-line, so that the LDS reads of later steps are issued ahead of the MFMAs of earlier ones
+#pragma unroll
+      for (int ks = 0; ks < kWRows / 16; ++ks) k_step(ks);
+    } else {
+      for (int ks = 0; ks < rows / 16; ++ks) k_step(ks);
+    }
+  };
+  for (int part = 0; part * kWRows < R; part += 2) {
+    part_step(part, wreg[0]);
+    part_step(part + 1, wreg[1]);
   }
-  const int j = wave * 32 + c32;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
-    const int sl = (r >> 2) * 8 + g * 4 + (r & 3), s = m0 + sl;
-    if (sl < n_valid) {
-      const size_t o = ((size_t)s * h * gridDim.z + blockIdx.z * h + head) * kDh + j;
-      store_f32(out, o, acc[r] * out_scale * (gate ? bf16_to_f32(gate[o]) : 1.f));   // gate: Appendix E
-    }
+    const int sl = (r >> 2) * 8 + g * 4 + (r & 3);
+    if (sl < n_valid)
+      store_f32(out, out_at(r), acc[r] * out_scale * (gate ? bf16_to_f32(gate_v[r]) : 1.f));   // gate: Appendix E
   }
 }
 
@@ -507,50 +452,63 @@ int launch_absorb_q_mfma(int batch, int h, int d_h, int n_blocks, int groups, in
   return check_launch();
 }
 
-// Dynamic LDS of the merge + up-projection kernel: the weight rows, the normalised z rows of 32 sequences,
-// the merge weights of every (sequence, block, chunk), the active-chunk counts.
-static size_t merge_upproj_lds_bytes(const DecodeArgs& a) {
+// Dynamic LDS of the merge + up-projection kernel: the weight rows, the normalised z rows of 32 sequences and, when
+// there is something to merge, the weights of every (sequence, block, chunk).
+static size_t merge_upproj_lds_bytes(const DecodeArgs& a, bool direct) {
   const int bpg = a.n_blocks / a.groups, R = bpg * a.d_cb;
-  return (size_t)kWRowsLds * 256 + (size_t)32 * (R + 8) * 2 + (size_t)64 * bpg * a.plan.n_splits * sizeof(float) +
-         32 * sizeof(int);
+  return (size_t)kWRows * 256 + (size_t)32 * (R + 8) * 2 + (direct ? 0 : (size_t)32 * bpg * a.plan.n_splits * sizeof(float));
 }
 constexpr size_t kMergeLdsLimit = 160 * 1024;
 
-// (shapes whose tables would not fit the 160 KiB of LDS take the generic epilogue instead of failing at launch)
+// Up to 1024 latent channels and 128 (block, chunk) slots per sequence, as long as z rows and slots together stay
+// moderate (at most 98,176 bytes at 64 per z channel and 256 per slot); everything else takes the fp32 epilogue.
 bool merge_upproj_mfma_supported(const DecodeArgs& a) {
-  return a.dtype == MLRA_BF16 && a.d_h == kDh && a.d_cb % 32 == 0 && a.n_blocks / a.groups * a.d_cb <= 1024 &&
-         a.n_blocks / a.groups * a.plan.n_splits <= 128 && merge_upproj_lds_bytes(a) <= kMergeLdsLimit;
+  const int bpg = a.n_blocks / a.groups;
+  return a.dtype == MLRA_BF16 && a.d_h == kDh && a.d_cb % 32 == 0 && bpg * a.d_cb <= 1024 &&
+         bpg * a.plan.n_splits <= 128 && 64L * (bpg * a.d_cb + 8) + 256L * bpg * a.plan.n_splits <= 98176;
 }
 
-int launch_merge_upproj_mfma(const DecodeArgs& a) {
-  const size_t lds = merge_upproj_lds_bytes(a);
+template <typename TO, int MODE, int U, int KK>
+static int launch_merge_as(const DecodeArgs& a, dim3 grid, int spw) {
   static PerDeviceSetup setup;
   int setup_dev = -1;
   if (setup.needed(&setup_dev)) {
-    if (hipFuncSetAttribute((const void*)merge_upproj_mfma_kernel<bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kMergeLdsLimit) != hipSuccess ||
-        hipFuncSetAttribute((const void*)merge_upproj_mfma_kernel<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)kMergeLdsLimit) != hipSuccess)
+    if (hipFuncSetAttribute((const void*)merge_upproj_mfma_kernel<TO, MODE, U, KK>,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMergeLdsLimit) != hipSuccess)
       return MLRA_ERR_LAUNCH;
     setup.done(setup_dev);
   }
-  // small batches: fewer sequences per workgroup while that brings more workgroups onto idle CUs
+  const int32_t* const chunk_tab = a.balanced ? a.chunk_tab : nullptr;
+  MLRA_LAUNCH_TIMED(a.t_epi, (merge_upproj_mfma_kernel<TO, MODE, U, KK>), grid, dim3(256),
+                    merge_upproj_lds_bytes(a, MODE == kDirect), a.stream, (const float*)a.part_z,
+                    (const float*)a.part_ml, a.seq_lens, (const bf16_t*)a.w_uv, (TO*)a.out, a.lse, a.batch, a.h,
+                    a.n_blocks, a.d_cb, a.plan.n_splits, a.plan.chunk_tokens, chunk_tab, a.out_scale,
+                    (const bf16_t*)a.gate, spw);
+  return check_launch();
+}
+
+template <typename TO>
+static int launch_merge_typed(const DecodeArgs& a, dim3 grid, int spw) {
+  // U items per thread and step: many chunks (small batches) go one item per thread with all loads on its chunks, few
+  // chunks several items
+  // (at most four slots: the forms that leave a batch of nearly equal lengths uncut, one or two of them are used)
+  if (a.rows_bf16) {
+    if (a.plan.n_splits == 1) return launch_merge_as<TO, kDirect, 8, 1>(a, grid, spw);
+    if (a.plan.n_splits > 8) return launch_merge_as<TO, kRows, 1, 16>(a, grid, spw);
+    if (a.plan.n_splits > 4) return launch_merge_as<TO, kRows, 2, 8>(a, grid, spw);
+    return launch_merge_as<TO, kRows, 4, 2>(a, grid, spw);
+  }
+  if (a.plan.n_splits > 4) return launch_merge_as<TO, kItems, 1, 8>(a, grid, spw);
+  return launch_merge_as<TO, kItems, 4, 2>(a, grid, spw);
+}
+
+int launch_merge_upproj_mfma(const DecodeArgs& a) {
+  // small batches: fewer sequences per workgroup while that brings more workgroups onto idle CUs (not below 8: with 4 or
+  // 2, 4 sequences of up to 128K took the same 17 us; two workgroups per CU instead of one cost 64 sequences 3 us)
   int spw = 32;
   while (spw > 8 && (long)a.h * a.groups * ((a.batch + spw - 1) / spw) < device_cu_count()) spw /= 2;
-  dim3 grid(a.h, (a.batch + spw - 1) / spw, a.groups);
-  const int32_t* const chunk_tab = a.balanced ? a.chunk_tab : nullptr;
-  const int direct = a.rows_bf16 ? 1 : 0;
-  if (a.out_dtype == MLRA_BF16)
-    MLRA_LAUNCH_TIMED(a.t_epi, merge_upproj_mfma_kernel<bf16_t>, grid, dim3(256), lds, a.stream, (const float*)a.part_z,
-                      (const float*)a.part_ml, a.seq_lens, (const bf16_t*)a.w_uv, (bf16_t*)a.out, a.lse, a.batch, a.h,
-                      a.n_blocks, a.d_cb, a.plan.n_splits, a.plan.chunk_tokens, chunk_tab, a.out_scale,
-                      (const bf16_t*)a.gate, direct, spw);
-  else
-    MLRA_LAUNCH_TIMED(a.t_epi, merge_upproj_mfma_kernel<float>, grid, dim3(256), lds, a.stream, (const float*)a.part_z,
-                      (const float*)a.part_ml, a.seq_lens, (const bf16_t*)a.w_uv, (float*)a.out, a.lse, a.batch, a.h,
-                      a.n_blocks, a.d_cb, a.plan.n_splits, a.plan.chunk_tokens, chunk_tab, a.out_scale,
-                      (const bf16_t*)a.gate, direct, spw);
-  return check_launch();
+  const dim3 grid(a.h, (a.batch + spw - 1) / spw, a.groups);
+  return a.out_dtype == MLRA_BF16 ? launch_merge_typed<bf16_t>(a, grid, spw) : launch_merge_typed<float>(a, grid, spw);
 }
 
 }  // namespace mlra

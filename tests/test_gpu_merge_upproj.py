@@ -1,0 +1,67 @@
+"""The merge + up-projection kernel of the bf16 path at the edges of its forms: one chunk per sequence (rows only
+copied), few and many chunk slots (lane groups of sixteen, remainders), fp32 partials, tiles of 32 sequences, two passes
+over the items, gate and log-sum-exp.  Against the fp64 oracle, bar 1e-2 (bf16 operands), lse 2e-2 absolute."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import mlra_oracle as orc
+from paper_2603_02188_amd import binding as mlra
+from paper_2603_02188_amd import inputs as gen
+
+from gpu_util import device_cache, device_queries_weights, host, max_rel_err, oracle_views, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,nb,h,n_max,slots,gated", [
+    (1, 1, 128, 5000, 40, True), (2, 1, 16, 2100, 17, False), (3, 2, 128, 1000, 8, True), (16, 4, 128, 300, 3, True),
+    (33, 4, 16, 520, 3, True), (64, 4, 16, 90, 1, True), (33, 8, 128, 70, 1, False), (66, 4, 24, 65, 1, True)])
+def test_chunks_tiles_and_gate(batch, nb, h, n_max, slots, gated):
+    wl = gen.WORKLOADS["C5"].scaled(name="merge", batch=batch, n_min=0, n_max=n_max, n_blocks=nb, h=h, index=3000 + batch)
+    lens = np.random.default_rng(batch).integers(0, n_max + 1, size=batch).astype(np.int32)
+    lens[0], lens[-1] = (n_max, 0) if batch > 1 else (n_max, n_max)
+    info = mlra.mlra_decode_plan_info(batch, h, 128, 1, nb, 128, 64, 64, -(-n_max // 64) * 64, torch.bfloat16)
+    print(f"[case] merge B={batch} NB={nb} h={h} n_max={n_max} gated={gated} {info}", flush=True)
+    assert info["merge_mfma"] and info["chunk_slots"] == slots
+    inp = gen.make_decode_inputs(wl, poison=True, seq_lens=lens)
+    cache = device_cache(inp)
+    q_nope, q_rope, w_uk, w_uv = device_queries_weights(inp)
+    q_abs = mlra.mlra_absorb_q(q_nope, w_uk)
+    lse = torch.full((batch, nb, h), float("nan"), device="cuda")
+    gate = np.random.default_rng(7).uniform(0.0, 1.0, size=(batch, h, 128)).astype(np.float32)
+    gate16 = gen.to_storage(gate, "bf16")
+    kw = dict(out_dtype=torch.float32, lse=lse)
+    if gated:
+        out = mlra.mlra_decode_attn_gated(cache, q_abs, q_rope, w_uv, to_device(gate16, "bf16"), wl.tau, 0.5, **kw)
+    else:
+        out = mlra.mlra_decode_attn(cache, q_abs, q_rope, w_uv, wl.tau, 0.5, **kw)
+    torch.cuda.synchronize()
+    v = oracle_views(inp)
+    ref, ref_lse = orc.mlra_decode_batch(v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"],
+                                         v["q_rope"], v["w_uk"], v["w_uv"], wl.tau, 0.5, return_lse=True)
+    if gated:
+        ref = ref * gen.to_f64(gate16, "bf16")
+    err = max_rel_err(host(out), ref)
+    print(f"       max rel err {err:.3e}", flush=True)
+    assert err <= 1e-2
+    got, live = host(lse), np.isfinite(ref_lse)
+    assert np.array_equal(np.isfinite(got), live) and np.max(np.abs(got[live] - ref_lse[live])) <= 2e-2
+
+
+@pytest.mark.parametrize("batch,h,n_max", [(1, 64, 5000), (5, 128, 2000), (33, 16, 300)])
+def test_fp32_partials(batch, h, n_max):
+    wl = gen.WORKLOADS["C5"].scaled(name="merge-mla", batch=batch, n_min=1, n_max=n_max, h=h, index=3100 + batch)
+    inp = gen.make_decode_inputs(wl, poison=True)
+    one = gen.as_single_latent(inp)
+    info = mlra.mlra_decode_plan_info(batch, h, 128, 1, 1, 512, 64, 64, n_max, torch.bfloat16)
+    print(f"[case] merge fp32 partials B={batch} h={h} {info}", flush=True)
+    assert info["kernel"] == "mfma-mla" and info["merge_mfma"]
+    cache = device_cache(one)
+    q_nope, q_rope, w_uk, w_uv = device_queries_weights(one)
+    out = mlra.mla_decode_attn(cache, mlra.mlra_absorb_q(q_nope, w_uk), q_rope, w_uv, wl.tau, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    v = oracle_views(one)
+    ref = orc.mlra_decode_batch(v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"],
+                                v["q_rope"], v["w_uk"], v["w_uv"], wl.tau, 1.0)
+    assert max_rel_err(host(out), ref) <= 1e-2
