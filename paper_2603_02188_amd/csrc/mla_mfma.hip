@@ -1,9 +1,9 @@
 // MFMA decode kernel for the MLA comparison: one 512-dim latent plus a 64-dim RoPE key per token
 // (Section 2.1, Steps 1-3 with d_c = 512; bf16 caches).
 //
-// One workgroup (4 wavefronts) owns one (sequence, context chunk, 64 query heads) and walks the chunk in
-// tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads, four stages deep
-// (three tiles in flight while one is worked on).  The two products split the work differently:
+// One workgroup (4 wavefronts, two workgroups per CU) owns one (sequence, context chunk, 64 query heads) and walks the
+// chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads, two stages deep (one tile
+// in flight while one is worked on).  The two products split the work differently:
 //   * scores and softmax by heads: wave w owns heads [16 w, 16 w + 16) and computes their complete scores
 //     S^T = [C | K^R] [q~ | q^R]^T over all 576 channels with 16x16x32 MFMAs (tokens x heads), so the
 //     softmax of a head is computed once, by one wave, with its running maximum and sum in that wave;
@@ -14,6 +14,14 @@
 // product's B operand, together with the factors by which a wave lowered the weight of its heads'
 // history when their running maximum grew (refreshed lazily, so almost always none).  Two workgroup
 // barriers per tile: one hands the landed tile and the freed stage around, one publishes P^T.
+// A wave's chain through a tile (LDS latencies, softmax, the hand-overs) is 2.5 times the 1088 cycles of matrix pipe in
+// it, so the second workgroup of the CU matters more than deeper buffering: it takes 256 registers per wave, all of them
+// (accumulators 128, queries 72, the rest operands in flight), and whatever can be recomputed is, because a spill inside
+// the loop also waits for the tile loads.  64 heads x 512 + 64 channels, 256 sequences of 2176 tokens x 128 heads:
+// 222 -> 191 us against one workgroup per CU with four stages (128 sequences of 512 to 8192 in chunks: 274 -> 228;
+// one workgroup per CU, 128 sequences of 4352: 221 -> 217).  Measured and not kept: 16-token tiles in four stages
+// (198 / 237 / 250 us), two groups of four waves one barrier apart in one workgroup (223 / 260 / 215), 32 heads x 16
+// tokens per wave (216 / 264 / 214), the channels of the scores split over two waves (224 / 265 / 298).
 // The two head halves of a sequence are placed on the same XCD (ids 8 apart), so the cache is fetched
 // from HBM once.  Partials go to the workspace in the layout of the MLRA path with n_blocks = 1,
 // d_cb = 512.
@@ -30,12 +38,12 @@ constexpr int kMHeads = 64;                        // query heads per workgroup
 constexpr int kMLatBytes = kMTok * kMDc * 2;       // 32 KiB
 constexpr int kMRopeBytes = kMTok * kDr * 2;       //  4 KiB
 constexpr int kMStage = kMLatBytes + kMRopeBytes;  // 36 KiB
-constexpr int kMStages = 4;
-constexpr int kMPOff = kMStages * kMStage;         // P^T: [2 tiles][2 head tiles][2 token halves][64 lanes][16 B]
+constexpr int kMStages = 2;
+constexpr int kMPOff = kMStages * kMStage;         // P^T: [2 head tiles][2 token halves][64 lanes][16 B]
 constexpr int kMPBytes = 4 * 1024;
-constexpr int kMAOff = kMPOff + 2 * kMPBytes;      // rescale factors: [2 tiles][64 heads] floats, then [2][4] flags
-constexpr int kMFOff = kMAOff + 2 * kMHeads * 4;
-constexpr int kMLds = kMFOff + 2 * 4 * 4;          // 156,192 bytes
+constexpr int kMAOff = kMPOff + kMPBytes;          // rescale factors: [64 heads] floats, then [4 waves] flags
+constexpr int kMFOff = kMAOff + kMHeads * 4;
+constexpr int kMLds = kMFOff + 4 * 4;              // 78,096 bytes: two workgroups per CU
 constexpr int kMLoads = 9;                         // direct-to-LDS loads per wave and tile
 
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
@@ -68,7 +76,7 @@ __device__ __forceinline__ float head_sum(float v) {
   return a + b;
 }
 
-__global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
+__global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // workgroup -> (sequence, chunk, head half); the halves of one (sequence, chunk) get ids 8 apart
   const int n_hg = (p.h + kMHeads - 1) / kMHeads;
@@ -133,40 +141,41 @@ __global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
   const const_i32_ptr pt_row = (const_i32_ptr)(p.page_table + (size_t)seq * p.max_pages);
   const size_t lat_page_bytes = (size_t)p.page_size * (kMDc * 2);
   const size_t rope_page_bytes = (size_t)p.page_size * (kDr * 2);
-  unsigned lat_voff[8];
+  // (the swizzle of a row is uniform, so the lane offset of load i is one exclusive or away from 16 lane)
+  // Tiles are issued in order, nine loads each (0..7: latent rows, 8: the RoPE rows).  Pages hold whole tiles, and the id
+  // of the page after the current one is always loaded already.
+  int iss_tok = t0, iss_page_at = t0 / p.page_size, iss_slot = t0 % p.page_size, iss_stage = 0;
+  unsigned iss_page = (unsigned)pt_row[iss_page_at];
+  unsigned iss_page_next = (unsigned)pt_row[min(iss_page_at + 1, p.max_pages - 1)];
+  const unsigned lane16 = lane * 16;
+  auto issue_tile = [&]() {
+    const char* const lat = (const char*)p.latent + iss_page * lat_page_bytes + (size_t)iss_slot * (kMDc * 2);
+    const char* const rope = (const char*)p.rope + iss_page * rope_page_bytes + (size_t)iss_slot * (kDr * 2);
+    const int last = min(kMTok, t1 - iss_tok) - 1;     // rows past it re-read it (finite values, weight 0 later)
+    const unsigned dst = lds_base + iss_stage * kMStage;
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    lat_voff[i] = (lane >> 4) * 256 + (((lane & 15) ^ lat_swz(8 * wave + i)) << 4);
-  const int rope_t = 8 * wave + (lane >> 3);
-  // A tile is issued in parts so that the parts can sit behind different MFMAs: issue_begin (scalar
-  // address work), nine loads (0..7: latent rows, 8: the RoPE rows).
-  const char* iss_lat = nullptr;
-  const char* iss_rope = nullptr;
-  unsigned iss_dst = 0;
-  int iss_last = 0;
-  auto issue_begin = [&](int jj) {
-    const int tok = t0 + jj * kMTok;
-    const unsigned page = (unsigned)pt_row[min(tok / p.page_size, p.max_pages - 1)];
-    const int slot = tok % p.page_size;
-    iss_lat = (const char*)p.latent + page * lat_page_bytes + (size_t)slot * (kMDc * 2);
-    iss_rope = (const char*)p.rope + page * rope_page_bytes + (size_t)slot * (kDr * 2);
-    iss_last = min(kMTok, t1 - tok) - 1;     // rows past it re-read it (finite values, weight 0 later)
-    iss_dst = lds_base + (jj % kMStages) * kMStage;
-  };
-  auto issue_part = [&](int i) {
-    if (i < 8) {
-      const int t = 8 * wave_u + i;
-      set_m0(iss_dst + t * 1024);
-      lds_dma16<0>(iss_lat + (size_t)min(t, iss_last) * 1024, lat_voff[i]);
-    } else {
-      set_m0(iss_dst + kMLatBytes + wave_u * 1024);
-      lds_dma16<0>(iss_rope, (unsigned)min(rope_t, iss_last) * (kDr * 2) + (((lane & 7) ^ rope_swz(rope_t)) << 4));
+    for (int i = 0; i < kMLoads; ++i) {
+      unsigned l16 = lane16;
+      asm volatile("" : "+v"(l16));    // (or the offsets of all nine loads would be kept in registers: there are none left)
+      if (i < 8) {
+        const int t = 8 * wave_u + i;
+        set_m0(dst + t * 1024);
+        lds_dma16<0>(lat + (size_t)min(t, last) * 1024, l16 ^ (unsigned)(lat_swz(t) << 4));
+      } else {
+        const int t = 8 * wave_u + (l16 >> 7);       // lane / 8 rows on
+        set_m0(dst + kMLatBytes + wave_u * 1024);
+        lds_dma16<0>(rope, (unsigned)min(t, last) * (kDr * 2) + ((l16 & 0x70) ^ (rope_swz(t) << 4)));
+      }
     }
-  };
-  auto issue_tile = [&](int jj) {
-    issue_begin(jj);
-#pragma unroll
-    for (int i = 0; i < kMLoads; ++i) issue_part(i);
+    iss_tok += kMTok;
+    iss_slot += kMTok;
+    iss_stage ^= 1;
+    if (iss_slot == p.page_size) {
+      iss_slot = 0;
+      ++iss_page_at;
+      iss_page = iss_page_next;
+      iss_page_next = (unsigned)pt_row[min(iss_page_at + 1, p.max_pages - 1)];
+    }
   };
 
   // ---- per-lane LDS read offsets inside a stage (XOR swizzle, see mfma_tile.h and decode_mfma.hip).
@@ -179,21 +188,14 @@ __global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
   // 4.6 instead of 8 cycles per read).  Output rows 4 q4 .. + 3 are then tokens 4 q4t .. + 3.
   const int k_tok = c16 ^ ((c16 & 4) << 1);
   const int q4t = q4 ^ ((q4 & 1) << 1);
-  unsigned k_lat_off[2], k_rope_off[2];
-#pragma unroll
-  for (int th = 0; th < 2; ++th) {
-    const int t = 16 * th + k_tok;
-    k_lat_off[th] = t * 1024 + ((q4 ^ lat_swz(t)) << 4);                         // ^ ((ks % 4) << 6), + 256 (ks / 4)
-    k_rope_off[th] = kMLatBytes + t * (kDr * 2) + ((q4 ^ rope_swz(t)) << 4);     // ^ (kr << 6)
-  }
-  unsigned v_off[2];                                                          // ^ (mt << 6), + 16 KiB ss
+  // (the swizzles repeat every 16 tokens: token half th is th * 16 rows further on)
+  const unsigned k_lat_off = k_tok * 1024 + ((q4 ^ lat_swz(k_tok)) << 4);                      // ^ ((ks % 4) << 6), + 256 (ks / 4)
+  const unsigned k_rope_off = kMLatBytes + k_tok * (kDr * 2) + ((q4 ^ rope_swz(k_tok)) << 4);  // ^ (kr << 6)
+  // Values: lane group's token ta = 8 half + 4 g + k of 16; half 1 is 8 rows on and flips bit 1 of the swizzle.
+  unsigned v_off;                                                             // ^ (mt << 6), + 16 KiB ss
   {
-    const int k = (lane & 15) >> 2, seg = lane & 3, hb = (lane >> 4) & 1;
-#pragma unroll
-    for (int half = 0; half < 2; ++half) {
-      const int ta = 8 * half + 4 * g + k;
-      v_off[half] = ta * 1024 + wave * 256 + (((2 * hb + (seg >> 1)) ^ lat_swz(ta)) << 4) + ((seg & 1) << 3);
-    }
+    const int k = (lane & 15) >> 2, seg = lane & 3, hb = (lane >> 4) & 1, ta = 4 * g + k;
+    v_off = ta * 1024 + wave * 256 + (((2 * hb + (seg >> 1)) ^ lat_swz(ta)) << 4) + ((seg & 1) << 3);
   }
   // P^T: the B operand (head tile w / 2, token half th) pairs with the transposed value operand, whose
   // lane group g holds tokens 4 g .. 4 g + 3 and 8 + 4 g .. 8 + 4 g + 3 of the 16.  This lane's four
@@ -210,39 +212,41 @@ __global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) zacc[mt][nt][i] = 0.f;
 
-  for (int jj = 0; jj < kMStages - 1 && jj < ntiles; ++jj) issue_tile(jj);
+  issue_tile();
   for (int j = 0; j < ntiles; ++j) {
-    // tile j landed in this wave's share (the tiles issued after it may still be in flight) ...
-    if (j + 2 < ntiles) wait_vm_lgkm<2 * kMLoads>();
-    else if (j + 1 < ntiles) wait_vm_lgkm<kMLoads>();
-    else wait_vm_lgkm<0>();
+    // tile j landed in this wave's share ...
+    wait_vm_lgkm<0>();
     // ... and in everybody's; every wave is also done with tile j-1, whose stage is refilled now
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    const bool refill = j + kMStages - 1 < ntiles;     // its loads go out behind the value MFMAs below
-    if (refill) issue_begin(j + kMStages - 1);
-    const unsigned base = lds_base + (j % kMStages) * kMStage;
-    const int par = j & 1;
+    if (j + 1 < ntiles) issue_tile();
+    const unsigned base = lds_base + (j & 1) * kMStage;
 
-    // ---- scores of this wave's 16 heads: 36 MFMAs, operand reads twelve ahead
+    // ---- scores of this wave's 16 heads: 36 MFMAs
     f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
     {
       auto k_read = [&](int i) {     // i = 2 ks + th
         const int ks = i >> 1, th = i & 1;
-        const unsigned addr = ks < 16 ? ((base + k_lat_off[th] + (ks >> 2) * 256) ^ ((ks & 3) << 6))
-                                      : ((base + k_rope_off[th]) ^ ((ks - 16) << 6));
+        const unsigned addr = ks < 16 ? ((base + k_lat_off) ^ ((ks & 3) << 6)) + (ks >> 2) * 256 + th * 16 * 1024
+                                      : ((base + k_rope_off) ^ ((ks - 16) << 6)) + th * 16 * (kDr * 2);
         return *(lds_bf16x8_ptr)(size_t)addr;
       };
-      constexpr int kAhead = 12;
-      bf16x8 ka[kAhead];
+      // (the order is pinned: left to itself, the scheduler reads one operand at a time and waits for it)
+      constexpr int kAhead = 5;
+      bf16x8 ka[36];
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < kAhead; ++i) ka[i] = k_read(i);
+      for (int i = 0; i < 36; ++i) ka[i] = k_read(i);
 #pragma unroll
-      for (int i = 0; i < 36; ++i) {
-        const bf16x8 cur = ka[i % kAhead];
-        if (i + kAhead < 36) ka[i % kAhead] = k_read(i + kAhead);
-        s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(cur, qreg[i >> 1], s[i & 1], 0, 0, 0);
+      for (int i = 0; i < 36; ++i) s[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i], qreg[i >> 1], s[i & 1], 0, 0, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, kAhead, 0);
+#pragma unroll
+      for (int i = 0; i < 36 - kAhead; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
       }
+      __builtin_amdgcn_sched_group_barrier(0x008, kAhead, 0);
+      __builtin_amdgcn_sched_barrier(0);
     }
 
     // ---- softmax of the 16 heads (running maximum refreshed lazily, see decode_mfma.hip)
@@ -272,33 +276,37 @@ __global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
       }
       typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
       const bf16x4 pk = {(__bf16)pe[0], (__bf16)pe[1], (__bf16)pe[2], (__bf16)pe[3]};
-      *(bf16x4*)(smem + kMPOff + par * kMPBytes + th * 1024 + p_wr_off) = pk;
+      *(bf16x4*)(smem + kMPOff + th * 1024 + p_wr_off) = pk;
     }
-    if (q4 == 0) ((float*)(smem + kMAOff))[par * kMHeads + 16 * wave + c16] = alpha;
-    if (lane == 0) ((int*)(smem + kMFOff))[par * 4 + wave] = any_grow ? 1 : 0;
+    if (q4 == 0) ((float*)(smem + kMAOff))[16 * wave + c16] = alpha;
+    if (lane == 0) ((int*)(smem + kMFOff))[wave_u] = any_grow ? 1 : 0;
 
-    // ---- the transposed value operands of this wave's channels do not depend on P^T: fetch them first
-    bf16x8 va[2][4];
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");     // P^T, the factors and the flags of every wave are visible
+
+    // P^T and value operands of the first token half are on their way while the flags are looked at
+    bf16x8 pb[2], va[4];
+    auto read_half = [&](int ss) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) {
-      const lds_byte_ptr lo_p = (lds_byte_ptr)(size_t)((base + v_off[0]) ^ (mt << 6));
-      const lds_byte_ptr hi_p = (lds_byte_ptr)(size_t)((base + v_off[1]) ^ (mt << 6));
+      for (int nt = 0; nt < 2; ++nt)
+        pb[nt] = *(const bf16x8*)(smem + kMPOff + (nt * 2 + ss) * 1024 + lane * 16);
 #pragma unroll
-      for (int ss = 0; ss < 2; ++ss) {
-        const short4v lo = lds_tr16(lo_p + ss * 16 * 1024);
-        const short4v hi = lds_tr16(hi_p + ss * 16 * 1024);
-        va[ss][mt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      for (int mt = 0; mt < 4; ++mt) {
+        const short4v lo = lds_tr16((lds_byte_ptr)(size_t)((base + v_off) ^ (mt << 6)) + ss * 16 * 1024);
+        const short4v hi = lds_tr16((lds_byte_ptr)(size_t)((base + v_off) ^ (mt << 6) ^ 32) + (ss * 16 + 8) * 1024);
+        va[mt] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
       }
-    }
-    __syncthreads();     // P^T, the factors and the flags of every wave are visible
-
+    };
+    const int4 fl = *(const int4*)(smem + kMFOff);
+    read_half(0);
+    __builtin_amdgcn_sched_barrier(0);
     // ---- a head's history loses weight when its maximum grew: the owner of the head said by how much
     {
-      const int4 fl = *(const int4*)(smem + kMFOff + par * 16);
       if (__builtin_amdgcn_readfirstlane(fl.x | fl.y | fl.z | fl.w)) {
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) {
-          const float a_h = ((const float*)(smem + kMAOff))[par * kMHeads + nt * 32 + c32];
+          const float a_h = ((const float*)(smem + kMAOff))[nt * 32 + c32];
 #pragma unroll
           for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
@@ -307,27 +315,15 @@ __global__ __launch_bounds__(256) void mla_mfma_kernel(MfmaParams p) {
       }
     }
     // ---- values: Z_w^T += C_w^T P^T
-    bf16x8 pb[2][2];
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int ss = 0; ss < 2; ++ss)
-        pb[nt][ss] = *(const bf16x8*)(smem + kMPOff + par * kMPBytes + (nt * 2 + ss) * 1024 + lane * 16);
-#pragma unroll
-    for (int ss = 0; ss < 2; ++ss)
+    for (int ss = 0; ss < 2; ++ss) {
+      if (ss == 1) read_half(1);
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) {
-        zacc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ss][mt], pb[0][ss], zacc[mt][0], 0, 0, 0);
-        zacc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[ss][mt], pb[1][ss], zacc[mt][1], 0, 0, 0);
-        // the loads of tile j+3 into the stage tile j-1 left (free since the barrier at the top), one or
-        // two behind each pair of MFMAs: the CU's address unit takes about 16 cycles per load
-        if (refill) {
-          const int k = ss * 4 + mt;       // 0..7
-          issue_part(k);
-          if (k == 7) issue_part(8);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+        zacc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[mt], pb[0], zacc[mt][0], 0, 0, 0);
+        zacc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[mt], pb[1], zacc[mt][1], 0, 0, 0);
       }
+    }
   }
 
   // ---- write the chunk's partial: every wave its 128 channels of all 64 heads, and (m, l) of its 16 heads

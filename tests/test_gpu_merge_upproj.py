@@ -65,3 +65,26 @@ def test_fp32_partials(batch, h, n_max):
     ref = orc.mlra_decode_batch(v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"],
                                 v["q_rope"], v["w_uk"], v["w_uv"], wl.tau, 1.0)
     assert max_rel_err(host(out), ref) <= 1e-2
+
+
+# the MLA kernel: chunks of one tile and less, both stages, ragged ends, page turns at every tile and at every third,
+# head counts below, at and above the 64 of a workgroup
+@pytest.mark.parametrize("h,page,lens", [(64, 32, [1, 31, 32, 33, 64, 65, 0, 400]), (128, 96, [95, 96, 97, 130, 1000]),
+                                         (70, 64, [63, 129, 2]), (16, 160, [3000, 161])])
+def test_mla_tiles_and_pages(h, page, lens):
+    wl = gen.WORKLOADS["C5"].scaled(name="mla-tiles", batch=len(lens), n_min=0, n_max=max(lens), h=h, page_size=page,
+                                    index=3200 + h)
+    one = gen.as_single_latent(gen.make_decode_inputs(wl, poison=True, seq_lens=np.array(lens, dtype=np.int32)))
+    print(f"[case] mla tiles h={h} page={page} lens={lens}", flush=True)
+    cache = device_cache(one)
+    q_nope, q_rope, w_uk, w_uv = device_queries_weights(one)
+    lse = torch.full((len(lens), 1, h), float("nan"), device="cuda")
+    out = mlra.mla_decode_attn(cache, mlra.mlra_absorb_q(q_nope, w_uk), q_rope, w_uv, wl.tau, out_dtype=torch.float32,
+                               lse=lse)
+    torch.cuda.synchronize()
+    v = oracle_views(one)
+    ref, ref_lse = orc.mlra_decode_batch(v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"],
+                                         v["q_rope"], v["w_uk"], v["w_uv"], wl.tau, 1.0, return_lse=True)
+    assert max_rel_err(host(out), ref) <= 1e-2
+    got, live = host(lse), np.isfinite(ref_lse)
+    assert np.array_equal(np.isfinite(got), live) and np.max(np.abs(got[live] - ref_lse[live])) <= 2e-2
