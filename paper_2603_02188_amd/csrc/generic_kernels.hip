@@ -328,39 +328,65 @@ int launch_gqa_generic(const GqaArgs& a) {
   return check_launch();
 }
 
+// Merge of the chunks' partials: one wavefront per (sequence, head).  The chunks' (m, l) are reduced across the lanes,
+// their weights 2^(m_k - m*) / L wait in LDS, and the rows are added four channels per lane (element by element if the
+// rows are not made of runs of four).  One thread per channel that walked the chunks' (m, l) serially took, on one
+// sequence of 16K tokens with 8 KV heads, 7 us longer (whole call 33 -> 26 us).
 template <typename TO>
 __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict__ part_o,
                                                         const float* __restrict__ part_ml,
                                                         const int32_t* __restrict__ seq_lens, TO* __restrict__ out,
                                                         int h, int d_h, int n_splits, int chunk) {
-  const int head = blockIdx.x, s = blockIdx.y;
+  extern __shared__ float wtab[];          // [4 waves][n_splits]
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, head = blockIdx.x * 4 + wave, s = blockIdx.y;
+  if (head >= h) return;                   // (no barrier follows: a wave reads only what it wrote)
   const int n = seq_lens[s];
   const int active = min(n_splits, (n + chunk - 1) / chunk);
-  const size_t unit0 = (size_t)s * n_splits;
+  const size_t unit0 = (size_t)s * n_splits, stride = (size_t)h * d_h;
+  const float* const ml = part_ml + (unit0 * h + head) * 2;
+  float* const w = wtab + wave * n_splits;
   float m_star = kNegBig;
-  for (int k = 0; k < active; ++k) m_star = fmaxf(m_star, part_ml[((unit0 + k) * h + head) * 2]);
+  for (int k = lane; k < active; k += 64) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);
+  m_star = wave_max(m_star);
   float L = 0.f;
-  for (int k = 0; k < active; ++k) {
-    const float* ml = part_ml + ((unit0 + k) * h + head) * 2;
-    L += exp2f(ml[0] - m_star) * ml[1];
+  for (int k = lane; k < active; k += 64) {
+    w[k] = exp2f(ml[(size_t)k * h * 2] - m_star);
+    L += w[k] * ml[(size_t)k * h * 2 + 1];
   }
+  L = wave_sum(L);
   const float inv = L > 0.f ? 1.f / L : 0.f;
-  for (int c = threadIdx.x; c < d_h; c += 256) {
-    float z = 0.f;
-    for (int k = 0; k < active; ++k)
-      z += exp2f(part_ml[((unit0 + k) * h + head) * 2] - m_star) * part_o[((unit0 + k) * h + head) * d_h + c];
-    store_f32(out, ((size_t)s * h + head) * d_h + c, z * inv);
+  __builtin_amdgcn_wave_barrier();
+  const float* const po = part_o + (unit0 * h + head) * d_h;
+  const size_t o = ((size_t)s * h + head) * d_h;
+  if (d_h % 4 == 0) {
+    for (int c = lane * 4; c < d_h; c += 256) {
+      float z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 8
+      for (int k = 0; k < active; ++k) {
+        const float4 v = *(const float4*)(po + k * stride + c);
+        z[0] += w[k] * v.x; z[1] += w[k] * v.y; z[2] += w[k] * v.z; z[3] += w[k] * v.w;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) store_f32(out, o + c + e, z[e] * inv);
+    }
+  } else {
+    for (int c = lane; c < d_h; c += 64) {
+      float z = 0.f;
+      for (int k = 0; k < active; ++k) z += w[k] * po[k * stride + c];
+      store_f32(out, o + c, z * inv);
+    }
   }
 }
 
 int launch_gqa_merge(const GqaArgs& a) {
-  dim3 grid(a.h, a.batch);
+  const dim3 grid((a.h + 3) / 4, a.batch);
+  const size_t lds = (size_t)4 * a.plan.n_splits * sizeof(float);   // at most one chunk per CU and sequence: 4 KiB
   if (a.out_dtype == MLRA_BF16)
-    gqa_merge_kernel<bf16_t><<<grid, 256, 0, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (bf16_t*)a.out, a.h, a.d_h,
-                                                         a.plan.n_splits, a.plan.chunk_tokens);
+    gqa_merge_kernel<bf16_t><<<grid, 256, lds, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (bf16_t*)a.out, a.h, a.d_h,
+                                                           a.plan.n_splits, a.plan.chunk_tokens);
   else
-    gqa_merge_kernel<float><<<grid, 256, 0, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (float*)a.out, a.h, a.d_h,
-                                                        a.plan.n_splits, a.plan.chunk_tokens);
+    gqa_merge_kernel<float><<<grid, 256, lds, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (float*)a.out, a.h, a.d_h,
+                                                          a.plan.n_splits, a.plan.chunk_tokens);
   return check_launch();
 }
 

@@ -541,7 +541,7 @@ int gqa_decode_attn(const void* k_pool, const void* v_pool, const int32_t* page_
   a.out_dtype = out_dtype;
   a.stream = (hipStream_t)stream;
   int st = use_mfma ? launch_gqa_mfma(a) : launch_gqa_generic(a);
-  if (st != MLRA_OK) return st;
+  if (st != MLRA_OK || (use_mfma && gqa_mfma_writes_output(a))) return st;
   return launch_gqa_merge(a);
 }
 

@@ -166,6 +166,7 @@ struct GqaArgs {
 int launch_gqa_generic(const GqaArgs& a);
 bool gqa_mfma_supported(const GqaArgs& a);
 int launch_gqa_mfma(const GqaArgs& a);
+bool gqa_mfma_writes_output(const GqaArgs& a);   // nothing is left for launch_gqa_merge
 int launch_gqa_merge(const GqaArgs& a);
 
 // ---- pre-attention of the new token (pre_attn.hip) ----------------------------------------------
