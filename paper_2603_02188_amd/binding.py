@@ -130,17 +130,26 @@ def _dt(t: torch.dtype) -> int:
     raise TypeError(f"libmlra supports bfloat16 and float32, not {t}")
 
 
+# Pointers and streams are passed as plain integers (the argtypes convert them), and the current stream is asked for as
+# its handle: a decode step is three calls, and a c_void_p object per argument and a torch.cuda.Stream object per call
+# were 10 of the 33 us of host work in it (a step on one short sequence is bound by the host).
 def _ptr(t: Optional[torch.Tensor]):
     if t is None:
         return None
     if not t.is_cuda or not t.is_contiguous():
         raise ValueError("libmlra takes contiguous device tensors")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
-def _stream(stream) -> ctypes.c_void_p:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
+def _stream(stream) -> int:
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is None or not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return _current_raw_stream(torch._C._cuda_getDevice())
 
 
 @dataclass
@@ -153,13 +162,15 @@ class Cache:
     seq_lens: torch.Tensor    # [batch] int32
 
     def struct(self) -> _CacheStruct:
-        P, NB, ps, dcb = self.latent.shape
-        assert self.rope.shape[0] == P and self.rope.shape[1] == ps
-        assert self.page_table.dtype == torch.int32 and self.seq_lens.dtype == torch.int32
-        assert self.rope.dtype == self.latent.dtype
-        return _CacheStruct(self.latent.data_ptr(), self.rope.data_ptr(), self.page_table.data_ptr(),
-                            self.seq_lens.data_ptr(), P, ps, self.page_table.shape[1], NB, dcb,
-                            self.rope.shape[2], _dt(self.latent.dtype))
+        latent, rope, table, lens = self.latent, self.rope, self.page_table, self.seq_lens
+        P, NB, ps, dcb = latent.shape
+        rope_pages, rope_ps, d_r = rope.shape
+        assert rope_pages == P and rope_ps == ps
+        assert table.dtype == torch.int32 and lens.dtype == torch.int32
+        dtype = latent.dtype
+        assert rope.dtype == dtype
+        return _CacheStruct(latent.data_ptr(), rope.data_ptr(), table.data_ptr(), lens.data_ptr(), P, ps,
+                            table.shape[1], NB, dcb, d_r, _dt(dtype))
 
     @property
     def max_seq_len(self) -> int:
