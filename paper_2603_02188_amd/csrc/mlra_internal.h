@@ -102,7 +102,7 @@ struct DecodeArgs {
   int32_t* unit_tab;   // [batch * n_splits] active (sequence, chunk) pairs, then -1 (workspace); same
   bool balanced;       // chunk lengths follow the sequence lengths (chunk_tab) instead of plan.chunk_tokens
   bool rows_bf16;      // the decode kernel writes each chunk's partial as a normalised bf16 row z / l (the MLRA
-                       // MFMA kernels); otherwise fp32 partials Z (the MLA and the generic kernels)
+                       // MFMA kernels); otherwise fp32 partials Z (the MLA and the fp32 kernels)
   SplitPlan plan;
   int dtype;
   hipStream_t stream;

@@ -171,7 +171,8 @@ __global__ __launch_bounds__(256) void absorb_q_mfma_kernel(const bf16_t* __rest
 //            (row = sequence).  kDirect: every sequence has one chunk and the decode kernel has normalised and rounded
 //            its row, which is only copied.  kRows / kItems: z = sum_k w_k z_k over the chunks, whose partials are
 //            normalised bf16 rows / fp32 Z; a thread takes U items (sequence, 8 channels) at a time and the first
-//            KK chunks of each are in flight while sixteen lanes per (sequence, block) turn the chunks' (m, l) into the
+//            KK chunks of each are in flight while sixteen lanes (a thread, if there are at most
+//            four slots) per (sequence, block) turn the chunks' (m, l) into the
 //            weights w_k = 2^(m_k - m*) (l_k) / L in LDS and write the log-sum-exp;
 //   phase 2: out[seq][j] = sum_r z[seq][r] W^UV[r][head*128 + j]; W^UV goes through LDS 128 rows at a time (the rows
 //            after the next 128 are fetched into the registers that were just stored) and reaches the MFMA B operand
@@ -180,7 +181,8 @@ __global__ __launch_bounds__(256) void absorb_q_mfma_kernel(const bf16_t* __rest
 // One kernel for all three forms held the registers of the largest (448), so that a CU had one workgroup.
 // Kernel times, before -> after the forms were split (128 heads, 512 latent channels): 128 sequences with gate and
 // log-sum-exp 41 -> 19 us, 64 sequences 15.6 -> 13.0, 4 sequences of up to 128K in 32 chunk slots 22.4 -> 17.4, one
-// sequence in 12 chunks 11.5 -> 8.9, fp32 partials of 128 sequences in 4 slots 32.9 -> 26.9.
+// sequence in 12 chunks 11.5 -> 8.9, fp32 partials of 128 sequences in 4 slots 32.9 -> 26.9.  Lane groups for two slots as
+// well cost a step on 44 decode units 4 us (57.0 against 52.6): the shuffles of a pair take longer than its two loads.
 // ------------------------------------------------------------------------------------------------
 constexpr int kWRows = 128;       // W^UV rows in LDS at a time (32 KiB); twice as many in registers
 enum MergeMode { kDirect, kRows, kItems };
@@ -294,9 +296,36 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
       load_chunks(0);
       if (!have_weights) {     // (uniform) weights of all (sequence, block) pairs, once
         have_weights = true;
+        const int n_pairs = n_valid * n_blocks;
+        if constexpr (KK == 2) {
+          // at most four slots: one thread per pair, all of them in its registers
+          for (int pair = tid; pair < n_pairs; pair += 256) {
+            const int ps = pair / n_blocks, b = pair - ps * n_blocks, seq = m0 + ps, active = active_chunks(seq);
+            const float* ml = part_ml + ((((size_t)seq * nb_total + b0 + b) * n_splits) * h + head) * 2;
+            float2 got[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) got[k] = *(const float2*)(ml + (size_t)min(k, n_splits - 1) * h * 2);
+            float m_star = kNegBig, L = 0.f, w[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (k < active) m_star = fmaxf(m_star, got[k].x);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              w[k] = k < active ? exp2f(got[k].x - m_star) : 0.f;
+              if (k < active) L += w[k] * got[k].y;
+              if (MODE == kRows) w[k] *= got[k].y;
+            }
+            const float inv = L > 0.f ? 1.f / L : 0.f;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+              if (k < active) wtab[ps * units_per_seq + b * n_splits + k] = w[k] * inv;
+            if (lse)
+              lse[((size_t)seq * nb_total + b0 + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
+          }
+        } else {
         // (four pairs of a lane group at a time, so that their loads overlap; chunk l16 of each stays in a register,
         // and only chunks from 16 on are read twice)
-        const int l16 = lane & 15, n_pairs = n_valid * n_blocks;
+        const int l16 = lane & 15;
         for (int pair0 = tid >> 4; pair0 < n_pairs; pair0 += 64) {
           float2 first[4];
           int active[4];
@@ -337,6 +366,7 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
             if (lse && l16 == 0)
               lse[((size_t)seq * nb_total + b0 + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
           }
+        }
         }
         __syncthreads();
       }
@@ -491,7 +521,8 @@ template <typename TO>
 static int launch_merge_typed(const DecodeArgs& a, dim3 grid, int spw) {
   // U items per thread and step: many chunks (small batches) go one item per thread with all loads on its chunks, few
   // chunks several items
-  // (at most four slots: the forms that leave a batch of nearly equal lengths uncut, one or two of them are used)
+  // (KK = 2: at most four slots.  Among them are the forms that leave a batch of nearly equal lengths uncut, of which one
+  // or two are used)
   if (a.rows_bf16) {
     if (a.plan.n_splits == 1) return launch_merge_as<TO, kDirect, 8, 1>(a, grid, spw);
     if (a.plan.n_splits > 8) return launch_merge_as<TO, kRows, 1, 16>(a, grid, spw);
