@@ -35,11 +35,14 @@ __device__ __forceinline__ f32x4 cut_row4(f32x4 v, int k, int len) {
 // absorb_q.  One workgroup per (head, block, 16 sequences); wave w produces channel tiles w and w + 4 of every eight.
 // Query rows are the A operand, weight rows (one per latent channel, contiguous along d_h) the B operand; k is dealt
 // as 16 i + 4 q + j (q = lane / 16, j = step), so that both are read four elements at a time, straight from global
-// memory: a weight element is used by one workgroup only, and eight k groups (24 loads) are in flight per wave.
+// memory: a weight element is used by one workgroup only, and U k groups (3 U loads) are in flight per wave.
+// Every MFMA starts from zero and the partial sums of four products are added as a tree: chained through one
+// accumulator, 128 products have a rounding error of sqrt(64.5) roundings (2.0e-7 of the result, 2-norm), as a tree of
+// sqrt(7.5) (7.3e-8; a dot product split over 64 lanes, one workgroup per sequence, had 7.35e-8).
 // Bound by the weights' stream at small batches: 8 sequences, 128 heads, 4 blocks x 128 channels in fp32 (33.5 MB)
-// take 10.4 us; one workgroup per sequence, which read them once each, took 62.
+// take 9.5 us; one workgroup per sequence, which read them once each, took 53.
 // ------------------------------------------------------------------------------------------------
-template <typename T, bool VEC>
+template <typename T, bool VEC, int U>   // U: k groups in flight
 __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__ q_nope, const T* __restrict__ w_uk,
                                                            T* __restrict__ q_abs, int batch, int h, int d_h,
                                                            int n_blocks, int groups, int d_cb, float fold,
@@ -60,36 +63,42 @@ __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__
   const int q_head = (b / (n_blocks / groups)) * h + head;   // Eq. (6): block b serves the heads of its group
   const size_t ldw = (size_t)h * d_h;
   const T* const qrow = q_nope + ((size_t)(m0 + min(r16, n_seq - 1)) * q_heads + q_head) * d_h;
-  constexpr int U = 8;   // k groups in flight
   for (int ct0 = wave; ct0 * 16 < d_cb; ct0 += 8) {
     const T* wrow[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
       wrow[t] = w_uk + ((size_t)b * d_cb + min((ct0 + 4 * t) * 16 + r16, d_cb - 1)) * ldw + (size_t)head * d_h;
-    f32x4 acc[2] = {opaque_zero4(), opaque_zero4()};
+    f32x4 acc[2] = {};
     for (int k0 = 0; k0 < d_h; k0 += 16 * U) {
       Raw a[U], w[U][2];
 #pragma unroll
       for (int i = 0; i < U; ++i) {
-        if (k0 + 16 * i >= d_h) break;
         const int k = k0 + 16 * i + 4 * q;
         a[i] = load_row4<VEC>(qrow, k, d_h);
 #pragma unroll
         for (int t = 0; t < 2; ++t) w[i][t] = load_row4<VEC>(wrow[t], k, d_h);
       }
       __builtin_amdgcn_sched_barrier(0);
+      f32x4 sum[2][U];
 #pragma unroll
       for (int i = 0; i < U; ++i) {
-        if (k0 + 16 * i >= d_h) break;
         const int k = k0 + 16 * i + 4 * q;
         const f32x4 av = cut_row4(a[i].get(), k, d_h);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           const f32x4 wv = cut_row4(w[i][t].get(), k, d_h);
+          f32x4 part[4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], wv[e], acc[t], 0, 0, 0);
+          for (int e = 0; e < 4; ++e)
+            part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[e], wv[e], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+          sum[t][i] = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+          for (int s = 1; (i + 1) % (2 * s) == 0 && s < U; s *= 2) sum[t][i + 1 - 2 * s] += sum[t][i + 1 - s];
         }
+        __builtin_amdgcn_sched_barrier(0);   // (or all 64 partial sums would be held at once)
       }
+#pragma unroll
+      for (int t = 0; t < 2; ++t) acc[t] += sum[t][0];
     }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
@@ -322,16 +331,25 @@ int launch_absorb_q_f32(int batch, int h, int d_h, int n_blocks, int groups, int
                         void* q_rope_out, int d_r) {
   const dim3 grid(h, n_blocks + (q_rope_out ? 1 : 0), (batch + 15) / 16);
   const bool vec = d_h % 4 == 0 && aligned4(q_nope, dtype) && aligned4(w_uk, dtype);
-#define MLRA_ABSORB(T, VEC)                                                                                          \
-  absorb_q_f32_kernel<T, VEC><<<grid, 256, 0, stream>>>((const T*)q_nope, (const T*)w_uk, (T*)q_abs, batch, h, d_h,  \
-                                                        n_blocks, groups, d_cb, fold, (const T*)q_rope,              \
-                                                        (T*)q_rope_out, d_r)
+#define MLRA_ABSORB_U(T, VEC, U)                                                                                     \
+  absorb_q_f32_kernel<T, VEC, U><<<grid, 256, 0, stream>>>((const T*)q_nope, (const T*)w_uk, (T*)q_abs, batch, h,    \
+                                                           d_h, n_blocks, groups, d_cb, fold, (const T*)q_rope,      \
+                                                           (T*)q_rope_out, d_r)
+  // as many k groups at a time as a short row has: the rest of a step is multiplied with zeros (16 sequences, 128 heads,
+  // 4 blocks x 128 channels, d_h = 64: 6.7 us with four groups, 9.9 with eight)
+#define MLRA_ABSORB(T, VEC)                       \
+  do {                                            \
+    if (d_h <= 32) MLRA_ABSORB_U(T, VEC, 2);      \
+    else if (d_h <= 64) MLRA_ABSORB_U(T, VEC, 4); \
+    else MLRA_ABSORB_U(T, VEC, 8);                \
+  } while (0)
   if (dtype == MLRA_BF16) {
     if (vec) MLRA_ABSORB(bf16_t, true); else MLRA_ABSORB(bf16_t, false);
   } else {
     if (vec) MLRA_ABSORB(float, true); else MLRA_ABSORB(float, false);
   }
 #undef MLRA_ABSORB
+#undef MLRA_ABSORB_U
   return check_launch();
 }
 
