@@ -65,8 +65,10 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   // workgroup -> (chunk, sequence, block, head group).  Ids go round-robin over the eight XCDs: the head groups of
   // one (chunk, sequence, block) read the same rows and get ids 8 apart (one XCD, one L2), and the chunk is the
   // slowest index, so that the chunk slots that a ragged batch leaves empty are spread over the XCDs evenly.
+  // (A grid that one dimension does not hold is cut into rows of a multiple of eight; the last one is padded.)
   const int units = p.n_splits * p.batch * p.n_blocks, full = units & ~7;
-  int wg = blockIdx.x, u, hg;
+  int wg = blockIdx.y * gridDim.x + blockIdx.x, u, hg;
+  if (wg >= units * p.n_hg) return;
   if (wg < full * p.n_hg) {
     const int r = wg >> 3;
     hg = r % p.n_hg;
@@ -314,8 +316,11 @@ int launch_one(const DecodeArgs& a, const F32Params& p) {
     }
   }
   const long long wgs = (long long)a.plan.n_splits * a.n_blocks * a.batch * p.n_hg;
-  if (wgs > 0x7fffffffLL) return MLRA_ERR_LAUNCH;
-  decode_f32_kernel<T, VEC, KG, NCT, TT, HT><<<dim3((unsigned)wgs), 256, lds, a.stream>>>(p);
+  // A dimension of a launch holds fewer than 2^32 threads (more wrap around without an error): rows of 2^23 workgroups.
+  constexpr long long kRow = 1 << 23;
+  if (wgs > 0x7fffffffLL - kRow) return MLRA_ERR_LAUNCH;
+  const dim3 grid((unsigned)(wgs < kRow ? wgs : kRow), (unsigned)((wgs + kRow - 1) / kRow));
+  decode_f32_kernel<T, VEC, KG, NCT, TT, HT><<<grid, 256, lds, a.stream>>>(p);
   return check_launch();
 }
 

@@ -94,3 +94,21 @@ def test_bases_that_are_not_aligned_for_wide_loads(dtype, h, d_cb, d_r, d_h):
 def test_head_groups():
     _run(_wl(batch=3, n_min=1, n_max=600, h=36, groups=2), [600, 1, 65])
     _run(_wl(batch=3, n_min=1, n_max=600, h=36, groups=2, dtype="bf16"), [600, 0, 65], folded=True)
+
+
+def test_more_workgroups_than_one_grid_dimension_holds():
+    """65535 sequences x 257 blocks are more than 2^32 / 256 workgroups, the most that one dimension of a launch holds."""
+    batch, nb, pages = 65535, 257, 64
+    print(f"[case] f32 grid B={batch} NB={nb}", flush=True)
+    gen_ = torch.Generator(device="cuda").manual_seed(5)
+    latent = torch.randn((pages, nb, 1, 1), generator=gen_, device="cuda")
+    table = (torch.arange(batch, device="cuda") % pages).to(torch.int32).view(batch, 1)
+    cache = mlra.Cache(latent, torch.randn((pages, 1, 1), generator=gen_, device="cuda"), table,
+                       torch.ones(batch, dtype=torch.int32, device="cuda"))
+    w_uv = torch.randn((nb, 1, 1), generator=gen_, device="cuda")
+    q_abs = torch.randn((batch, nb, 1, 1), generator=gen_, device="cuda")
+    out = mlra.mlra_decode_attn(cache, q_abs, torch.randn((batch, 1, 1), generator=gen_, device="cuda"), w_uv, 0.5)
+    torch.cuda.synchronize()
+    # one token: its weight is 1 and the output is the sum of the blocks' channels times their weights
+    ref = (latent.double().view(pages, nb) @ w_uv.double().view(nb, 1))[table.long().view(-1)].view(batch, 1, 1)
+    assert max_rel_err(host(out), host(ref)) <= 1e-5
