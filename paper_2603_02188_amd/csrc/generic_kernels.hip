@@ -328,22 +328,76 @@ int launch_gqa_generic(const GqaArgs& a) {
   return check_launch();
 }
 
-// Merge of the chunks' partials: one wavefront per (sequence, head).  The chunks' (m, l) are reduced across the lanes,
-// their weights 2^(m_k - m*) / L wait in LDS, and the rows are added four channels per lane (element by element if the
-// rows are not made of runs of four).  One thread per channel that walked the chunks' (m, l) serially took, on one
-// sequence of 16K tokens with 8 KV heads, 7 us longer (whole call 33 -> 26 us).
-template <typename TO>
+// Merge of the chunks' partials: one wavefront per (sequence, head); the rows are added four channels per lane (element by
+// element if the rows are not made of runs of four).
+// FEW (at most kFewChunks slots): every lane reduces the chunks' (m, l) itself, and they are on their way together with
+// the first rows while the sequence's length is fetched (a slot exists in the workspace whether or not its chunk ran).
+// Otherwise the (m, l) are reduced across the lanes and the weights 2^(m_k - m*) wait in LDS.  One thread per channel that
+// walked the chunks' (m, l) serially took, on one sequence of 16K tokens with 8 KV heads, 7 us longer (whole call 33 -> 26
+// us); with two to four chunks the lane reduction is what takes longer (one sequence of 130 tokens, 4 KV heads, 128 heads,
+// whole call: serial threads 8.3 us, lane reduction 9.0, FEW 7.85).
+constexpr int kFewChunks = 4;
+template <typename TO, bool FEW>
 __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict__ part_o,
                                                         const float* __restrict__ part_ml,
                                                         const int32_t* __restrict__ seq_lens, TO* __restrict__ out,
                                                         int h, int d_h, int n_splits, int chunk) {
-  extern __shared__ float wtab[];          // [4 waves][n_splits]
+  extern __shared__ float wtab[];          // [4 waves][n_splits] (not FEW)
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, head = blockIdx.x * 4 + wave, s = blockIdx.y;
   if (head >= h) return;                   // (no barrier follows: a wave reads only what it wrote)
-  const int n = seq_lens[s];
-  const int active = min(n_splits, (n + chunk - 1) / chunk);
   const size_t unit0 = (size_t)s * n_splits, stride = (size_t)h * d_h;
   const float* const ml = part_ml + (unit0 * h + head) * 2;
+  const float* const po = part_o + (unit0 * h + head) * d_h;
+  const size_t o = ((size_t)s * h + head) * d_h;
+  if constexpr (FEW) {
+    float2 got[kFewChunks];
+    size_t row[kFewChunks];
+    float w[kFewChunks];
+#pragma unroll
+    for (int k = 0; k < kFewChunks; ++k) {
+      const size_t slot = min(k, n_splits - 1);
+      got[k] = *(const float2*)(ml + slot * h * 2);
+      row[k] = slot * stride;
+    }
+    const int n = seq_lens[s];
+    const int active = min(n_splits, (n + chunk - 1) / chunk);
+    float m_star = kNegBig, L = 0.f;
+#pragma unroll
+    for (int k = 0; k < kFewChunks; ++k)
+      if (k < active) m_star = fmaxf(m_star, got[k].x);
+#pragma unroll
+    for (int k = 0; k < kFewChunks; ++k) {
+      w[k] = exp2f(got[k].x - m_star);
+      if (k < active) L += w[k] * got[k].y;
+    }
+    const float inv = L > 0.f ? 1.f / L : 0.f;
+    if (d_h % 4 == 0) {
+      for (int c = lane * 4; c < d_h; c += 256) {
+        float4 v[kFewChunks];
+        float z[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < kFewChunks; ++k) v[k] = *(const float4*)(po + row[k] + c);
+#pragma unroll
+        for (int k = 0; k < kFewChunks; ++k)
+          if (k < active) { z[0] += w[k] * v[k].x; z[1] += w[k] * v[k].y; z[2] += w[k] * v[k].z; z[3] += w[k] * v[k].w; }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) store_f32(out, o + c + e, z[e] * inv);
+      }
+    } else {
+      for (int c = lane; c < d_h; c += 64) {
+        float z = 0.f;
+#pragma unroll
+        for (int k = 0; k < kFewChunks; ++k) {
+          const float v = po[row[k] + c];
+          if (k < active) z += w[k] * v;
+        }
+        store_f32(out, o + c, z * inv);
+      }
+    }
+    return;
+  }
+  const int n = seq_lens[s];
+  const int active = min(n_splits, (n + chunk - 1) / chunk);
   float* const w = wtab + wave * n_splits;
   float m_star = kNegBig;
   for (int k = lane; k < active; k += 64) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);
@@ -356,8 +410,6 @@ __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict_
   L = wave_sum(L);
   const float inv = L > 0.f ? 1.f / L : 0.f;
   __builtin_amdgcn_wave_barrier();
-  const float* const po = part_o + (unit0 * h + head) * d_h;
-  const size_t o = ((size_t)s * h + head) * d_h;
   if (d_h % 4 == 0) {
     for (int c = lane * 4; c < d_h; c += 256) {
       float z[4] = {0.f, 0.f, 0.f, 0.f};
@@ -378,15 +430,21 @@ __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict_
   }
 }
 
-int launch_gqa_merge(const GqaArgs& a) {
+template <typename TO>
+static void launch_gqa_merge_typed(const GqaArgs& a) {
   const dim3 grid((a.h + 3) / 4, a.batch);
   const size_t lds = (size_t)4 * a.plan.n_splits * sizeof(float);   // at most one chunk per CU and sequence: 4 KiB
-  if (a.out_dtype == MLRA_BF16)
-    gqa_merge_kernel<bf16_t><<<grid, 256, lds, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (bf16_t*)a.out, a.h, a.d_h,
+  if (a.plan.n_splits <= kFewChunks)
+    gqa_merge_kernel<TO, true><<<grid, 256, 0, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (TO*)a.out, a.h, a.d_h,
                                                            a.plan.n_splits, a.plan.chunk_tokens);
   else
-    gqa_merge_kernel<float><<<grid, 256, lds, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (float*)a.out, a.h, a.d_h,
-                                                          a.plan.n_splits, a.plan.chunk_tokens);
+    gqa_merge_kernel<TO, false><<<grid, 256, lds, a.stream>>>(a.part_o, a.part_ml, a.seq_lens, (TO*)a.out, a.h, a.d_h,
+                                                              a.plan.n_splits, a.plan.chunk_tokens);
+}
+
+int launch_gqa_merge(const GqaArgs& a) {
+  if (a.out_dtype == MLRA_BF16) launch_gqa_merge_typed<bf16_t>(a);
+  else launch_gqa_merge_typed<float>(a);
   return check_launch();
 }
 

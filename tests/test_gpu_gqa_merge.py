@@ -18,6 +18,10 @@ pytestmark = pytest.mark.gpu
     ("bf16", 64, 4, 128, [0, 1, 31, 32, 33, 640] * 12),         # 288 workgroups for 256 CUs: one chunk each
     ("bf16", 128, 128, 128, [0, 65, 300]),                      # one query head per KV head
     ("bf16", 40, 8, 128, [9000]), ("bf16", 8, 1, 128, [20000, 0, 129]),   # 32 and 66 chunk slots
+    # two to five slots: every lane's own weights up to four, lanes reduced from five on
+    ("bf16", 24, 8, 128, [256, 0, 129]), ("bf16", 40, 8, 128, [300, 0, 129]), ("bf16", 40, 8, 128, [512, 1, 0, 385]),
+    ("bf16", 40, 8, 128, [640, 513, 0]), ("f32", 6, 2, 30, [250, 0, 65]), ("f32", 5, 1, 64, [400, 0, 129]),
+    ("f32", 6, 2, 30, [100] * 40),                              # one slot, merged (the plain kernel writes partials)
     ("f32", 6, 2, 30, [700, 0, 65]), ("f32", 5, 1, 64, [3000])])
 def test_output_written_or_merged(dtype, h, g, d_h, lens):
     wl = gen.WORKLOADS["C5"].scaled(name="gqa-merge", batch=len(lens), n_min=0, n_max=max(lens), h=h, g=g, d_h=d_h,
