@@ -409,7 +409,10 @@ __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict_
   }
   L = wave_sum(L);
   const float inv = L > 0.f ? 1.f / L : 0.f;
+  // the weights are read by the wave's other lanes (the barrier alone orders no memory accesses)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (d_h % 4 == 0) {
     for (int c = lane * 4; c < d_h; c += 256) {
       float z[4] = {0.f, 0.f, 0.f, 0.f};
