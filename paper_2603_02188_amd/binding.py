@@ -164,13 +164,13 @@ class Cache:
     def struct(self) -> _CacheStruct:
         latent, rope, table, lens = self.latent, self.rope, self.page_table, self.seq_lens
         P, NB, ps, dcb = latent.shape
-        rope_pages, rope_ps, d_r = rope.shape
-        assert rope_pages == P and rope_ps == ps
+        rope_shape = rope.shape       # (trailing dimensions of one are accepted)
+        assert rope_shape[0] == P and rope_shape[1] == ps
         assert table.dtype == torch.int32 and lens.dtype == torch.int32
         dtype = latent.dtype
         assert rope.dtype == dtype
         return _CacheStruct(latent.data_ptr(), rope.data_ptr(), table.data_ptr(), lens.data_ptr(), P, ps,
-                            table.shape[1], NB, dcb, d_r, _dt(dtype))
+                            table.shape[1], NB, dcb, rope_shape[2], _dt(dtype))
 
     @property
     def max_seq_len(self) -> int:

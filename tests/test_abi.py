@@ -100,6 +100,17 @@ def test_null_and_shape_errors_are_reported_on_the_host():
                                null) == -1
 
 
+def test_cache_takes_a_rope_pool_with_trailing_dimensions_of_one():
+    import torch
+    latent, table, lens = torch.zeros(3, 4, 16, 8), torch.zeros(2, 5, dtype=torch.int32), torch.ones(2, dtype=torch.int32)
+    for shape in ((3, 16, 6), (3, 16, 6, 1)):
+        cs = mlra.Cache(latent, torch.zeros(shape), table, lens).struct()
+        assert (cs.num_pages, cs.page_size, cs.max_pages_per_seq, cs.n_blocks, cs.d_cb, cs.d_r) == (3, 16, 5, 4, 8, 6)
+    for shape in ((2, 16, 6), (3, 15, 6)):
+        with pytest.raises(AssertionError):
+            mlra.Cache(latent, torch.zeros(shape), table, lens).struct()
+
+
 def test_workspace_sizing():
     assert mlra.mlra_decode_workspace_bytes(0, 8, 4, 64, 256) == 0
     small = mlra.mlra_decode_workspace_bytes(1, 8, 4, 64, 256)
