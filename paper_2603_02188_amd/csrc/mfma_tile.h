@@ -40,6 +40,7 @@ struct MfmaParams {
   int groups;                 // head groups (Eq. (6)): block b serves the h heads of group b / (n_blocks / groups);
                               // q_rope holds groups * h heads.  1 = every block serves every head (Eq. (5))
   float scale_log2;
+  int split_major = 0;        // (MLA) dispatch order: all sequences' first chunks, then all second ones, ...
   int rows_bf16;              // 1: part_z receives each chunk's partial as z / l rounded to bf16, [..][chunk][head][channels]
                               // (what the MFMA epilogue merges); 0: fp32 partials, not normalised (generic merge, MLA)
 };

@@ -1,9 +1,9 @@
 // MFMA decode kernel for the MLA comparison: one 512-dim latent plus a 64-dim RoPE key per token
 // (Section 2.1, Steps 1-3 with d_c = 512; bf16 caches).
 //
-// One workgroup (4 wavefronts, two workgroups per CU) owns one (sequence, context chunk, 64 query heads) and walks the
-// chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads, two stages deep (one tile
-// in flight while one is worked on).  The two products split the work differently:
+// One workgroup (4 wavefronts) owns one (sequence, context chunk, 64 query heads) and walks the
+// chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads, two stages deep with two
+// workgroups per CU or four stages deep with one.  The two products split the work differently:
 //   * scores and softmax by heads: wave w owns heads [16 w, 16 w + 16) and computes their complete scores
 //     S^T = [C | K^R] [q~ | q^R]^T over all 576 channels with 16x16x32 MFMAs (tokens x heads), so the
 //     softmax of a head is computed once, by one wave, with its running maximum and sum in that wave;
@@ -15,13 +15,15 @@
 // history when their running maximum grew (refreshed lazily, so almost always none).  Two workgroup
 // barriers per tile: one hands the landed tile and the freed stage around, one publishes P^T.
 // A wave's chain through a tile (LDS latencies, softmax, the hand-overs) is 2.5 times the 1088 cycles of matrix pipe in
-// it, so the second workgroup of the CU matters more than deeper buffering: it takes 256 registers per wave, all of them
-// (accumulators 128, queries 72, the rest operands in flight), and whatever can be recomputed is, because a spill inside
-// the loop also waits for the tile loads.  64 heads x 512 + 64 channels, 256 sequences of 2176 tokens x 128 heads:
-// 222 -> 191 us against one workgroup per CU with four stages (128 sequences of 512 to 8192 in chunks: 274 -> 228;
-// one workgroup per CU, 128 sequences of 4352: 221 -> 217).  Measured and not kept: 16-token tiles in four stages
+// it, so a second workgroup on the CU matters more than deeper buffering: the two-stage form takes 256 registers per wave,
+// all of them (accumulators 128, queries 72, the rest operands in flight), and whatever can be recomputed is, because a
+// spill inside the loop also waits for the tile loads (six registers are spilled in front of it and reloaded after it).  64 heads x 512 + 64 channels, two stages against four stages of the same width with one workgroup
+// per CU: 256 sequences of 2176 tokens x 128 heads 222 -> 185 us, 128 sequences of 512 to 8192 in chunks 275 -> 221, 128
+// sequences of 4352 (one workgroup per CU) 221 -> 212.  Measured and not kept: 16-token tiles in four stages
 // (198 / 237 / 250 us), two groups of four waves one barrier apart in one workgroup (223 / 260 / 215), 32 heads x 16
 // tokens per wave (216 / 264 / 214), the channels of the scores split over two waves (224 / 265 / 298).
+// With one workgroup per CU and no second head half beside it to share rows with in L2, two stages leave the loads too
+// little time: see the rule in launch_mla_mfma.
 // The two head halves of a sequence are placed on the same XCD (ids 8 apart), so the cache is fetched
 // from HBM once.  Partials go to the workspace in the layout of the MLRA path with n_blocks = 1,
 // d_cb = 512.
@@ -38,12 +40,10 @@ constexpr int kMHeads = 64;                        // query heads per workgroup
 constexpr int kMLatBytes = kMTok * kMDc * 2;       // 32 KiB
 constexpr int kMRopeBytes = kMTok * kDr * 2;       //  4 KiB
 constexpr int kMStage = kMLatBytes + kMRopeBytes;  // 36 KiB
-constexpr int kMStages = 2;
-constexpr int kMPOff = kMStages * kMStage;         // P^T: [2 head tiles][2 token halves][64 lanes][16 B]
-constexpr int kMPBytes = 4 * 1024;
-constexpr int kMAOff = kMPOff + kMPBytes;          // rescale factors: [64 heads] floats, then [4 waves] flags
-constexpr int kMFOff = kMAOff + kMHeads * 4;
-constexpr int kMLds = kMFOff + 4 * 4;              // 78,096 bytes: two workgroups per CU
+constexpr int kMPBytes = 4 * 1024;                 // P^T: [2 head tiles][2 token halves][64 lanes][16 B]
+// LDS: the stages, P^T, the rescale factors ([64 heads] floats) and the four waves' flags
+constexpr int mla_lds_bytes(int stages) { return stages * kMStage + kMPBytes + kMHeads * 4 + 4 * 4; }
+static_assert(2 * mla_lds_bytes(2) <= 160 * 1024 && mla_lds_bytes(4) <= 160 * 1024, "two workgroups per CU / one");
 constexpr int kMLoads = 9;                         // direct-to-LDS loads per wave and tile
 
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
@@ -76,7 +76,10 @@ __device__ __forceinline__ float head_sum(float v) {
   return a + b;
 }
 
-__global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
+template <int STAGES>
+__global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(MfmaParams p) {
+  static_assert(STAGES == 2 || STAGES == 4, "a power of two, and the waits below");
+  constexpr int kMPOff = STAGES * kMStage, kMAOff = kMPOff + kMPBytes, kMFOff = kMAOff + kMHeads * 4;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // workgroup -> (sequence, chunk, head half); the halves of one (sequence, chunk) get ids 8 apart
   const int n_hg = (p.h + kMHeads - 1) / kMHeads;
@@ -100,8 +103,13 @@ __global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
     split = code & 1023;
     chunk_len = p.chunk_tab[seq];
   } else {
-    split = su % p.n_splits;
-    seq = p.seq_order ? p.seq_order[su / p.n_splits] : su / p.n_splits;
+    // longest sequences first, and with several slots per sequence all first chunks, then all second ones, ...: the
+    // slots that shorter sequences leave empty come late and in runs.  (Sequence by sequence they lie between the others,
+    // and CUs that were dealt empty ones stay idle while others get a second workgroup: 50 sequences of 1666 to 5000
+    // tokens x 64 heads, whole step 98 us against 83.)
+    const int slot = p.split_major ? su % p.batch : su / p.n_splits;
+    split = p.split_major ? su / p.batch : su % p.n_splits;
+    seq = p.seq_order ? p.seq_order[slot] : slot;
     chunk_len = p.chunk;
   }
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
@@ -169,7 +177,7 @@ __global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
     }
     iss_tok += kMTok;
     iss_slot += kMTok;
-    iss_stage ^= 1;
+    iss_stage = (iss_stage + 1) & (STAGES - 1);
     if (iss_slot == p.page_size) {
       iss_slot = 0;
       ++iss_page_at;
@@ -212,15 +220,17 @@ __global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) zacc[mt][nt][i] = 0.f;
 
-  issue_tile();
+  for (int jj = 0; jj < STAGES - 1 && jj < ntiles; ++jj) issue_tile();
   for (int j = 0; j < ntiles; ++j) {
-    // tile j landed in this wave's share ...
-    wait_vm_lgkm<0>();
+    // tile j landed in this wave's share (the tiles issued after it may still be in flight) ...
+    if (STAGES > 2 && j + 2 < ntiles) wait_vm_lgkm<2 * kMLoads>();
+    else if (STAGES > 2 && j + 1 < ntiles) wait_vm_lgkm<kMLoads>();
+    else wait_vm_lgkm<0>();
     // ... and in everybody's; every wave is also done with tile j-1, whose stage is refilled now
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (j + 1 < ntiles) issue_tile();
-    const unsigned base = lds_base + (j & 1) * kMStage;
+    if (j + STAGES - 1 < ntiles) issue_tile();
+    const unsigned base = lds_base + (j & (STAGES - 1)) * kMStage;
 
     // ---- scores of this wave's 16 heads: 36 MFMAs
     f32x4 s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
@@ -232,7 +242,7 @@ __global__ __launch_bounds__(256, 2) void mla_mfma_kernel(MfmaParams p) {
         return *(lds_bf16x8_ptr)(size_t)addr;
       };
       // (the order is pinned: left to itself, the scheduler reads one operand at a time and waits for it)
-      constexpr int kAhead = 5;
+      constexpr int kAhead = STAGES == 2 ? 5 : 12;
       bf16x8 ka[36];
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -360,15 +370,21 @@ bool mla_mfma_supported(const DecodeArgs& a) {
          a.plan.chunk_tokens % kMTok == 0;
 }
 
-int launch_mla_mfma(const DecodeArgs& a) {
+template <int STAGES>
+static int launch_mla_as(const DecodeArgs& a, const MfmaParams& p, unsigned n_wg) {
   static PerDeviceSetup setup;
   int setup_dev = -1;
   if (setup.needed(&setup_dev)) {
-    if (hipFuncSetAttribute((const void*)mla_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kMLds) !=
-        hipSuccess)
+    if (hipFuncSetAttribute((const void*)mla_mfma_kernel<STAGES>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            mla_lds_bytes(STAGES)) != hipSuccess)
       return MLRA_ERR_LAUNCH;
     setup.done(setup_dev);
   }
+  MLRA_LAUNCH_TIMED(a.t_main, mla_mfma_kernel<STAGES>, dim3(n_wg), dim3(256), mla_lds_bytes(STAGES), a.stream, p);
+  return check_launch();
+}
+
+int launch_mla_mfma(const DecodeArgs& a) {
   MfmaParams p;
   p.latent = (const bf16_t*)a.latent;
   p.rope = (const bf16_t*)a.rope;
@@ -395,8 +411,17 @@ int launch_mla_mfma(const DecodeArgs& a) {
   const long long n_wg = (long long)a.plan.n_splits * n_hg * a.batch;
   if (n_wg <= 0 || n_wg > 0x7fffffffLL) return MLRA_ERR_SHAPE;
   if (!a.balanced && (n_wg > device_cu_count() || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
-  MLRA_LAUNCH_TIMED(a.t_main, mla_mfma_kernel, dim3((unsigned)n_wg), dim3(256), kMLds, a.stream, p);
-  return check_launch();
+  // (the query tokens of one sequence are kept side by side in the order)
+  p.split_major = p.seq_order && a.q_group <= 1;
+  // Four stages where every CU has one workgroup at most, none of them shares its rows with another (one head group) and
+  // the chunks are long: 64 sequences of 6000 tokens x 64 heads in four chunks, whole step 124 us against 130 with two
+  // stages, 128 of 3000 in two 128 against 134.  Two stages otherwise: with two head groups 64 of 6000 take 181 us (182.7
+  // with four stages), in chunks below 1024 tokens 30 of 2500 53 (55), with more workgroups than CUs 140 of 2000 128 (155).
+  // (Planned chunks: a batch of nearly equal lengths is left uncut and has one workgroup per sequence; 256 of 2000 x 32
+  // heads 157 against 161, and 512 chunks of a ragged one take the same or less.)
+  const long long most = a.balanced ? a.batch : n_wg;
+  const bool four = n_hg == 1 && most <= device_cu_count() && a.plan.chunk_tokens >= 1024;
+  return four ? launch_mla_as<4>(a, p, (unsigned)n_wg) : launch_mla_as<2>(a, p, (unsigned)n_wg);
 }
 
 }  // namespace mlra
