@@ -1,6 +1,8 @@
 """The kernels on the fp32 matrix instructions (absorb, decode, merge + up-projection of every shape outside the bf16
 fast paths) at the edges of their tiles, against the fp64 oracle.  Bars as for the other parity tests:
 max|gpu - ref| / max|ref| <= 1e-5 (fp32 storage) and 1e-2 (bf16 storage)."""
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -9,7 +11,7 @@ from oracle import mlra_oracle as orc
 from paper_2603_02188_amd import binding as mlra
 from paper_2603_02188_amd import inputs as gen
 
-from gpu_util import device_cache, device_queries_weights, host, max_rel_err, oracle_views
+from gpu_util import device_cache, device_queries_weights, host, max_rel_err, oracle_views, to_device
 
 pytestmark = pytest.mark.gpu
 
@@ -23,7 +25,22 @@ def _shifted(t):
     return buf[1:].view(t.shape)
 
 
-def _run(wl, lens, shift=False, folded=False, out_dtype=torch.float32):
+def _lse_reference(v, q_abs, q_rope, groups, scale):
+    """Log-sum-exp [B][NB][h / groups] in 64 bits from the absorbed queries as they are stored (so that their rounding, which
+    grows with the score, stays out of it)."""
+    batch, nb, hb, d_cb = q_abs.shape
+    lse = np.full((batch, nb, hb), -np.inf)
+    for s in range(batch):
+        n = int(v["seq_lens"][s])
+        c, kr = orc.gather_sequence(v["latent_pool"], v["rope_pool"], v["page_table"][s], n)
+        for b in range(nb if n else 0):
+            first = b // (nb // groups) * hb
+            x = scale * (c[:, b * d_cb:(b + 1) * d_cb] @ q_abs[s, b].T + kr @ q_rope[s, first:first + hb].T)
+            lse[s, b] = x.max(axis=0) + np.log(np.exp(x - x.max(axis=0)).sum(axis=0))
+    return lse
+
+
+def _run(wl, lens, shift=False, folded=False, out_dtype=torch.float32, gated=False):
     print(f"[case] {wl.name} B={wl.batch} NB={wl.n_blocks} d_cb={wl.d_cb} d_r={wl.d_r} h={wl.h} d_h={wl.d_h} "
           f"{wl.dtype} page={wl.page_size} groups={wl.groups} shift={shift} folded={folded} lens={list(lens)}", flush=True)
     inp = gen.make_decode_inputs(wl, poison=True, seq_lens=np.array(lens, dtype=np.int32))
@@ -40,19 +57,34 @@ def _run(wl, lens, shift=False, folded=False, out_dtype=torch.float32):
     else:
         q_abs = (mlra.mlra2_absorb_q if two else mlra.mlra_absorb_q)(q_nope, w_uk)
     lse = torch.full((wl.batch, wl.n_blocks, wl.h // wl.groups), float("nan"), device="cuda")
-    out = (mlra.mlra2_decode_attn if two else mlra.mlra_decode_attn)(cache, q_abs, q_rope, w_uv, scale, 0.5,
-                                                                     out_dtype=out_dtype, lse=lse)
+    kw = dict(out_dtype=out_dtype, lse=lse)
+    if gated:
+        gate = gen.to_storage(np.random.default_rng(7).uniform(0.0, 1.0, size=(wl.batch, wl.h, wl.d_h)).astype(np.float32), wl.dtype)
+        gate_dev = to_device(gate, "bf16" if wl.dtype == "bf16" else None)
+        out = mlra.mlra_decode_attn_gated(cache, q_abs, q_rope, w_uv, gate_dev, scale, 0.5, **kw)
+    else:
+        out = (mlra.mlra2_decode_attn if two else mlra.mlra_decode_attn)(cache, q_abs, q_rope, w_uv, scale, 0.5, **kw)
     torch.cuda.synchronize()
     v = oracle_views(inp)
     args = (v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"], v["q_rope"], v["w_uk"],
             v["w_uv"], wl.tau)
-    ref = orc.mlra2_decode_batch(*args, 0.5) if two else orc.mlra_decode_batch(*args, 0.5)
+    ref = (orc.mlra2_decode_batch if two else orc.mlra_decode_batch)(*args, 0.5)
+    if gated:
+        ref = ref * gen.to_f64(gate, wl.dtype)
     err = max_rel_err(host(out), ref)
     print(f"       max rel err {err:.3e}", flush=True)
     assert err <= (1e-2 if out_dtype == torch.bfloat16 else TOL[wl.dtype])
-    lse = host(lse)
-    for s, n in enumerate(lens):
-        assert np.all(np.isneginf(lse[s])) if n == 0 else np.all(np.isfinite(lse[s]))
+    ref_lse = _lse_reference(v, host(q_abs), host(q_rope), wl.groups, math.log(2.0) if folded else wl.tau)
+    got, live = host(lse), np.isfinite(ref_lse)
+    assert np.array_equal(np.isneginf(got), ~live) and np.array_equal(np.isfinite(got), live)
+    # fp32 scores of size 10 and sums of hundreds: 1e-5 of either.  The bf16 kernels round the scaled queries and the
+    # probabilities to bf16: 2^-9 of a score of up to 8 and 2^-9 of the sum
+    info = mlra.mlra_decode_plan_info(wl.batch, wl.h, wl.d_h, wl.groups, wl.n_blocks, wl.d_cb, wl.d_r, wl.page_size,
+                                      cache.max_seq_len, q_abs.dtype)
+    tol = 2e-2 if info["kernel"].startswith("mfma") else 1e-4
+    lse_err = float(np.max(np.abs(got[live] - ref_lse[live])))
+    print(f"       lse {lse_err:.3e}", flush=True)
+    assert lse_err <= tol
 
 
 def _wl(**kw):
@@ -89,6 +121,13 @@ def test_batches_and_chunks(batch, n, page):
 def test_bases_that_are_not_aligned_for_wide_loads(dtype, h, d_cb, d_r, d_h):
     _run(_wl(batch=3, n_min=1, n_max=400, h=h, d_cb=d_cb, d_r=d_r, d_h=d_h, n_blocks=2, dtype=dtype), [400, 1, 77],
          shift=True, folded=True)
+
+
+# a block that straddles the merge's channel slabs, gate and log-sum-exp over several slabs
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_merge_of_several_slabs(dtype):
+    for gated in (False, True):
+        _run(_wl(batch=2, n_min=0, n_max=700, h=4, d_cb=96, d_r=32, d_h=40, n_blocks=7, dtype=dtype), [700, 311], gated=gated)
 
 
 def test_head_groups():
