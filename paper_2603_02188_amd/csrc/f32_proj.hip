@@ -113,30 +113,32 @@ __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__
 
 // ------------------------------------------------------------------------------------------------
 // merge + up-projection.  One workgroup per (output head, 16 sequences, 64 output columns); the head's latent channels
-// (all blocks of its group, R of them) go through in slabs of at most 512:
+// (all blocks of its group, R of them) go through in slabs of at most SLAB:
 //   1. this wave's share of the slab's W^UV rows is fetched into registers (in flight during 2 and 3);
-//   2. sixteen lanes per (sequence, block) reduce the chunks' (m, l) to the maximum m* and 1 / L in LDS, and write the
-//      log-sum-exp;
-//   3. z = sum_k 2^(m_k - m*) Z_k / L of the slab is built in LDS, eight independent four-channel pieces per thread at
-//      a time; with few sequences the chunks of a piece are dealt to several threads (KP of them) and added in LDS;
+//   2. sixteen lanes per (sequence, block), four pairs at a time (one thread, if there are at most four slots), reduce
+//      the chunks' (m, l) to the maximum m* and 1 / L in LDS, and write the log-sum-exp;
+//   3. z = sum_k 2^(m_k - m*) Z_k / L of the slab is built in LDS, a thread's four-channel pieces side by side (eight
+//      single channels, if the rows are not made of runs of four); with few sequences the chunks of a piece are dealt to
+//      several threads (KP of them) and added in LDS;
 //   4. out += z W^UV: z rows (sequences) are the A operand, W^UV rows the B operand (k dealt as 16 i + 4 q + j; column
 //      tile ct takes columns 4 c + ct, so that a lane reads four consecutive ones), the four waves take every
 //      fourth k group each and are added through LDS at the end.
 // Bound by the streams of the weights and the partials: on the shape above (33.5 MB + 16.8 MB of partials in eight
-// chunks) 20.6 us; one workgroup per (head, sequence) took 63.
+// chunks) 20.6 us; one workgroup per (head, sequence) took 63.  A slab of 512 takes 300 to 354 registers per wave, most of
+// them weights; heads of few channels have one of 128 (up to 157 registers, a quarter of the LDS), see the rule below.
 // ------------------------------------------------------------------------------------------------
-constexpr int kSlab = 512, kZPitch = kSlab + 4, kSlabBlocks = 64, kPieces = 8;
-static_assert(16 * kSlab / 4 <= kPieces * 256, "every piece of a slab needs a thread");
-static_assert(kPieces * 256 * 4 <= 16 * kZPitch, "the chunk parts are exchanged in the z rows' space");
-static_assert(4 * 16 * 68 <= 16 * kZPitch, "the waves' sums are exchanged in the z rows' space");
+constexpr int kSlabBlocks = 64, kChannels = 8;
 
-template <typename T, typename TO, bool VEC>
+template <typename T, typename TO, bool VEC, int SLAB>
 __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
     const float* __restrict__ part_z, const float* __restrict__ part_ml, const int32_t* __restrict__ seq_lens,
     const T* __restrict__ w_uv, TO* __restrict__ out, float* __restrict__ lse, int batch, int h, int d_h, int n_blocks,
     int d_cb, int n_splits, int chunk, float out_scale, int groups, const T* __restrict__ gate) {
   typedef typename RawOf<T>::type Raw;
-  __shared__ __attribute__((aligned(16))) float zs[16 * kZPitch];
+  constexpr int kZPitch = SLAB + 4, kPieces = SLAB / 64, kZRows = 16 * kZPitch, kExchange = 4 * 16 * 68;
+  static_assert(16 * SLAB / 4 <= kPieces * 256, "every piece of a slab needs a thread");
+  static_assert(kPieces * 256 * 4 <= kZRows && kChannels * 256 <= kZRows, "the chunk parts are exchanged in the z rows' space");
+  __shared__ __attribute__((aligned(16))) float zs[kZRows > kExchange ? kZRows : kExchange];   // (the waves' sums as well)
   __shared__ float mtab[16 * kSlabBlocks], itab[16 * kSlabBlocks];
   __shared__ int act[16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -148,7 +150,7 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
   const int n_seq = min(16, batch - m0);
   const size_t ldw = (size_t)h * d_h;
   // (at most kSlabBlocks blocks per slab: with fewer than nine channels a block, a slab is whole blocks)
-  const int slab = min(kSlab, kSlabBlocks * d_cb);
+  const int slab = min(SLAB, kSlabBlocks * d_cb);
   const T* const wcol = w_uv + (size_t)b0 * d_cb * ldw + (size_t)head * d_h;
   f32x4 acc[4] = {opaque_zero4(), opaque_zero4(), opaque_zero4(), opaque_zero4()};
   if (tid < 16) {
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
   for (int r0 = 0; r0 < R; r0 += slab) {
     const int len = min(slab, R - r0);
     // 1. (a row past the slab repeats its last row; z is zero there, and so is the row once it is used)
-    constexpr int KG = kSlab / 16 / 4;
+    constexpr int KG = SLAB / 16 / 4;
     Raw w[VEC ? KG : 1][4];
     auto fetch_w = [&](int i, Raw (&x)[4]) {
 #pragma unroll
@@ -173,27 +175,66 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
       for (int i = 0; i < KG; ++i)
         if ((4 * i + wave) * 16 < len) fetch_w(i, w[i]);   // (uniform per wave)
     }
-    __syncthreads();      // act is there; the previous slab's z rows are no longer read
     // 2.
     const int blk0 = r0 / d_cb, nblk = (r0 + len - 1) / d_cb - blk0 + 1;
-    for (int pair = tid >> 4; pair < n_seq * nblk; pair += 16) {
-      const int sl = pair / nblk, bb = pair - sl * nblk, b = b0 + blk0 + bb, n_act = act[sl];
-      const float* ml = part_ml + ((((size_t)(m0 + sl) * n_blocks + b) * n_splits) * h + head) * 2;
-      float m_star = kNegBig, L = 0.f;
-      for (int k = r16; k < n_act; k += 16) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);
+    const int n_pairs = n_seq * nblk;
+    auto ml_of = [&](int sl, int bb) {
+      return part_ml + ((((size_t)(m0 + sl) * n_blocks + b0 + blk0 + bb) * n_splits) * h + head) * 2;
+    };
+    auto put_pair = [&](int sl, int bb, float m_star, float L) {
+      mtab[sl * kSlabBlocks + bb] = m_star;
+      itab[sl * kSlabBlocks + bb] = L > 0.f ? 1.f / L : 0.f;
+      if (lse && blockIdx.z == 0 && (blk0 + bb) * d_cb >= r0)
+        lse[((size_t)(m0 + sl) * n_blocks + b0 + blk0 + bb) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
+    };
+    if (n_splits <= 4) {       // a thread per pair, its chunks and the length fetched at once
+      for (int pair = tid; pair < n_pairs; pair += 256) {
+        const int sl = pair / nblk, bb = pair - sl * nblk;
+        const float* ml = ml_of(sl, bb);
+        const int n_act = min(n_splits, (seq_lens[m0 + sl] + chunk - 1) / chunk);
+        float2 got[4];
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, o));
-      for (int k = r16; k < n_act; k += 16) L += exp2f(ml[(size_t)k * h * 2] - m_star) * ml[(size_t)k * h * 2 + 1];
+        for (int k = 0; k < 4; ++k) got[k] = *(const float2*)(ml + (size_t)min(k, n_splits - 1) * h * 2);
+        float m_star = kNegBig, L = 0.f;
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) L += __shfl_xor(L, o);
-      if (r16 == 0) {
-        mtab[sl * kSlabBlocks + bb] = m_star;
-        itab[sl * kSlabBlocks + bb] = L > 0.f ? 1.f / L : 0.f;
-        if (lse && blockIdx.z == 0 && (blk0 + bb) * d_cb >= r0)
-          lse[((size_t)(m0 + sl) * n_blocks + b) * h + head] = L > 0.f ? (m_star + log2f(L)) * kLn2 : -INFINITY;
+        for (int k = 0; k < 4; ++k)
+          if (k < n_act) m_star = fmaxf(m_star, got[k].x);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+          if (k < n_act) L += exp2f(got[k].x - m_star) * got[k].y;
+        put_pair(sl, bb, m_star, L);
+      }
+    } else {
+      __syncthreads();         // (act)
+      for (int pair0 = tid >> 4; pair0 < n_pairs; pair0 += 64) {
+        float2 first[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int pair = min(pair0 + 16 * i, n_pairs - 1), sl = pair / nblk;
+          first[i] = *(const float2*)(ml_of(sl, pair - sl * nblk) + (size_t)min(r16, n_splits - 1) * h * 2);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int pair = pair0 + 16 * i, sl = pair / nblk, bb = pair - sl * nblk;
+          if (pair >= n_pairs) break;
+          const int n_act = act[sl];
+          const float* ml = ml_of(sl, bb);
+          float m_star = r16 < n_act ? fmaxf(kNegBig, first[i].x) : kNegBig, L = 0.f;
+          for (int k = r16 + 16; k < n_act; k += 16) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);
+#pragma unroll
+          for (int o = 8; o > 0; o >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, o));
+          if (r16 < n_act) L = exp2f(first[i].x - m_star) * first[i].y;
+          for (int k = r16 + 16; k < n_act; k += 16) {
+            const float2 got = *(const float2*)(ml + (size_t)k * h * 2);
+            L += exp2f(got.x - m_star) * got.y;
+          }
+#pragma unroll
+          for (int o = 8; o > 0; o >>= 1) L += __shfl_xor(L, o);
+          if (r16 == 0) put_pair(sl, bb, m_star, L);
+        }
       }
     }
-    __syncthreads();
+    __syncthreads();           // the tables and act are there; the previous slab's z rows are no longer read
     // 3.  (zero: rows past the batch, channels past the slab's end up to its last k group's)
     const int pad = (len + 15) / 16 * 16;
     if constexpr (VEC) {
@@ -260,20 +301,65 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
         const int sl = t / (pad / 4), c = 4 * (t - sl * (pad / 4));
         if (sl >= n_seq || c >= len) *(f32x4*)(zs + sl * kZPitch + c) = f32x4{0.f, 0.f, 0.f, 0.f};
       }
-    } else {              // (rows that are not made of aligned runs of four: one channel at a time)
-      for (int t = tid; t < 16 * pad; t += 256) {
-        const int sl = t / pad, c = t - sl * pad, r = r0 + c;
-        float z = 0.f;
-        if (sl < n_seq && c < len) {
-          const size_t unit0 = ((size_t)(m0 + sl) * n_blocks + b0 + r / d_cb) * n_splits;
-          const int at = sl * kSlabBlocks + r / d_cb - blk0;
-          for (int k = 0; k < act[sl]; ++k) {
-            const size_t o = (unit0 + k) * h + head;
-            z += exp2f(part_ml[o * 2] - mtab[at]) * part_z[o * d_cb + r % d_cb];
-          }
-          z *= itab[at];
+    } else {              // (rows that are not made of aligned runs of four: one channel at a time, eight in flight)
+      const int items = n_seq * len;
+      int max_act = 0;
+      for (int sl = 0; sl < n_seq; ++sl) max_act = max(max_act, act[sl]);
+      const int KP = max(1, min(256 * kChannels / items, max_act)), total = items * KP;   // (KP > 1: one pass)
+      for (int base = tid; base - tid < total; base += 256 * kChannels) {
+        const int np = min(kChannels, (total - (base - tid) + 255) / 256);   // (uniform)
+        const float* src[kChannels];
+        const float* mls[kChannels];
+        float z[kChannels], m_star[kChannels];
+        int n_act[kChannels], at[kChannels], zrow[kChannels], kfirst[kChannels];
+#pragma unroll
+        for (int u = 0; u < kChannels; ++u) {
+          if (u >= np) break;
+          const int id = min(base + 256 * u, total - 1), kp = id / items, it = id - kp * items;
+          const int sl = it / len, c = it - sl * len, bb = (r0 + c) / d_cb;
+          const size_t unit0 = ((size_t)(m0 + sl) * n_blocks + b0 + bb) * n_splits;
+          src[u] = part_z + (unit0 * h + head) * d_cb + r0 + c - bb * d_cb;
+          mls[u] = part_ml + (unit0 * h + head) * 2;
+          kfirst[u] = kp;
+          n_act[u] = act[sl];
+          at[u] = sl * kSlabBlocks + bb - blk0;
+          zrow[u] = sl * kZPitch + c;
+          m_star[u] = mtab[at[u]];
+          z[u] = 0.f;
         }
-        zs[sl * kZPitch + c] = z;
+        for (int k = 0; k < max_act; k += KP) {
+          float v[kChannels], m[kChannels];
+#pragma unroll
+          for (int u = 0; u < kChannels; ++u) {
+            if (u >= np) break;
+            const size_t o = k + kfirst[u] < n_act[u] ? (size_t)(k + kfirst[u]) * h : 0;
+            v[u] = src[u][o * d_cb];
+            m[u] = mls[u][o * 2];
+          }
+#pragma unroll
+          for (int u = 0; u < kChannels; ++u) {
+            if (u >= np) break;
+            z[u] += k + kfirst[u] < n_act[u] ? exp2f(m[u] - m_star[u]) * v[u] : 0.f;
+          }
+        }
+        if (KP > 1) {     // (uniform) add the chunk parts
+#pragma unroll
+          for (int u = 0; u < kChannels; ++u)
+            if (u < np && base + 256 * u < total) zs[base + 256 * u] = z[u];
+          __syncthreads();
+#pragma unroll
+          for (int u = 0; u < kChannels; ++u)
+            if (u < np && base + 256 * u < items)
+              for (int kp = 1; kp < KP; ++kp) z[u] += zs[base + 256 * u + kp * items];
+          __syncthreads();
+        }
+#pragma unroll
+        for (int u = 0; u < kChannels; ++u)
+          if (u < np && base + 256 * u < items) zs[zrow[u]] = z[u] * itab[at[u]];
+      }
+      for (int t = tid; t < 16 * pad; t += 256) {
+        const int sl = t / pad, c = t - sl * pad;
+        if (sl >= n_seq || c >= len) zs[sl * kZPitch + c] = 0.f;
       }
     }
     __syncthreads();
@@ -356,8 +442,16 @@ int launch_absorb_q_f32(int batch, int h, int d_h, int n_blocks, int groups, int
 int launch_merge_upproj_f32(const DecodeArgs& a) {
   const dim3 grid(a.h * a.groups, (a.batch + 15) / 16, (a.d_h + 63) / 64);
   const bool vec = a.d_h % 4 == 0 && a.d_cb % 4 == 0 && aligned4(a.w_uv, a.dtype);
-#define MLRA_MERGE(T, TO, VEC)                                                                                      \
-  merge_upproj_f32_kernel<T, TO, VEC><<<grid, 256, 0, a.stream>>>(                                                  \
+  // One small slab where it holds all channels of a head: several workgroups then share a CU (510 sequences, 32 heads,
+  // one block of 4 channels, d_h = 256: 33 us, with the large slab 107; one workgroup per head and sequence 41).
+  const bool small = a.n_blocks / a.groups * a.d_cb <= 128;
+#define MLRA_MERGE(T, TO, VEC)                                \
+  do {                                                        \
+    if (small) MLRA_MERGE_SLAB(T, TO, VEC, 128);              \
+    else MLRA_MERGE_SLAB(T, TO, VEC, 512);                    \
+  } while (0)
+#define MLRA_MERGE_SLAB(T, TO, VEC, SLAB)                                                                           \
+  merge_upproj_f32_kernel<T, TO, VEC, SLAB><<<grid, 256, 0, a.stream>>>(                                            \
       a.part_z, a.part_ml, a.seq_lens, (const T*)a.w_uv, (TO*)a.out, a.lse, a.batch, a.h, a.d_h, a.n_blocks, a.d_cb, \
       a.plan.n_splits, a.plan.chunk_tokens, a.out_scale, a.groups, (const T*)a.gate)
 #define MLRA_MERGE_OUT(T, VEC)                                  \
@@ -372,6 +466,7 @@ int launch_merge_upproj_f32(const DecodeArgs& a) {
   }
 #undef MLRA_MERGE_OUT
 #undef MLRA_MERGE
+#undef MLRA_MERGE_SLAB
   return check_launch();
 }
 

@@ -123,11 +123,20 @@ def test_bases_that_are_not_aligned_for_wide_loads(dtype, h, d_cb, d_r, d_h):
          shift=True, folded=True)
 
 
-# a block that straddles the merge's channel slabs, gate and log-sum-exp over several slabs
+# merge: heads of up to 128 channels (small slab) and more, blocks that straddle the slabs' ends (96 and 36 channels over
+# 512), more blocks than a slab's table has, up to four chunk slots (a thread per pair) and from five on (lane groups: 16
+# chunks and more), chunk parts of rows that are not made of runs of four; gate and log-sum-exp of all of them
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_merge_of_several_slabs(dtype):
+@pytest.mark.parametrize("batch,n,h,d_cb,d_r,d_h,nb", [
+    (3, 500, 3, 32, 16, 24, 4), (3, 500, 3, 33, 16, 70, 4), (17, 130, 2, 16, 16, 16, 8), (2, 700, 4, 96, 32, 40, 7),
+    (2, 300, 2, 36, 4, 20, 30), (1, 9000, 2, 61, 3, 64, 2), (3, 5000, 2, 9, 7, 16, 1), (2, 2500, 2, 4, 2, 8, 70),
+    (1, 2300, 5, 30, 2, 128, 20)])
+def test_merge_slabs_and_slots(dtype, batch, n, h, d_cb, d_r, d_h, nb):
+    lens = np.random.default_rng(d_cb).integers(0, n + 1, size=batch)
+    lens[0] = n
     for gated in (False, True):
-        _run(_wl(batch=2, n_min=0, n_max=700, h=4, d_cb=96, d_r=32, d_h=40, n_blocks=7, dtype=dtype), [700, 311], gated=gated)
+        _run(_wl(batch=batch, n_min=0, n_max=n, h=h, d_cb=d_cb, d_r=d_r, d_h=d_h, n_blocks=nb, dtype=dtype), lens.tolist(),
+             gated=gated)
 
 
 def test_head_groups():
