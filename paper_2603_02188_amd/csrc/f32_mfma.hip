@@ -42,6 +42,8 @@ struct F32Params {
 
 template <int KG, int NCT, int TT>
 constexpr size_t f32_lds_bytes() {
+  // (a tile narrower than its 64-channel value groups is read past its rows' ends: into the next rows, and after the last
+  // one into the merge buffer's space; those channels are not stored)
   const size_t tile = (size_t)TT * (16 * KG + 4) * 4, merge = (size_t)64 * (64 * NCT + 4) * 4;
   return (tile > merge ? tile : merge) + 4 * TT * sizeof(long long) + 2 * 64 * sizeof(float);
 }
@@ -53,7 +55,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   static_assert(NTT >= 1, "every wave needs a token tile");
   constexpr int P = 16 * KG + 4, ZP = 64 * NCT + 4;          // floats per tile row / merge row
   constexpr int V4 = 4 * KG;                                 // four-element pieces per tile row
-  constexpr int LPR = V4 <= 32 ? 32 : 64, RPI = 64 / LPR;    // lanes per row, rows per load instruction
+  constexpr int LPR = V4 <= 8 ? 8 : V4 <= 32 ? 32 : 64, RPI = 64 / LPR;   // lanes per row, rows per load instruction
   constexpr int CI = (V4 + LPR - 1) / LPR, NR = TT / (4 * RPI);
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   float* const tile = (float*)smem;
@@ -328,6 +330,12 @@ template <typename T, bool VEC>
 int launch_typed(const DecodeArgs& a, F32Params& p, int ht) {
   const int D = a.d_cb + a.d_r;
   p.n_hg = (a.h + 16 * ht - 1) / (16 * ht);
+  // Tiles of 32 channels for the smallest blocks: with 96, most loads and three quarters of the score MFMAs are padding
+  // (184 bf16 sequences of 194 tokens x 64 blocks of 4 + 2 channels: 153 us, with 96 channels 289, the plain kernel 148).
+  if (D <= 32)
+    return ht == 4   ? launch_one<T, VEC, 2, 1, 64, 4>(a, p)
+           : ht == 2 ? launch_one<T, VEC, 2, 1, 64, 2>(a, p)
+                     : launch_one<T, VEC, 2, 1, 64, 1>(a, p);
   if (a.d_cb <= 64 && D <= 96)
     return ht == 4   ? launch_one<T, VEC, 6, 1, 64, 4>(a, p)
            : ht == 2 ? launch_one<T, VEC, 6, 1, 64, 2>(a, p)

@@ -94,13 +94,14 @@ def _wl(**kw):
 LENS = [0, 1, 63, 64, 65, 129, 300, 511]
 
 
-# heads: one tile, its edges, 2 and 4 tiles per workgroup and a remainder; dims: the edges of each register size (96 / 64,
+# heads: one tile, its edges, 2 and 4 tiles per workgroup and a remainder; dims: the edges of each register size (32, 96 / 64,
 # 192 / 128, 320 / 256 channels), beyond the last one (the plain kernel), odd ones (element loads), one channel
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("h,d_cb,d_r,d_h,nb", [
     (1, 64, 32, 64, 1), (16, 64, 32, 65, 2), (17, 60, 36, 24, 2), (33, 61, 3, 63, 1), (8, 65, 32, 64, 2),
     (64, 128, 64, 128, 1), (65, 96, 32, 128, 1), (20, 127, 65, 66, 1), (130, 68, 24, 40, 2), (33, 129, 64, 64, 1),
-    (64, 256, 64, 64, 1), (17, 253, 67, 30, 1), (5, 260, 64, 64, 1), (3, 1, 2, 6, 80), (6, 7, 2, 130, 90)])
+    (64, 256, 64, 64, 1), (17, 253, 67, 30, 1), (5, 260, 64, 64, 1), (5, 16, 16, 20, 3),
+    (17, 30, 2, 24, 2), (64, 24, 8, 32, 2), (33, 31, 1, 16, 2), (40, 17, 16, 30, 2), (3, 1, 2, 6, 80), (6, 7, 2, 130, 90)])
 def test_dims_and_heads(dtype, h, d_cb, d_r, d_h, nb):
     _run(_wl(batch=len(LENS), n_min=0, n_max=511, h=h, d_cb=d_cb, d_r=d_r, d_h=d_h, n_blocks=nb, dtype=dtype), LENS)
 
