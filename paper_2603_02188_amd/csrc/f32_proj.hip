@@ -32,7 +32,9 @@ __device__ __forceinline__ f32x4 cut_row4(f32x4 v, int k, int len) {
 }
 
 // ------------------------------------------------------------------------------------------------
-// absorb_q.  One workgroup per (head, block, 16 sequences); wave w produces channel tiles w and w + 4 of every eight.
+// absorb_q.  One workgroup per (head, block, 16 sequences); wave w produces channel tiles w and w + 4 of every eight
+// (SPLIT, for blocks of at most two tiles: every wave produces both, from a quarter of the k groups each, and the four
+// parts are added through LDS).
 // Query rows are the A operand, weight rows (one per latent channel, contiguous along d_h) the B operand; k is dealt
 // as 16 i + 4 q + j (q = lane / 16, j = step), so that both are read four elements at a time, straight from global
 // memory: a weight element is used by one workgroup only, and U k groups (3 U loads) are in flight per wave.
@@ -42,7 +44,7 @@ __device__ __forceinline__ f32x4 cut_row4(f32x4 v, int k, int len) {
 // Bound by the weights' stream at small batches: 8 sequences, 128 heads, 4 blocks x 128 channels in fp32 (33.5 MB)
 // take 9.5 us; one workgroup per sequence, which read them once each, took 53.
 // ------------------------------------------------------------------------------------------------
-template <typename T, bool VEC, int U>   // U: k groups in flight
+template <typename T, bool VEC, int U, bool SPLIT>   // U: k groups in flight
 __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__ q_nope, const T* __restrict__ w_uk,
                                                            T* __restrict__ q_abs, int batch, int h, int d_h,
                                                            int n_blocks, int groups, int d_cb, float fold,
@@ -63,13 +65,14 @@ __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__
   const int q_head = (b / (n_blocks / groups)) * h + head;   // Eq. (6): block b serves the heads of its group
   const size_t ldw = (size_t)h * d_h;
   const T* const qrow = q_nope + ((size_t)(m0 + min(r16, n_seq - 1)) * q_heads + q_head) * d_h;
-  for (int ct0 = wave; ct0 * 16 < d_cb; ct0 += 8) {
+  constexpr int TS = SPLIT ? 1 : 4;      // distance of this wave's two channel tiles
+  for (int ct0 = SPLIT ? 0 : wave; ct0 * 16 < d_cb; ct0 += 8) {
     const T* wrow[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t)
-      wrow[t] = w_uk + ((size_t)b * d_cb + min((ct0 + 4 * t) * 16 + r16, d_cb - 1)) * ldw + (size_t)head * d_h;
+      wrow[t] = w_uk + ((size_t)b * d_cb + min((ct0 + TS * t) * 16 + r16, d_cb - 1)) * ldw + (size_t)head * d_h;
     f32x4 acc[2] = {};
-    for (int k0 = 0; k0 < d_h; k0 += 16 * U) {
+    for (int k0 = SPLIT ? wave * 16 * U : 0; k0 < d_h; k0 += (SPLIT ? 64 : 16) * U) {
       Raw a[U], w[U][2];
 #pragma unroll
       for (int i = 0; i < U; ++i) {
@@ -100,9 +103,17 @@ __global__ __launch_bounds__(256) void absorb_q_f32_kernel(const T* __restrict__
 #pragma unroll
       for (int t = 0; t < 2; ++t) acc[t] += sum[t][0];
     }
+    if constexpr (SPLIT) {
+      __shared__ __attribute__((aligned(16))) f32x4 part[2][4][64];
 #pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const int c = (ct0 + 4 * t) * 16 + r16;
+      for (int t = 0; t < 2; ++t) part[t][wave][lane] = acc[t];
+      __syncthreads();
+      if (wave >= 2) return;               // wave t adds and stores tile t
+      acc[0] = (part[wave][0][lane] + part[wave][1][lane]) + (part[wave][2][lane] + part[wave][3][lane]);
+    }
+#pragma unroll
+    for (int t = 0; t < (SPLIT ? 1 : 2); ++t) {
+      const int c = (SPLIT ? wave : ct0 + 4 * t) * 16 + r16;
 #pragma unroll
       for (int i = 0; i < 4; ++i)
         if (c < d_cb && 4 * q + i < n_seq)
@@ -417,17 +428,21 @@ int launch_absorb_q_f32(int batch, int h, int d_h, int n_blocks, int groups, int
                         void* q_rope_out, int d_r) {
   const dim3 grid(h, n_blocks + (q_rope_out ? 1 : 0), (batch + 15) / 16);
   const bool vec = d_h % 4 == 0 && aligned4(q_nope, dtype) && aligned4(w_uk, dtype);
-#define MLRA_ABSORB_U(T, VEC, U)                                                                                     \
-  absorb_q_f32_kernel<T, VEC, U><<<grid, 256, 0, stream>>>((const T*)q_nope, (const T*)w_uk, (T*)q_abs, batch, h,    \
-                                                           d_h, n_blocks, groups, d_cb, fold, (const T*)q_rope,      \
-                                                           (T*)q_rope_out, d_r)
-  // as many k groups at a time as a short row has: the rest of a step is multiplied with zeros (16 sequences, 128 heads,
-  // 4 blocks x 128 channels, d_h = 64: 6.7 us with four groups, 9.9 with eight)
-#define MLRA_ABSORB(T, VEC)                       \
-  do {                                            \
-    if (d_h <= 32) MLRA_ABSORB_U(T, VEC, 2);      \
-    else if (d_h <= 64) MLRA_ABSORB_U(T, VEC, 4); \
-    else MLRA_ABSORB_U(T, VEC, 8);                \
+#define MLRA_ABSORB_U(T, VEC, U, SPLIT)                                                                              \
+  absorb_q_f32_kernel<T, VEC, U, SPLIT><<<grid, 256, 0, stream>>>(                                                   \
+      (const T*)q_nope, (const T*)w_uk, (T*)q_abs, batch, h, d_h, n_blocks, groups, d_cb, fold, (const T*)q_rope,    \
+      (T*)q_rope_out, d_r)
+  // As many k groups at a time as a short row has: the rest of a step is multiplied with zeros (16 sequences, 128 heads,
+  // 4 blocks x 128 channels, d_h = 64: 6.7 us with four groups, 9.9 with eight); element loads go four groups at a time.
+  // Long rows of narrow blocks are shared by the waves (60 sequences x 8 heads x 4 channels, d_h = 256: 4.3 us, by one
+  // wave 6.7).
+#define MLRA_ABSORB(T, VEC)                                                 \
+  do {                                                                      \
+    if (d_h <= 32) MLRA_ABSORB_U(T, VEC, 2, false);                         \
+    else if (d_h <= 64) MLRA_ABSORB_U(T, VEC, 4, false);                    \
+    else if (d_cb <= 32 && d_h <= 128) MLRA_ABSORB_U(T, VEC, 2, true);      \
+    else if (d_cb <= 32) MLRA_ABSORB_U(T, VEC, 4, true);                    \
+    else MLRA_ABSORB_U(T, VEC, (VEC ? 8 : 4), false);                       \
   } while (0)
   if (dtype == MLRA_BF16) {
     if (vec) MLRA_ABSORB(bf16_t, true); else MLRA_ABSORB(bf16_t, false);

@@ -12,9 +12,11 @@ from paper_2603_02188_amd import binding as mlra
 pytestmark = pytest.mark.gpu
 
 
-# depths: one step of each form (32, 64, 128), several steps, a remainder, rows that are not made of runs of four
+# depths: one step of each form (32, 64, 128), several steps, a remainder, rows that are not made of runs of four; blocks
+# of one and two channel tiles, whose rows the waves share
 @pytest.mark.parametrize("batch,h,d_h,nb,d_cb", [(16, 16, 32, 2, 64), (16, 16, 64, 4, 64), (8, 32, 128, 4, 128),
-                                                 (17, 12, 200, 2, 100), (5, 8, 1024, 2, 24), (9, 8, 127, 2, 61)])
+                                                 (17, 12, 200, 2, 100), (5, 8, 1024, 2, 24), (9, 8, 127, 2, 61),
+                                                 (40, 8, 128, 2, 16), (33, 8, 200, 2, 17), (18, 8, 258, 2, 31)])
 def test_absorb_adds_as_a_tree(batch, h, d_h, nb, d_cb):
     print(f"[case] absorb precision B={batch} h={h} d_h={d_h} NB={nb} d_cb={d_cb}", flush=True)
     gen = torch.Generator().manual_seed(d_h)
