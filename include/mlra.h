@@ -282,12 +282,13 @@ MLRA_API int mlra_probe_shader_clock(long long* out, int32_t spin_us, void* stre
  * the total number of query heads, groups is 1 for mlra_decode_attn / mla_decode_attn and 2 for
  * mlra2_decode_attn, dtype the cache dtype, max_seq_len = max_pages_per_seq * page_size.  info is a HOST
  * array of 6 values:
- *   [0] decode kernel: 0 generic, 1 MFMA plain form, 2 MFMA PAIRED form (two blocks per workgroup),
- *       3 MFMA GLA form (256-channel latent heads), 4 MFMA MLA kernel (one 512-channel latent)
+ *   [0] decode kernel: 0 plain kernel without matrix instructions (latent blocks wider than the others take), 1 MFMA
+ *       plain form, 2 MFMA PAIRED form (two blocks per workgroup), 3 MFMA GLA form (256-channel latent heads), 4 MFMA
+ *       MLA kernel (one 512-channel latent), 5 fp32 matrix instructions (fp32 caches and every other bf16 shape)
  *   [1] chunk slots per (sequence, block)     [2] uniform chunk length in tokens
  *   [3] > 0: chunk lengths may follow the sequence lengths (planning kernel), with this many chunks per block
  *       as the target                          [4] 1: a batch of nearly equal lengths is then left uncut
- *   [5] 1: the merge + up-projection epilogue runs on MFMA, 0: generic
+ *   [5] 1: the merge + up-projection epilogue is the bf16 one, 0: the fp32 one
  * Returns MLRA_OK, or MLRA_ERR_NULL / MLRA_ERR_SHAPE / MLRA_ERR_DTYPE as the decode entry points would. */
 MLRA_API int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks, int32_t d_cb,
                                    int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype, int32_t* info);

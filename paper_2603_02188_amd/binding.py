@@ -465,7 +465,7 @@ def gqa_decode_attn(k_pool: torch.Tensor, v_pool: torch.Tensor, page_table: torc
     return out
 
 
-DECODE_KERNELS = ("generic", "mfma", "mfma-paired", "mfma-gla", "mfma-mla")
+DECODE_KERNELS = ("generic", "mfma", "mfma-paired", "mfma-gla", "mfma-mla", "f32")
 
 
 def mlra_decode_plan_info(batch: int, h: int, d_h: int, groups: int, n_blocks: int, d_cb: int, d_r: int,

@@ -448,7 +448,8 @@ int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups,
   info[0] = decode_mfma_supported(a) ? (decode_mfma_paired(a.h, n_blocks) ? 2 : 1)
             : decode_gla_supported(a) ? 3
             : mla_mfma_supported(a)  ? 4
-                                     : 0;
+            : decode_f32_supported(a) ? 5
+                                      : 0;
   info[1] = a.plan.n_splits;
   info[2] = a.plan.chunk_tokens;
   info[3] = a.plan.target_chunks;

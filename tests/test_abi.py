@@ -155,7 +155,11 @@ def test_workload_shapes_take_the_fast_paths():
         args.update(kw)
         return mlra.mlra_decode_plan_info(**args)
 
-    assert info("C1")["kernel"] == "generic"                         # fp32 cache
+    assert info("C1")["kernel"] == "f32"                             # fp32 cache: fp32 matrix instructions
+    # ... up to 256 latent and 320 channels in all, bf16 storage as well; the plain kernel beyond
+    for dt in (torch.float32, torch.bfloat16):
+        assert [info("C1", d_cb=d_cb, d_r=d_r, dtype=dt)["kernel"] for d_cb, d_r in
+                ((1, 2), (256, 62), (257, 2), (254, 66), (254, 67))] == ["f32", "f32", "generic", "f32", "generic"]
     c2 = info("C2")
     assert (c2["kernel"], c2["chunk_slots"], c2["chunk_tokens"], c2["merge_mfma"]) == ("mfma", 16, 1024, True)
     c3 = info("C3")
@@ -164,7 +168,7 @@ def test_workload_shapes_take_the_fast_paths():
     assert c4["kernel"] == "mfma" and c4["target_chunks"] == 64 and c4["chunk_slots"] == 32 and c4["merge_mfma"]
     c5 = info("C5")
     assert (c5["kernel"], c5["chunk_slots"], c5["target_chunks"]) == ("mfma", 1, 0)
-    assert info("C5", page_size=16)["kernel"] == "mfma" and info("C5", page_size=48)["kernel"] == "generic"
+    assert info("C5", page_size=16)["kernel"] == "mfma" and info("C5", page_size=48)["kernel"] == "f32"
     m2, g2 = info("M2"), info("G2")
     assert (m2["kernel"], m2["chunk_slots"], m2["target_chunks"]) == ("mfma-paired", 2, 0)
     assert (g2["kernel"], g2["chunk_slots"], g2["target_chunks"]) == ("mfma-gla", 2, 0)

@@ -81,6 +81,7 @@ def _run(wl, lens, shift=False, folded=False, out_dtype=torch.float32, gated=Fal
     # probabilities to bf16: 2^-9 of a score of up to 8 and 2^-9 of the sum
     info = mlra.mlra_decode_plan_info(wl.batch, wl.h, wl.d_h, wl.groups, wl.n_blocks, wl.d_cb, wl.d_r, wl.page_size,
                                       cache.max_seq_len, q_abs.dtype)
+    assert (info["kernel"] == "generic") == (wl.d_cb > 256)
     tol = 2e-2 if info["kernel"].startswith("mfma") else 1e-4
     lse_err = float(np.max(np.abs(got[live] - ref_lse[live])))
     print(f"       lse {lse_err:.3e}", flush=True)
