@@ -15,9 +15,9 @@ import sys
 from concurrent.futures import ThreadPoolExecutor
 
 try:
-    from .check_isa import find_overlaps, find_reserved_acc_uses
+    from .check_isa import find_overlaps, find_reserved_acc_uses, find_scratch_in_loops
 except ImportError:  # run as a script
-    from check_isa import find_overlaps, find_reserved_acc_uses
+    from check_isa import find_overlaps, find_reserved_acc_uses, find_scratch_in_loops
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -71,6 +71,11 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         bad = find_reserved_acc_uses(text, r"decode_mfma_kernel", 136)
         if bad:
             raise RuntimeError(f"{src}: compiler-generated code touches the reserved accumulation registers:\n" +
+                               "\n".join(f"  {asm}:{ln}: {text}" for ln, text in bad[:20]))
+        # a spill inside the MLA kernel's tile loop would wait for the tile loads in flight
+        bad = find_scratch_in_loops(text, r"mla_mfma_kernel")
+        if bad:
+            raise RuntimeError(f"{src}: scratch accesses inside the loop of the MLA kernel:\n" +
                                "\n".join(f"  {asm}:{ln}: {text}" for ln, text in bad[:20]))
         return obj
 

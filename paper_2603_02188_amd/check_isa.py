@@ -3,7 +3,8 @@
 An MFMA with a destination wider than four registers must not write registers it still reads as srcA /
 srcB (the narrow forms, 16x16 results of four registers, read their operands before the first write and
 may overlap).  The build runs this over every kernel's assembly and fails if such an instruction was
-emitted.
+emitted.  Two more scans are for single kernels: accumulation registers that belong to inline asm, and spills inside a
+loop.
 """
 from __future__ import annotations
 
@@ -63,6 +64,27 @@ def find_reserved_acc_uses(asm_text: str, kernel_pattern: str, reserved: int):
             if lo < reserved:
                 bad.append((ln, text))
                 break
+    return bad
+
+
+_BLOCK = re.compile(r"^(\.LBB\w+:|; %bb\.\d+:)(.*)$")
+
+
+def find_scratch_in_loops(asm_text: str, kernel_pattern: str):
+    """Scratch accesses (spills, reloads) in the loop blocks of kernels whose name matches kernel_pattern: in a loop that
+    counts its outstanding loads, a reload waits for every tile load issued before it.  The compiler's comments say which
+    blocks belong to a loop."""
+    bad = []
+    in_kernel = in_loop = False
+    for ln, line in enumerate(asm_text.splitlines(), 1):
+        text = line.strip()
+        block = _BLOCK.match(text)
+        if block:
+            in_loop = "Loop" in block.group(2)
+        elif re.match(r"^[A-Za-z_$][\w.$]*:", text):
+            in_kernel, in_loop = re.search(kernel_pattern, text) is not None, False
+        elif in_kernel and in_loop and re.match(r"(scratch_|buffer_(load|store)_\w+ .*\boffset:.*\bs\[0:3\])", text):
+            bad.append((ln, text))
     return bad
 
 

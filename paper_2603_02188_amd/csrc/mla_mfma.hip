@@ -17,8 +17,9 @@
 // A wave's chain through a tile (LDS latencies, softmax, the hand-overs) is 2.5 times the 1088 cycles of matrix pipe in
 // it, so a second workgroup on the CU matters more than deeper buffering: the two-stage form takes 256 registers per wave,
 // all of them (accumulators 128, queries 72, the rest operands in flight), and whatever can be recomputed is, because a
-// spill inside the loop also waits for the tile loads (six registers are spilled in front of it and reloaded after it).  64 heads x 512 + 64 channels, two stages against four stages of the same width with one workgroup
-// per CU: 256 sequences of 2176 tokens x 128 heads 222 -> 185 us, 128 sequences of 512 to 8192 in chunks 275 -> 221, 128
+// spill inside the loop also waits for the tile loads (six registers are spilled in front of it and reloaded after it;
+// the build fails if the loop holds a scratch access).  64 heads x 512 + 64 channels, two stages against four stages of
+// the same width with one workgroup per CU: 256 sequences of 2176 tokens x 128 heads 222 -> 185 us, 128 sequences of 512 to 8192 in chunks 275 -> 221, 128
 // sequences of 4352 (one workgroup per CU) 221 -> 212.  Measured and not kept: 16-token tiles in four stages
 // (198 / 237 / 250 us), two groups of four waves one barrier apart in one workgroup (223 / 260 / 215), 32 heads x 16
 // tokens per wave (216 / 264 / 214), the channels of the scores split over two waves (224 / 265 / 298).
