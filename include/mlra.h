@@ -259,7 +259,7 @@ MLRA_API int gqa_decode_attn(const void* k_pool, const void* v_pool, const int32
  * mla_decode_attn call records, for at most max_calls calls, the start and the end of its main decode
  * kernel and of its merge + up-projection epilogue kernel into HIP events: the kernel's own execution
  * interval on the bf16 fast paths (what a kernel trace reports as its duration; planning kernels that
- * precede the decode kernel are not part of it), stream markers around the kernel on the generic paths.
+ * precede the decode kernel are not part of it), stream markers around the kernel on the others.
  * mlra_kernel_timing_end waits for those events, stores the average duration in milliseconds of the two
  * kernels and the number of calls measured into the given HOST pointers, and releases the events.
  * begin allocates host event objects; neither call belongs in a latency-critical loop. */

@@ -16,7 +16,7 @@
 //   * Z^T and the row sums live in accumulation registers a0..a135 that only inline asm names (the MFMAs of
 //     the main loop are asm statements); the compiler never sees them as values.
 //   * The chunk's partial leaves as the normalised row z / l in bf16 with (m, l) in fp32 beside it (fp32,
-//     un-normalised, for shapes whose epilogue is the generic merge kernel).
+//     un-normalised, for shapes whose epilogue is the fp32 merge kernel).
 //
 // PAIRED form, for blocks that serve 64 heads (MLRA-2, Eq. (6), at h = 128): one workgroup owns two
 // neighbouring latent blocks and 64 heads.  The head half hw of a wave becomes its block: wave (hw, tw)
@@ -1015,7 +1015,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
       }
     }
   } else {
-    // (for the generic merge kernel, which takes shapes whose tables do not fit the MFMA epilogue's LDS: fp32, not normalised)
+    // (for the fp32 merge kernel, which takes the shapes that the bf16 epilogue does not: fp32, not normalised)
     for (int idx = tid; idx < kHeadsWG * (kDcb / 4); idx += 256) {
       const int hl = idx / (kDcb / 4), f4 = idx % (kDcb / 4);
       const int row_blk = (PAIRED && !GLA) ? blk0 + (hl >> 6) : blk0;

@@ -42,7 +42,7 @@ struct MfmaParams {
   float scale_log2;
   int split_major = 0;        // (MLA) dispatch order: all sequences' first chunks, then all second ones, ...
   int rows_bf16;              // 1: part_z receives each chunk's partial as z / l rounded to bf16, [..][chunk][head][channels]
-                              // (what the MFMA epilogue merges); 0: fp32 partials, not normalised (generic merge, MLA)
+                              // (what the MFMA epilogue merges); 0: fp32 partials, not normalised (fp32 merge, MLA)
 };
 
 // LDS has 64 four-byte banks; a 128-bit read is served 16 lanes at a time and a 64-bit transpose read

@@ -191,7 +191,7 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
     a.balanced = launch_plan_chunks(a) == MLRA_OK;
   // the MLRA MFMA kernels hand the epilogue normalised bf16 rows (one per chunk) instead of fp32 partials
   a.rows_bf16 = merge_upproj_mfma_supported(a) && (decode_mfma_supported(a) || decode_gla_supported(a));
-  // the MFMA launchers record their kernel's own start and end; the generic kernels are bracketed by stream markers
+  // the MFMA launchers record their kernel's own start and end; the others are bracketed by stream markers
   const bool main_fast = decode_mfma_supported(a) || decode_gla_supported(a) || mla_mfma_supported(a);
   const bool epi_fast = merge_upproj_mfma_supported(a);
   if (a.t_main.on() && !main_fast) (void)hipEventRecord(a.t_main.start, a.stream);

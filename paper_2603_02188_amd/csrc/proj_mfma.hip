@@ -490,8 +490,10 @@ static size_t merge_upproj_lds_bytes(const DecodeArgs& a, bool direct) {
 }
 constexpr size_t kMergeLdsLimit = 160 * 1024;
 
-// Up to 1024 latent channels and 128 (block, chunk) slots per sequence, as long as z rows and slots together stay
-// moderate (at most 98,176 bytes at 64 per z channel and 256 per slot); everything else takes the fp32 epilogue.
+// Up to 1024 latent channels and 128 (block, chunk) slots per sequence, and at most 98,176 bytes of both at 64 per z
+// channel and 256 per slot; everything else takes the fp32 epilogue (and fp32 partials).  This is no limit of the kernel:
+// with 128 bytes per slot and 32 KiB of weights it occupies up to 112 KiB of LDS here, and 256 slots at 512 channels (one
+// sequence of 8K tokens and up, four blocks) would fit; whether it is the better epilogue there has not been measured.
 bool merge_upproj_mfma_supported(const DecodeArgs& a) {
   const int bpg = a.n_blocks / a.groups;
   return a.dtype == MLRA_BF16 && a.d_h == kDh && a.d_cb % 32 == 0 && bpg * a.d_cb <= 1024 &&

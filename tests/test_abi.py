@@ -139,7 +139,7 @@ def test_binding_fails_loudly_without_the_library(monkeypatch, tmp_path):
 
 def test_workload_shapes_take_the_fast_paths():
     """Host logic: the benchmark shapes run on the MFMA kernels with the context split they were tuned with
-    (a shape that silently fell back to a generic kernel, or lost its planning mode, would still pass
+    (a shape that silently fell back to a slower kernel, or lost its planning mode, would still pass
     parity)."""
     import numpy as np
     import torch
@@ -177,7 +177,8 @@ def test_workload_shapes_take_the_fast_paths():
     assert mla["kernel"] == "mfma-mla" and mla["target_chunks"] == 256 and mla["single_if_uniform"]
     two = info("M2", batch=128, max_seq_len=8192)
     assert two["kernel"] == "mfma-paired" and two["chunk_slots"] == 4 and two["single_if_uniform"]
-    # 8 blocks x 16 chunks: the MFMA epilogue's LDS tables would exceed 160 KiB, so the generic epilogue runs
+    # 8 blocks x 16 chunks: more (z channels, chunk slots) than the bf16 epilogue takes (its bound on both together, not the
+    # 160 KiB of LDS: the kernel would use 113 KiB), so the fp32 epilogue runs
     big = info("C3", batch=2, n_blocks=8, max_seq_len=2048)
     assert (big["kernel"], big["chunk_slots"], big["merge_mfma"]) == ("mfma", 16, False)
     assert info("C3", batch=2, n_blocks=4, max_seq_len=2048)["merge_mfma"]

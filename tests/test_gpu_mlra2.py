@@ -95,7 +95,7 @@ def test_mlra2_length_proportional_chunks_on_a_ragged_long_batch():
 
 
 def test_mlra2_two_blocks_is_gla2_shape():
-    # n_blocks = 2: one block per group (GLA-2, Eq. (3)); d_cb = 2 d_h runs on the generic kernels
+    # n_blocks = 2: one block per group (GLA-2, Eq. (3)); d_cb = 2 d_h runs on the fp32 kernels
     wl = gen.WORKLOADS["C1"].scaled(name="gla2-shape", batch=2, n_blocks=2, d_cb=64, d_h=32, h=8, d_r=16,
                                     n_min=50, n_max=300, groups=2, dtype="bf16")
     inp = gen.make_decode_inputs(wl, poison=True)

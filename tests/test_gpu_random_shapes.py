@@ -90,9 +90,9 @@ def test_random_shapes_match_the_oracle(first):
 
 
 def test_eight_blocks_sixteen_chunks_epilogue_tables_exceed_lds():
-    """8 blocks x 128 channels with 16 chunks per sequence: the MFMA epilogue's tables (1024 latent channels
-    of z rows plus 128 merge weights per sequence) would need more than the 160 KiB of LDS, so the call has
-    to take the generic merge + up-projection (and must not fail at launch)."""
+    """8 blocks x 128 channels with 16 chunks per sequence: 1024 latent channels of z rows plus 128 merge weights per
+    sequence are beyond the bf16 epilogue's bound on its tables (98,176 bytes at 64 per channel and 256 per slot; with
+    the weights it would occupy 113 KiB of LDS), so the call has to take the fp32 merge + up-projection."""
     wl = gen.WORKLOADS["C3"].scaled(name="eight-blocks", batch=2, n_min=1500, n_max=2048, n_blocks=8, index=2001)
     lens = np.array([2048, 1501], dtype=np.int32)
     info = mlra.mlra_decode_plan_info(wl.batch, wl.h, wl.d_h, 1, wl.n_blocks, wl.d_cb, wl.d_r, wl.page_size, 2048,
