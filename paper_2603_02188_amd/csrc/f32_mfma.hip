@@ -17,8 +17,8 @@
 //   * the next tile is in flight in registers while a tile is worked on; the addresses of its rows come from a
 //     table in LDS that is computed one more tile ahead (one page lookup per token, not one per lane).
 // Bound by the matrix pipe: a tile of 64 tokens x 192 channels x 64 heads is 10240 cycles of MFMA per SIMD against
-// 2500 of LDS reads and 48 KiB of loads.  fp32, 4 blocks x 128 channels, 128 heads: 105 TFLOP/s on 8 sequences of 8192
-// tokens (of 157 nominal), 59 us on 8 of 300 to 2048 (the VALU kernel it replaces: 1710 us), of which about 12 us are
+// 2500 of LDS reads and 48 KiB of loads.  fp32, 4 blocks x 128 channels, 128 heads: 100 TFLOP/s on 8 sequences of 8192
+// tokens (of 157 nominal), 58 us on 8 of 300 to 2048 (the VALU kernel it replaces: 1710 us), of which about 12 us are
 // start-up, write-out and the launch.
 #include "f32_tile.h"
 
