@@ -13,6 +13,8 @@
 #include "mlra_internal.h"
 #include "mfma_tile.h"
 
+#include <algorithm>
+
 namespace mlra {
 namespace {
 
@@ -244,98 +246,103 @@ __global__ void skinny_gemm_generic_kernel(const T* __restrict__ A, int lda, int
   out_part[(size_t)m * ld_out + segs.out_col[seg] + j] = acc;
 }
 
+constexpr int kFinishThreads = 512;
+
 __device__ __forceinline__ float block_sum(float v, float* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  __syncthreads();
   if (lane == 0) red[wave] = v;
   __syncthreads();
   float s = 0.f;
-  for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += red[w];
+  for (int w = 0; w < kFinishThreads / 64; ++w) s += red[w];
   return s;
 }
 
-
-// Step 2.  One workgroup per sequence.  Columns of the summed down-projection: [0, d_cq) C^Q,
-// [d_cq, d_cq + d_c) C^KV, then d_r RoPE-key channels.
-template <typename T, typename TC>
-__global__ __launch_bounds__(256) void pre_finish_down_kernel(
+// Step 2.  Columns of the summed down-projection: [0, d_cq) C^Q, [d_cq, d_cq + d_c) C^KV, then d_r RoPE-key channels.  Two
+// workgroups per sequence, one for C^Q and one for the rest: the two norms have nothing in common.
+// The kernel is a chain of memory round trips, so a thread has the slices of its W neighbouring columns all in flight
+// together (one round at 2112 columns in 14 slices: 64 sequences 9.0 -> 4.6 us, hardly more than an empty kernel; one
+// workgroup of 256 threads per sequence had single columns and everything after the reduction in a row), the angles are computed by the last wavefronts while the others sum,
+// and the page lookup and the gains are fetched in front of the reduction that does not need them.
+template <typename T, typename TC, int W>   // W = 4: d_cq, d_c and d_r are multiples of four
+__global__ __launch_bounds__(kFinishThreads) void pre_finish_down_kernel(
     const float* __restrict__ part, int n_slices, int batch, int d_cq, int d_c, int d_r, int n_blocks,
     const T* __restrict__ gain_q, const T* __restrict__ gain_kv, float alpha_q, float alpha_kv, float eps,
     float rope_base, const int32_t* __restrict__ positions, const int32_t* __restrict__ page_table, int max_pages,
     int page_size, T* __restrict__ c_q, TC* __restrict__ latent, TC* __restrict__ rope_pool,
     float* __restrict__ cs_tab) {
-  extern __shared__ float row[];             // [d_cq + d_c + d_r] summed projections
-  __shared__ float red[4];
+  typedef __attribute__((ext_vector_type(W == 1 ? 2 : W))) float vec_t;   // (W = 1 uses element 0)
+  extern __shared__ __attribute__((aligned(16))) float row[];   // this workgroup's summed columns, times their gains
+  __shared__ float red[kFinishThreads / 64];
   __shared__ float cs_sh[256];               // (cos, sin) per RoPE frequency of this sequence's position
   const int s = blockIdx.x, tid = threadIdx.x;
+  const bool kv = blockIdx.y != 0;
   const int n1 = d_cq + d_c + d_r;
+  const int c0 = kv ? d_cq : 0, n_norm = kv ? d_c : d_cq, nc = kv ? d_c + d_r : d_cq;
+  const T* const gain = kv ? gain_kv : gain_q;
   const int pos = positions[s];
-  float ss_q = 0.f, ss_kv = 0.f;
-  // kU columns per thread and kKK slices at a time, all loads of such a round in flight together: the
-  // kernel is a chain of memory round trips (one workgroup per sequence), so it wants as few rounds as
-  // possible (the benchmark shape, 2112 columns in 14 slices, takes one)
-  constexpr int kU = 9, kKK = 16;
-  for (int j0 = 0; j0 < n1; j0 += kU * 256) {
-    float v[kU];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) v[u] = 0.f;
-    for (int k = 0; k < n_slices; k += kKK) {
-      float t[kKK][kU];
-#pragma unroll
-      for (int kk = 0; kk < kKK; ++kk) {
-        const float* src = part + ((size_t)min(k + kk, n_slices - 1) * batch + s) * n1;
-#pragma unroll
-        for (int u = 0; u < kU; ++u) t[kk][u] = src[min(j0 + u * 256 + tid, n1 - 1)];   // unconditional: all in flight
-      }
-#pragma unroll
-      for (int kk = 0; kk < kKK; ++kk)
-#pragma unroll
-        for (int u = 0; u < kU; ++u) v[u] += (k + kk < n_slices) ? t[kk][u] : 0.f;   // slices summed in order
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int j = j0 + u * 256 + tid;
-      if (j < n1) {
-        row[j] = v[u];
-        if (j < d_cq) ss_q += v[u] * v[u];
-        else if (j < d_cq + d_c) ss_kv += v[u] * v[u];
-      }
-    }
-  }
-  ss_q = block_sum(ss_q, red);
-  ss_kv = block_sum(ss_kv, red);
-  const float rq = alpha_q * rsqrtf(ss_q / d_cq + eps), rkv = alpha_kv * rsqrtf(ss_kv / d_c + eps);
+  const int page = kv && pos >= 0 ? page_table[(size_t)s * max_pages + pos / page_size] : 0;
   // cos / sin of position * theta_l.  Positions reach 10^5 and beyond, so the product and its reduction
   // to [-pi, pi] are done in double (a float angle would be off by ~1e-2 rad there); the reduced angle is
   // then accurate to ~1e-11 and float sine / cosine of it are good to a few ulp.
-  if (tid < d_r / 2) {
-    const double theta = exp2(-2.0 * tid / d_r * log2((double)rope_base));
+  const int freq = tid - (kFinishThreads - 128);
+  if (kv && freq >= 0 && freq < d_r / 2) {
+    const double theta = exp2(-2.0 * freq / d_r * log2((double)rope_base));
     const double ang = (double)max(pos, 0) * theta;
     const double two_pi = 6.283185307179586476925287;
     const float red_ang = (float)(ang - two_pi * rint(ang / two_pi));
     float sn, cs;
     sincosf(red_ang, &sn, &cs);
-    cs_sh[2 * tid] = (float)cs;
-    cs_sh[2 * tid + 1] = (float)sn;
-    cs_tab[((size_t)s * (d_r / 2) + tid) * 2 + 0] = (float)cs;   // for the query side (step 4)
-    cs_tab[((size_t)s * (d_r / 2) + tid) * 2 + 1] = (float)sn;
+    cs_sh[2 * freq] = cs;
+    cs_sh[2 * freq + 1] = sn;
+    cs_tab[((size_t)s * (d_r / 2) + freq) * 2 + 0] = cs;   // for the query side (step 4)
+    cs_tab[((size_t)s * (d_r / 2) + freq) * 2 + 1] = sn;
   }
-  for (int j = tid; j < d_cq; j += 256)
-    store_f32(c_q, (size_t)s * d_cq + j, row[j] * rq * (gain_q ? load_f32(gain_q, j) : 1.f));
+  float ss = 0.f;
+  constexpr int kKK = 16;
+  for (int j = W * tid; j < nc; j += W * kFinishThreads) {
+    float v[W], gn[W];
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      v[e] = 0.f;
+      gn[e] = gain && j < n_norm ? load_f32(gain, j + e) : 1.f;
+    }
+    for (int k = 0; k < n_slices; k += kKK) {
+      vec_t t[kKK];
+#pragma unroll
+      for (int kk = 0; kk < kKK; ++kk) {
+        const float* src = part + ((size_t)min(k + kk, n_slices - 1) * batch + s) * n1 + c0 + j;   // unconditional: all in flight
+        if constexpr (W == 1) t[kk][0] = *src;
+        else t[kk] = *(const vec_t*)src;
+      }
+#pragma unroll
+      for (int kk = 0; kk < kKK; ++kk)
+#pragma unroll
+        for (int e = 0; e < W; ++e) v[e] += (k + kk < n_slices) ? t[kk][e] : 0.f;   // slices summed in order
+    }
+#pragma unroll
+    for (int e = 0; e < W; ++e) {
+      if (j < n_norm) ss += v[e] * v[e];
+      row[j + e] = v[e] * gn[e];
+    }
+  }
+  ss = block_sum(ss, red);                    // (its barrier completes row and cs_sh as well)
+  const float r = (kv ? alpha_kv : alpha_q) * rsqrtf(ss / n_norm + eps);
+  if (!kv) {
+    for (int j = tid; j < d_cq; j += kFinishThreads) store_f32(c_q, (size_t)s * d_cq + j, row[j] * r);
+    return;
+  }
   if (pos < 0) return;                        // no cache row for this sequence (as in mlra_append_kv)
-  const int page = page_table[(size_t)s * max_pages + pos / page_size], slot = pos % page_size;
+  const int slot = pos % page_size;
   const int d_cb = d_c / n_blocks;
-  for (int j = tid; j < d_c; j += 256) {
+  for (int j = tid; j < d_c; j += kFinishThreads) {
     const int b = j / d_cb, c = j % d_cb;
-    const float v = row[d_cq + j] * rkv * (gain_kv ? load_f32(gain_kv, j) : 1.f);
-    store_f32(latent, (((size_t)page * n_blocks + b) * page_size + slot) * d_cb + c, v);
+    store_f32(latent, (((size_t)page * n_blocks + b) * page_size + slot) * d_cb + c, row[j] * r);
   }
-  __syncthreads();   // cs_sh is complete
-  for (int l = tid; l < d_r / 2; l += 256) {
+  for (int l = tid; l < d_r / 2; l += kFinishThreads) {
     const float c = cs_sh[2 * l], sn = cs_sh[2 * l + 1];
     float y0, y1;
-    rotate(row[d_cq + d_c + 2 * l], row[d_cq + d_c + 2 * l + 1], c, sn, y0, y1);
+    rotate(row[d_c + 2 * l], row[d_c + 2 * l + 1], c, sn, y0, y1);
     store_f32(rope_pool, ((size_t)page * page_size + slot) * d_r + 2 * l, y0);
     store_f32(rope_pool, ((size_t)page * page_size + slot) * d_r + 2 * l + 1, y1);
   }
@@ -486,17 +493,24 @@ int launch_pre_attention(const mlra_cache* c, const mlra_pre_weights* w, int bat
   int st = launch_gemm(w->dtype, hidden, w->d, batch, s1, w->d, p.slices1, p.rows1, part1, p.n1, stream);
   if (st != MLRA_OK) return st;
 
-  const size_t lds = (size_t)p.n1 * sizeof(float);
-#define MLRA_PRE_DOWN(T, TC)                                                                                       \
-  pre_finish_down_kernel<T, TC><<<batch, 256, lds, stream>>>(                                                      \
+  const size_t lds = (size_t)std::max(w->d_cq, d_c + c->d_r) * sizeof(float);
+  const bool quads = w->d_cq % 4 == 0 && d_c % 4 == 0 && c->d_r % 4 == 0;
+#define MLRA_PRE_DOWN_W(T, TC, W)                                                                                  \
+  pre_finish_down_kernel<T, TC, W><<<dim3(batch, 2), kFinishThreads, lds, stream>>>(                               \
       part1, p.slices1, batch, w->d_cq, d_c, c->d_r, c->n_blocks, (const T*)w->gain_q, (const T*)w->gain_kv,        \
       w->alpha_q, w->alpha_kv, w->eps, w->rope_base, positions, c->page_table, c->max_pages_per_seq, c->page_size, \
       (T*)c_q, (TC*)c->latent, (TC*)c->rope, cs_tab)
+#define MLRA_PRE_DOWN(T, TC)                    \
+  do {                                          \
+    if (quads) MLRA_PRE_DOWN_W(T, TC, 4);       \
+    else MLRA_PRE_DOWN_W(T, TC, 1);             \
+  } while (0)
   if (w->dtype == MLRA_BF16 && c->dtype == MLRA_BF16) MLRA_PRE_DOWN(bf16_t, bf16_t);
   else if (w->dtype == MLRA_BF16) MLRA_PRE_DOWN(bf16_t, float);
   else if (c->dtype == MLRA_BF16) MLRA_PRE_DOWN(float, bf16_t);
   else MLRA_PRE_DOWN(float, float);
 #undef MLRA_PRE_DOWN
+#undef MLRA_PRE_DOWN_W
   if ((st = check_launch()) != MLRA_OK) return st;
 
   GemmSegments s2;

@@ -118,3 +118,13 @@ def test_pre_attention_bf16_paper_shape_unit_gains():
     wl = gen.WORKLOADS["C3"].scaled(name="pre-paper-shape", batch=8, n_min=1, n_max=131072)
     lens = np.array([131072, 1, 70000, 8192, 4097, 64, 65, 100000], dtype=np.int32)
     _run_and_check(wl, d=7168, d_cq=1536, lens=lens, unit_gains=True)
+
+
+# the finishing kernel of the down-projection: columns one at a time (a segment that is no multiple of four) and four at a
+# time, below, at and beyond one round of its 512 threads, one K slice up to more than sixteen, the most RoPE channels
+@pytest.mark.parametrize("key,d,d_cq,nb,d_cb,d_r", [("C1", 40, 510, 1, 34, 6), ("C1", 24, 1030, 3, 171, 2),
+                                                    ("C1", 20, 2048, 2, 512, 256), ("C3", 4096, 128, 1, 64, 64),
+                                                    ("C3", 256, 2056, 4, 136, 8)])
+def test_pre_attention_finish_columns(key, d, d_cq, nb, d_cb, d_r):
+    wl = gen.WORKLOADS[key].scaled(name="pre-finish", batch=3, h=4, n_blocks=nb, d_cb=d_cb, d_r=d_r, n_min=1, n_max=500)
+    _run_and_check(wl, d=d, d_cq=d_cq, lens=np.array([500, 0, 65], dtype=np.int32))
