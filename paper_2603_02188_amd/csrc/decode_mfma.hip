@@ -31,6 +31,7 @@
 // them (a + b and b + a are the same float, so both hold identical scores and take identical softmax
 // decisions), and each then accumulates Z for its own 128 channels.  Three stages of 40 KiB plus a
 // 32 KiB exchange buffer; two workgroup barriers per tile.
+#include "chunk_fit.h"
 #include "mfma_tile.h"
 
 #include <type_traits>
@@ -217,6 +218,10 @@ __device__ __forceinline__ f32x4 acc_read4() {
   return f32x4{acc_read<base>(), acc_read<base + 1>(), acc_read<base + 2>(), acc_read<base + 3>()};
 }
 
+// What a workgroup costs beside its tiles (start-up, write-out), in tiles of about 1.1 us: sections of its life in the
+// 16-tile launch of 16 sequences of 16K tokens.
+constexpr int kFitOverhead = 10;
+
 template <int STAGES, int MODE>   // MODE 0: plain, 1: PAIRED, 2: GLA (see the head of the file)
 __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
@@ -234,7 +239,18 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   // on one XCD at about the same time and all but the first read of a shared row hit in that L2.
   const int n_hg = (p.h + kHeadsPerWG - 1) / kHeadsPerWG;
   const int fam = (GLA ? p.n_blocks : p.n_blocks / kBlocksWG) * n_hg;
-  const int n_units = p.n_splits * p.batch;
+  int n_units = p.n_splits * p.batch, fit_chunk = 0, fit_len = 0, fit_units = 0;
+  if (p.fit_min > 0) {
+    const int n_seqs = p.batch / p.fit_group, i = threadIdx.x & 63;
+    fit_len = i < n_seqs ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
+    fit_chunk = p.n_splits == 1 ? p.fit_min * kTile   // (only the order is wanted)
+                                : chunk_fit::fit_length(fit_len, n_seqs, fam * p.fit_group, p.cus, p.fit_min, kFitOverhead);
+    if (blockIdx.x == 0)
+      for (int e = threadIdx.x; e < p.batch; e += 256) p.chunk_out[e] = fit_chunk;
+    fit_units = chunk_fit::count(fit_len, fit_chunk);
+    n_units = ((fit_units + 7) & ~7) * p.fit_group;
+    if ((int)blockIdx.x >= n_units * fam) return;
+  }
   const int full_units = n_units & ~7;
   int wg = blockIdx.x, su, member;
   if (wg < full_units * fam) {
@@ -246,16 +262,28 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
     su = full_units + wg / fam;
     member = wg % fam;
   }
-  int split, seq, chunk_len;
-  if (p.unit_tab) {            // chunk lengths follow the sequence lengths: active units listed first
+  int split, seq, chunk_len, tab_row, behind = 0;   // tab_row: row of seq_lens and of the page table; behind: later queries
+  if (p.fit_min > 0) {
+    // The queries of one (sequence, chunk) take slots 8 apart: same XCD, side by side in time (see seq_order_kernel).  Runs
+    // of eight chunks go over the XCDs forwards and backwards in turn, so that the XCDs' loads stay alike.
+    const int run = su / (8 * p.fit_group), rem = su % (8 * p.fit_group), query = rem >> 3;
+    const int unit = 8 * run + (run & 1 ? 7 - (rem & 7) : rem & 7);
+    if (unit >= fit_units) return;
+    const chunk_fit::Chunk c = chunk_fit::find(fit_len, p.batch / p.fit_group, fit_chunk, unit);
+    seq = c.seq * p.fit_group + query;
+    tab_row = c.seq;
+    behind = p.fit_group - 1 - query;
+    split = c.split;
+    chunk_len = fit_chunk;
+  } else if (p.unit_tab) {     // chunk lengths follow the sequence lengths: active units listed first
     const int code = p.unit_tab[su];
     if (code < 0) return;
-    seq = code >> 10;
+    seq = tab_row = code >> 10;
     split = code & 1023;
     chunk_len = p.chunk_tab[seq];
   } else {
     split = su % p.n_splits;
-    seq = p.seq_order ? p.seq_order[su / p.n_splits] : su / p.n_splits;
+    seq = tab_row = p.seq_order ? p.seq_order[su / p.n_splits] : su / p.n_splits;
     chunk_len = p.chunk;
   }
   const int hgrp = member % n_hg;
@@ -307,13 +335,13 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   // page id of the first tile, fetched before the sequence length is known (the index is in range for
   // any length)
   typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
-  const const_i32_ptr pt_row = (const_i32_ptr)(p.page_table + (size_t)seq * p.max_pages);
+  const const_i32_ptr pt_row = (const_i32_ptr)(p.page_table + (size_t)tab_row * p.max_pages);
   // (pages hold a multiple of 16 tokens and chunks start on multiples of 64, so the 16 rows that a wave
   // loads of each tile lie in one page: the page ids below are this wave's; with pages of 16 or 32 tokens
   // the four waves of a tile read different pages)
   int issue_page_idx = (t0 + 16 * (int)wave_u) / p.page_size;
   int issue_page = pt_row[min(issue_page_idx, p.max_pages - 1)];
-  const int n = ((const_i32_ptr)p.seq_lens)[seq];
+  const int n = ((const_i32_ptr)p.seq_lens)[tab_row] - behind;
   if (t0 >= n) {
     wait_vmcnt<0>();   // the query loads target this workgroup's LDS: let them land before it is released
     return;
@@ -1066,10 +1094,16 @@ int launch_seq_order(const DecodeArgs& a) {
   return check_launch();
 }
 
+// The shortest chunk that the workspace has slots for, in tiles.
+static int fit_min_tiles(const DecodeArgs& a) {
+  const int tiles = (a.max_pages * a.page_size + kTile - 1) / kTile;
+  return (tiles + a.plan.n_splits - 1) / a.plan.n_splits;
+}
+
 // (several query tokens per sequence: the order is what brings a sequence's queries together, so it is
 // wanted even when one round of workgroups covers the launch)
 static bool want_seq_order(const DecodeArgs& a, long long n_wg) {
-  return !a.balanced && (n_wg > device_cu_count() || a.q_group > 1);
+  return !a.balanced && !a.fitted && (n_wg > device_cu_count() || a.q_group > 1);
 }
 
 // Pages of 16 or 32 tokens (a wave's 16 rows of a tile never straddle a page), or whole tiles.
@@ -1171,12 +1205,20 @@ int launch_decode_mfma(const DecodeArgs& a) {
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
   p.rows_bf16 = a.rows_bf16 ? 1 : 0;
   const int n_hg = paired ? (a.h + 63) / 64 : (a.h + kHeadsWG - 1) / kHeadsWG;
-  const long long n_wg = (long long)a.plan.n_splits * (paired ? a.n_blocks / 2 : a.n_blocks) * n_hg * a.batch;
+  const long long slots = (long long)a.plan.n_splits * a.batch, eights = 8 * a.q_group;
+  // (a fitted launch hands its chunks out in runs of eight)
+  const long long n_wg = (a.fitted ? (slots + eights - 1) / eights * eights : slots) * (paired ? a.n_blocks / 2 : a.n_blocks) * n_hg;
   if (n_wg <= 0 || n_wg > 0x7fffffffLL) return MLRA_ERR_SHAPE;
   // more than one round of workgroups (one per CU at a time): longest sequences first
   p.seq_order = nullptr;
   p.chunk_tab = a.balanced ? a.chunk_tab : nullptr;
   p.unit_tab = a.balanced ? a.unit_tab : nullptr;
+  if (a.fitted) {
+    p.fit_min = fit_min_tiles(a);
+    p.fit_group = a.q_group;
+    p.cus = device_cu_count();
+    p.chunk_out = a.chunk_tab;
+  }
   if (want_seq_order(a, n_wg) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
   if (paired)
     MLRA_LAUNCH_TIMED(a.t_main, (decode_mfma_kernel<kStagesPaired, 1>), dim3((unsigned)n_wg), dim3(256), lds, a.stream, p);

@@ -19,7 +19,8 @@
 // Bound by the matrix pipe: a tile of 64 tokens x 192 channels x 64 heads is 10240 cycles of MFMA per SIMD against
 // 2500 of LDS reads and 48 KiB of loads.  fp32, 4 blocks x 128 channels, 128 heads: 100 TFLOP/s on 8 sequences of 8192
 // tokens (of 157 nominal), 58 us on 8 of 300 to 2048 (the VALU kernel it replaces: 1710 us), of which about 12 us are
-// start-up, write-out and the launch.
+// start-up, write-out and the launch; with chunks fitted to the lengths (chunk_fit.h) 47 us.
+#include "chunk_fit.h"
 #include "f32_tile.h"
 
 namespace mlra {
@@ -36,7 +37,8 @@ struct F32Params {
   const void* q_rope;
   float* part_z;
   float* part_ml;
-  int page_size, max_pages, n_blocks, groups, d_cb, d_r, h, n_splits, chunk, n_hg, batch;
+  int32_t* chunk_tab;   // non-null: the chunk length is fitted to the lengths (chunk_fit.h) and left here for the merge
+  int page_size, max_pages, n_blocks, groups, d_cb, d_r, h, n_splits, chunk, n_hg, batch, cus;
   float scale_log2;
 };
 
@@ -68,9 +70,17 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   // one (chunk, sequence, block) read the same rows and get ids 8 apart (one XCD, one L2), and the chunk is the
   // slowest index, so that the chunk slots that a ragged batch leaves empty are spread over the XCDs evenly.
   // (A grid that one dimension does not hold is cut into rows of a multiple of eight; the last one is padded.)
-  const int units = p.n_splits * p.batch * p.n_blocks, full = units & ~7;
-  int wg = blockIdx.y * gridDim.x + blockIdx.x, u, hg;
+  int wg = blockIdx.y * gridDim.x + blockIdx.x, units = p.n_splits * p.batch * p.n_blocks, chunk = p.chunk, len = 0;
+  if (p.chunk_tab) {
+    const int lane = threadIdx.x & 63;
+    len = lane < p.batch ? max(0, min(p.seq_lens[lane], p.max_pages * p.page_size)) : 0;
+    chunk = chunk_fit::fit_length(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.chunk / chunk_fit::kTokens, 1);
+    if (wg == 0 && (int)threadIdx.x < p.batch) p.chunk_tab[threadIdx.x] = chunk;
+    units = chunk_fit::count(len, chunk) * p.n_blocks;
+  }
   if (wg >= units * p.n_hg) return;
+  const int full = units & ~7;
+  int u, hg;
   if (wg < full * p.n_hg) {
     const int r = wg >> 3;
     hg = r % p.n_hg;
@@ -80,11 +90,17 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
     u = full + wg / p.n_hg;
     hg = wg % p.n_hg;
   }
-  const int b = u % p.n_blocks, s = u / p.n_blocks % p.batch, split = u / p.n_blocks / p.batch;
+  const int b = u % p.n_blocks;
+  int s = u / p.n_blocks % p.batch, split = u / p.n_blocks / p.batch;
+  if (p.chunk_tab) {
+    const chunk_fit::Chunk c = chunk_fit::find(len, p.batch, chunk, u / p.n_blocks);
+    s = c.seq;
+    split = c.split;
+  }
   const int n = p.seq_lens[s];
-  const int t0 = split * p.chunk;
+  const int t0 = split * chunk;
   if (t0 >= n) return;
-  const int t1 = min(n, t0 + p.chunk);
+  const int t1 = min(n, t0 + chunk);
   const int ntiles = (t1 - t0 + TT - 1) / TT;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, r16 = lane & 15;
@@ -353,6 +369,31 @@ int launch_typed(const DecodeArgs& a, F32Params& p, int ht) {
 // Queries and accumulators live in registers: (d_cb + d_r) / 4 + d_cb / 4 of them per lane, beside the tile in flight.
 bool decode_f32_supported(const DecodeArgs& a) { return a.d_cb <= 256 && a.d_cb + a.d_r <= 320; }
 
+// Head tiles of 16 per workgroup: 64 heads where that gives every CU a workgroup (a tile is then staged for four head
+// tiles at once: 59 against 61 us with 32 and 77 with 16 on 8 sequences of 300 to 2048), fewer where it would leave CUs
+// idle (8 sequences of 256 tokens: 15 us with 32 heads, 22 with 64).
+static int head_tiles(const DecodeArgs& a) {
+  const int n_ht = (a.h + 15) / 16;
+  const long units = (long)a.plan.n_splits * a.n_blocks * a.batch;
+  int ht = n_ht >= 4 ? 4 : n_ht >= 2 ? 2 : 1;
+  while (ht > 1 && units * ((n_ht + ht - 1) / ht) < device_cu_count()) ht >>= 1;
+  return ht;
+}
+
+// Fitted chunk lengths (at most 64 sequences, whose lengths the kernel then knows) pay where the slots are more than a round
+// of workgroups, so that a longer chunk can bring a ragged batch down to one, and a chunk is long against the fit itself,
+// which takes 1 us for a few sequences and 4 for 60.  Whole steps, fp32, 128 heads, 4 x 128 channels: 8 sequences of 300 to
+// 2048 90.8 -> 78.0 us, 16 of 100 to 560 77.7 -> 66.1; with one round of slots 4 of 500 to 1000 48.7 -> 50.0, with chunks
+// of 9000 cycles (12 heads, 64 channels) 60 of 200 to 900 38.8 -> 43.0.
+bool decode_f32_fits_chunks(const DecodeArgs& a) {
+  if (a.batch < 2 || a.batch > chunk_fit::kMaxSeqs || a.plan.n_splits < 2 || a.q_group > 1) return false;
+  const int ht = head_tiles(a), D = a.d_cb + a.d_r;
+  const long wgs = (long)a.plan.n_splits * a.n_blocks * a.batch * ((a.h + 16 * ht - 1) / (16 * ht));
+  const int k16 = D <= 32 ? 2 : a.d_cb <= 64 && D <= 96 ? 6 : a.d_cb <= 128 && D <= 192 ? 12 : 20, v64 = (a.d_cb + 63) / 64;
+  const long cycles = 32L * ht * (4 * k16 + 16 * v64) * (a.plan.chunk_tokens / chunk_fit::kTokens);   // matrix pipe, per chunk
+  return wgs > device_cu_count() && cycles >= 12000;
+}
+
 int launch_decode_f32(const DecodeArgs& a) {
   F32Params p;
   p.latent = a.latent;
@@ -374,16 +415,12 @@ int launch_decode_f32(const DecodeArgs& a) {
   p.n_splits = a.plan.n_splits;
   p.chunk = a.plan.chunk_tokens;
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
+  p.chunk_tab = a.fitted ? a.chunk_tab : nullptr;
+  p.cus = device_cu_count();
   // four-element loads: every row and every head's query starts on a multiple of four elements, and so do the bases
   const uintptr_t bases = (uintptr_t)a.latent | (uintptr_t)a.rope | (uintptr_t)a.q_abs | (uintptr_t)a.q_rope;
   const bool vec = a.d_cb % 4 == 0 && a.d_r % 4 == 0 && bases % (a.dtype == MLRA_BF16 ? 8 : 16) == 0;
-  // Heads per workgroup: 64 where that gives every CU a workgroup (a tile is then staged for four head tiles at once:
-  // 59 against 61 us with 32 and 77 with 16 on the shape above), fewer where it would leave CUs idle (8 sequences of
-  // 256 tokens: 15 us with 32 heads, 22 with 64).
-  const int n_ht = (a.h + 15) / 16;
-  const long units = (long)a.plan.n_splits * a.n_blocks * a.batch;
-  int ht = n_ht >= 4 ? 4 : n_ht >= 2 ? 2 : 1;
-  while (ht > 1 && units * ((n_ht + ht - 1) / ht) < device_cu_count()) ht >>= 1;
+  const int ht = head_tiles(a);
   if (a.dtype == MLRA_BF16) return vec ? launch_typed<bf16_t, true>(a, p, ht) : launch_typed<bf16_t, false>(a, p, ht);
   return vec ? launch_typed<float, true>(a, p, ht) : launch_typed<float, false>(a, p, ht);
 }

@@ -144,7 +144,8 @@ template <typename T, typename TO, bool VEC, int SLAB>
 __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
     const float* __restrict__ part_z, const float* __restrict__ part_ml, const int32_t* __restrict__ seq_lens,
     const T* __restrict__ w_uv, TO* __restrict__ out, float* __restrict__ lse, int batch, int h, int d_h, int n_blocks,
-    int d_cb, int n_splits, int chunk, float out_scale, int groups, const T* __restrict__ gate) {
+    int d_cb, int n_splits, int chunk, const int32_t* __restrict__ fitted_chunk, float out_scale, int groups,
+    const T* __restrict__ gate) {
   typedef typename RawOf<T>::type Raw;
   constexpr int kZPitch = SLAB + 4, kPieces = SLAB / 64, kZRows = 16 * kZPitch, kExchange = 4 * 16 * 68;
   static_assert(16 * SLAB / 4 <= kPieces * 256, "every piece of a slab needs a thread");
@@ -164,6 +165,7 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
   const int slab = min(SLAB, kSlabBlocks * d_cb);
   const T* const wcol = w_uv + (size_t)b0 * d_cb * ldw + (size_t)head * d_h;
   f32x4 acc[4] = {opaque_zero4(), opaque_zero4(), opaque_zero4(), opaque_zero4()};
+  if (fitted_chunk) chunk = *fitted_chunk;   // (the decode kernel's own choice)
   if (tid < 16) {
     const int n = tid < n_seq ? seq_lens[m0 + tid] : 0;
     act[tid] = min(n_splits, (n + chunk - 1) / chunk);
@@ -468,7 +470,7 @@ int launch_merge_upproj_f32(const DecodeArgs& a) {
 #define MLRA_MERGE_SLAB(T, TO, VEC, SLAB)                                                                           \
   merge_upproj_f32_kernel<T, TO, VEC, SLAB><<<grid, 256, 0, a.stream>>>(                                            \
       a.part_z, a.part_ml, a.seq_lens, (const T*)a.w_uv, (TO*)a.out, a.lse, a.batch, a.h, a.d_h, a.n_blocks, a.d_cb, \
-      a.plan.n_splits, a.plan.chunk_tokens, a.out_scale, a.groups, (const T*)a.gate)
+      a.plan.n_splits, a.plan.chunk_tokens, a.fitted ? a.chunk_tab : nullptr, a.out_scale, a.groups, (const T*)a.gate)
 #define MLRA_MERGE_OUT(T, VEC)                                  \
   do {                                                          \
     if (a.out_dtype == MLRA_BF16) MLRA_MERGE(T, bf16_t, VEC);   \

@@ -132,10 +132,13 @@ static size_t decode_ws_bytes(int batch, int h, int n_blocks, int d_cb, const Sp
 }
 
 // h: heads served by one block (all heads when groups == 1, the heads of one group otherwise)
+// q_group > 1: the batch is batch / q_group sequences with q_group query tokens each; the rooms take a row of the lengths
+// and of the page table per query, for the kernels that want them
 static int decode_common(const mlra_cache* c, int batch, int h, int groups, int d_h, const void* q_abs,
                          const void* q_rope, const void* w_uv, float softmax_scale, float out_scale, void* out,
                          int out_dtype, float* lse, void* workspace, size_t workspace_bytes, void* stream,
-                         const void* gate = nullptr, int q_group = 1) {
+                         const void* gate = nullptr, int q_group = 1, int32_t* lens_room = nullptr,
+                         int32_t* table_room = nullptr) {
   if (!c || !q_abs || !q_rope || !w_uv || !out) return MLRA_ERR_NULL;
   if (!c->latent || !c->rope || !c->page_table || !c->seq_lens) return MLRA_ERR_NULL;
   if (!valid_dtype(c->dtype) || !valid_dtype(out_dtype)) return MLRA_ERR_DTYPE;
@@ -158,6 +161,7 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   a.chunk_tab = (int32_t*)((char*)a.seq_order + align_up((size_t)batch * sizeof(int32_t), 256));
   a.unit_tab = (int32_t*)((char*)a.chunk_tab + align_up((size_t)batch * sizeof(int32_t), 256));
   a.balanced = false;
+  a.fitted = false;
   a.rows_bf16 = false;
   a.q_group = q_group;
   a.latent = c->latent;
@@ -186,9 +190,24 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   a.stream = (hipStream_t)stream;
   a.t_main = timing_pair(0);
   a.t_epi = timing_pair(1);
-  // chunk lengths that follow the sequence lengths need both MFMA kernels (they read the table)
-  if (a.plan.target_chunks > 0 && merge_upproj_mfma_supported(a) &&
-      (decode_mfma_supported(a) || decode_gla_supported(a) || mla_mfma_supported(a)))
+  // Up to 64 sequences: the decode kernel finds its chunk from the lengths itself (chunk_fit.h), which saves the kernels in
+  // front that would plan or order the chunks.  The MLRA kernel does so with long chunks and with several query tokens per
+  // sequence, else its uniform chunks are as good and their workgroups start a round trip earlier; the fp32 kernel by its own
+  // rule.
+  // Other batches with a target: a kernel in front plans the chunks (both MFMA kernels read its table).
+  const bool mfma = decode_mfma_supported(a), merge_mfma = merge_upproj_mfma_supported(a);
+  const int n_seqs = batch / q_group;
+  if (mfma && merge_mfma && n_seqs <= 64) a.fitted = q_group > 1 || (a.plan.target_chunks > 0 && !a.plan.single_if_uniform);
+  const bool runs_f32 = !mfma && !decode_gla_supported(a) && !mla_mfma_supported(a) && decode_f32_supported(a);
+  if (runs_f32) a.fitted = decode_f32_fits_chunks(a);
+  if (q_group > 1 && !a.fitted) {
+    const int st = launch_expand_queries(c->seq_lens, c->page_table, n_seqs, q_group, c->max_pages_per_seq, lens_room,
+                                         table_room, a.stream);
+    if (st != MLRA_OK) return st;
+    a.seq_lens = lens_room;
+    a.page_table = table_room;
+  }
+  if (!a.fitted && a.plan.target_chunks > 0 && merge_mfma && (mfma || decode_gla_supported(a) || mla_mfma_supported(a)))
     a.balanced = launch_plan_chunks(a) == MLRA_OK;
   // the MLRA MFMA kernels hand the epilogue normalised bf16 rows (one per chunk) instead of fp32 partials
   a.rows_bf16 = merge_upproj_mfma_supported(a) && (decode_mfma_supported(a) || decode_gla_supported(a));
@@ -344,15 +363,9 @@ int mlra_decode_attn_multi(const mlra_cache* c, int32_t batch, int32_t q_len, in
   if (h <= 0 || d_h <= 0 || c->n_blocks <= 0 || c->d_cb <= 0 || c->d_r <= 0 || c->num_pages <= 0) return MLRA_ERR_SHAPE;
   int32_t* lens2 = (int32_t*)workspace;
   int32_t* table2 = (int32_t*)((char*)workspace + lens_bytes);
-  int st = launch_expand_queries(c->seq_lens, c->page_table, batch, q_len, c->max_pages_per_seq, lens2, table2,
-                                 (hipStream_t)stream);
-  if (st != MLRA_OK) return st;
-  mlra_cache c2 = *c;
-  c2.page_table = table2;
-  c2.seq_lens = lens2;
-  return decode_common(&c2, units, h, 1, d_h, q_abs, q_rope, w_uv, softmax_scale, out_scale, out, out_dtype, lse,
+  return decode_common(c, units, h, 1, d_h, q_abs, q_rope, w_uv, softmax_scale, out_scale, out, out_dtype, lse,
                        (char*)workspace + lens_bytes + table_bytes, workspace_bytes - lens_bytes - table_bytes,
-                       stream, nullptr, q_len);
+                       stream, nullptr, q_len, lens2, table2);
 }
 
 int mlra_decode_attn_gated(const mlra_cache* cache, int32_t batch, int32_t h, int32_t d_h, const void* q_abs,

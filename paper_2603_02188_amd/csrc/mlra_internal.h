@@ -96,11 +96,13 @@ struct DecodeArgs {
   const void* gate;    // optional [batch][groups * h][d_h] of the cache dtype: out is multiplied by it elementwise
   float* part_z;   // [batch][n_blocks][n_splits][h][d_cb]
   float* part_ml;  // [batch][n_blocks][n_splits][h][2]  (running max, running sum)
-  int q_group;         // > 1: entries [i q_group, (i + 1) q_group) of the batch are the query tokens of one sequence
+  int q_group;         // > 1: entries [i q_group, (i + 1) q_group) of the batch are the query tokens of one sequence (seq_lens
+                       // and page_table have one row per entry, or, with `fitted`, one per sequence)
   int32_t* seq_order;  // [batch] sequence ids, longest first (workspace); filled by the MFMA launcher when used
   int32_t* chunk_tab;  // [batch] per-sequence chunk length (workspace); filled by launch_plan_chunks when used
   int32_t* unit_tab;   // [batch * n_splits] active (sequence, chunk) pairs, then -1 (workspace); same
   bool balanced;       // chunk lengths follow the sequence lengths (chunk_tab) instead of plan.chunk_tokens
+  bool fitted;         // the decode kernel fits one chunk length to the lengths and leaves it in chunk_tab
   bool rows_bf16;      // the decode kernel writes each chunk's partial as a normalised bf16 row z / l (the MLRA
                        // MFMA kernels); otherwise fp32 partials Z (the MLA and the fp32 kernels)
   SplitPlan plan;
@@ -125,6 +127,7 @@ int launch_absorb_q_f32(int batch, int h, int d_h, int n_blocks, int groups, int
                             const void* q_rope = nullptr, void* q_rope_out = nullptr, int d_r = 0);
 int launch_decode_generic(const DecodeArgs& a);
 bool decode_f32_supported(const DecodeArgs& a);   // fp32 matrix instructions, any dtype and dims up to its registers
+bool decode_f32_fits_chunks(const DecodeArgs& a);   // for `fitted`
 int launch_decode_f32(const DecodeArgs& a);
 // seq_lens_out[s * q_len + j] = max(0, seq_lens[s] - (q_len - 1 - j)); page_table_out row s * q_len + j = row s
 int launch_expand_queries(const int32_t* seq_lens, const int32_t* page_table, int batch, int q_len, int max_pages,

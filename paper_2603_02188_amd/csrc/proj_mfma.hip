@@ -192,7 +192,7 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
     const float* __restrict__ part_z, const float* __restrict__ part_ml, const int32_t* __restrict__ seq_lens,
     const bf16_t* __restrict__ w_uv, TO* __restrict__ out, float* __restrict__ lse, int batch, int h, int nb_total,
     int d_cb, int n_splits, int chunk, const int32_t* __restrict__ chunk_tab, float out_scale,
-    const bf16_t* __restrict__ gate, int spw) {
+    const bf16_t* __restrict__ gate, int spw, int q_group, unsigned q_magic) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   // blockIdx.z = head group (Eq. (6)); one group of all blocks is Eq. (5).  h: heads per block; this
   // workgroup's head is h * group + head in out, and its branches are blocks [b0, b0 + n_blocks).
@@ -223,9 +223,16 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
   fetch_w(1, wreg[1]);
 
   // ---- phase 1
+  // q_group > 1: entries [i q_group, (i + 1) q_group) of the batch are the queries of one sequence, which share a length
+  // (q_magic = 2^32 / q_group rounded up: an exact quotient for 16-bit numbers)
+  auto len_of = [&](int seq) {
+    if (q_group == 1) return seq_lens[seq];
+    const int own = (int)__umulhi((unsigned)seq, q_magic);
+    return max(0, seq_lens[own] - (q_group - 1 - (seq - own * q_group)));
+  };
   auto active_chunks = [&](int seq) {
     const int ch = chunk_tab ? chunk_tab[seq] : chunk;
-    return min(n_splits, (seq_lens[seq] + ch - 1) / ch);
+    return min(n_splits, (len_of(seq) + ch - 1) / ch);
   };
   bf16x8 zero8;
 #pragma unroll
@@ -242,7 +249,7 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
       for (int u = 0; u < U; ++u) {
         const int item = min(base + u * 256, n_items - 1), sl = item / items_per_row, r0 = (item % items_per_row) * 8;
         row[u] = *(const bf16x8*)(zn + (((size_t)(m0 + sl) * nb_total + b0 + r0 / d_cb) * h + head) * d_cb + r0 % d_cb);
-        n[u] = seq_lens[m0 + sl];
+        n[u] = len_of(m0 + sl);
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) {
@@ -257,7 +264,7 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
         const int seq = m0 + t / n_blocks, b = b0 + t % n_blocks;
         const float2 ml = *(const float2*)(part_ml + (((size_t)seq * nb_total + b) * h + head) * 2);
         lse[((size_t)seq * nb_total + b) * h + head] =
-            seq_lens[seq] > 0 && ml.y > 0.f ? (ml.x + log2f(ml.y)) * kLn2 : -INFINITY;
+            len_of(seq) > 0 && ml.y > 0.f ? (ml.x + log2f(ml.y)) * kLn2 : -INFINITY;
       }
   } else {
     const size_t z_stride = (size_t)h * d_cb;
@@ -510,12 +517,13 @@ static int launch_merge_as(const DecodeArgs& a, dim3 grid, int spw) {
       return MLRA_ERR_LAUNCH;
     setup.done(setup_dev);
   }
-  const int32_t* const chunk_tab = a.balanced ? a.chunk_tab : nullptr;
+  const int q_group = a.fitted ? a.q_group : 1;
+  const int32_t* const chunk_tab = a.balanced || a.fitted ? a.chunk_tab : nullptr;
   MLRA_LAUNCH_TIMED(a.t_epi, (merge_upproj_mfma_kernel<TO, MODE, U, KK>), grid, dim3(256),
                     merge_upproj_lds_bytes(a, MODE == kDirect), a.stream, (const float*)a.part_z,
                     (const float*)a.part_ml, a.seq_lens, (const bf16_t*)a.w_uv, (TO*)a.out, a.lse, a.batch, a.h,
                     a.n_blocks, a.d_cb, a.plan.n_splits, a.plan.chunk_tokens, chunk_tab, a.out_scale,
-                    (const bf16_t*)a.gate, spw);
+                    (const bf16_t*)a.gate, spw, q_group, 0xffffffffu / (unsigned)q_group + 1u);
   return check_launch();
 }
 

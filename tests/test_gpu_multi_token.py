@@ -82,3 +82,16 @@ def test_multi_token_q_len_one_is_the_plain_decode():
 def test_multi_token_full_size_every_sequence():
     wl = gen.WORKLOADS["C3"]
     _check(wl, 4, gen.draw_seq_lens(wl), out_dtype=torch.bfloat16)
+
+
+# the queries' dispatch order, found by the decode kernel itself up to 64 sequences: runs of eight full and not, sequences
+# shorter than the queries, none of them, equal lengths; chunks of long contexts; and 65 sequences, which take the expanded tables
+@pytest.mark.parametrize("batch,q_len,n_max", [(1, 3, 700), (8, 2, 130), (9, 4, 70), (17, 3, 200), (64, 2, 66), (65, 2, 66),
+                                               (3, 2, 9000)])
+def test_multi_token_order(batch, q_len, n_max):
+    wl = gen.WORKLOADS["C5"].scaled(name="mt-order", batch=batch, n_min=0, n_max=n_max, index=4300 + batch)
+    lens = np.random.default_rng(batch).integers(0, n_max + 1, size=batch).astype(np.int32)
+    lens[0] = n_max
+    if batch > 4:
+        lens[1:5] = [0, 1, q_len - 1, n_max]
+    _check(wl, q_len, lens)
