@@ -925,24 +925,30 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
     }
   }
 
-  // ---- merge the two token halves of each head half through LDS, write the chunk's partial ----
+  // ---- merge the two token halves of each head half, write the chunk's partial ----
+  // Wave (hw, tw) finishes channel tiles 2 tw and 2 tw + 1 of its heads: it hands the other two, as they are, to its
+  // partner (hw, 1 - tw) through LDS and weighs what it keeps and what it gets when it reads them, so that both waves
+  // have half of the work, one barrier is enough and the rows leave from registers.  One wave of a pair summing in LDS, and
+  // all reading the rows from there again, took about 1.8 us longer per workgroup: whole steps of one request 30.4 -> 28.7 us,
+  // of 16 sequences of 16K tokens on one block 46.9 -> 44.8, MLRA-2 on 64 of 8K 133.5 -> 130.8, 128 of 512 to 8192 216.3 -> 212.7.
   {
   settle_acc();   // the last PV MFMAs have retired before ordinary code reads the accumulators
   // (the lane's indices are derived again from a thread id the compiler cannot connect to the first one:
   // otherwise it keeps a dozen of them alive across the main loop, spilled to scratch memory)
   int tid_again = threadIdx.x;
   asm volatile("" : "+v"(tid_again));
-  const int tid = tid_again, wave = tid >> 6, lane = tid & 63, hw = wave & 1, tw = wave >> 1, g = lane >> 5,
-            c32 = lane & 31;
+  const int tid = tid_again, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, hw = wave & 1, tw = wave >> 1,
+            g = lane >> 5, c32 = lane & 31;
   const int blk = (PAIRED && !GLA) ? blk0 + hw : blk0;
   const int wave_head0 = PAIRED ? hgrp * 64 : hgrp * kHeadsWG + hw * 64;
   float l_run[2];
   l_run[0] = acc_read<128>();   // (already summed over both token halves of the wave)
   l_run[1] = acc_read<132>();
   __builtin_amdgcn_s_barrier();     // every wave is past its last tile read: the stages can be reused
+  asm volatile("" ::: "memory");
   float* mbuf = (float*)smem;                 // [4 waves][64 heads]
   float* lbuf = mbuf + 256;
-  float* zbuf = (float*)(smem + 2048);        // [128 heads][kZPitch]
+  f32x4* const zbuf = (f32x4*)(smem + 2048);  // [4 waves][2 head tiles x 2 channel tiles x 4 quads][64 lanes]
   if (g == 0) {
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {
@@ -950,111 +956,84 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
       lbuf[wave * 64 + nt * 32 + c32] = l_run[nt];
     }
   }
+  // (compile-time loops over head tile, channel tile and register quad: the register names are immediates)
+  auto for_each_pair = [&](auto first_mt, auto&& fn) {       // fn(head tile, channel tile, pair of quads, running number)
+    constexpr int mt = decltype(first_mt)::value;
+    auto pairs = [&](auto nt_tag, auto mt_tag, auto at) {
+      constexpr int k = decltype(at)::value;
+      fn(nt_tag, mt_tag, std::integral_constant<int, 0>{}, std::integral_constant<int, k>{});
+      fn(nt_tag, mt_tag, std::integral_constant<int, 1>{}, std::integral_constant<int, k + 1>{});
+    };
+    pairs(std::integral_constant<int, 0>{}, std::integral_constant<int, mt>{}, std::integral_constant<int, 0>{});
+    pairs(std::integral_constant<int, 0>{}, std::integral_constant<int, mt + 1>{}, std::integral_constant<int, 2>{});
+    pairs(std::integral_constant<int, 1>{}, std::integral_constant<int, mt>{}, std::integral_constant<int, 4>{});
+    pairs(std::integral_constant<int, 1>{}, std::integral_constant<int, mt + 1>{}, std::integral_constant<int, 6>{});
+  };
+  auto give = [&](auto nt_tag, auto mt_tag, auto pair_tag, auto at) {
+    constexpr int nt = decltype(nt_tag)::value, mt = decltype(mt_tag)::value, pr = decltype(pair_tag)::value,
+                  k = decltype(at)::value;
+    zbuf[(wave * 16 + 2 * k) * 64 + lane] = acc_read4<mt, nt, 2 * pr>();
+    zbuf[(wave * 16 + 2 * k + 1) * 64 + lane] = acc_read4<mt, nt, 2 * pr + 1>();
+  };
+  if (tw == 0) for_each_pair(std::integral_constant<int, 2>{}, give);
+  else for_each_pair(std::integral_constant<int, 0>{}, give);
   __syncthreads();
-  float m_out[2], l_out[2], w_mine[2];
+  float m_out[2], l_out[2], w_own[2], w_par[2];
 #pragma unroll
   for (int nt = 0; nt < 2; ++nt) {
     const float mp = mbuf[(wave ^ 2) * 64 + nt * 32 + c32];
     const float lp = lbuf[(wave ^ 2) * 64 + nt * 32 + c32];
     const float ms = fmaxf(m_run[nt], mp);
-    const float w_own = __builtin_amdgcn_exp2f(m_run[nt] - ms);
-    const float w_par = __builtin_amdgcn_exp2f(mp - ms);
+    w_own[nt] = __builtin_amdgcn_exp2f(m_run[nt] - ms);
+    w_par[nt] = __builtin_amdgcn_exp2f(mp - ms);
     m_out[nt] = ms;
-    l_out[nt] = l_run[nt] * w_own + lp * w_par;
-    w_mine[nt] = w_own;
+    l_out[nt] = l_run[nt] * w_own[nt] + lp * w_par[nt];
   }
-  // this wave's Z^T, four registers at a time, weighted for the merge of the two token halves
-  auto z4 = [&](auto nt_tag, auto mt_tag, auto r4_tag) {
-    constexpr int nt = decltype(nt_tag)::value;
-    f32x4 v = acc_read4<decltype(mt_tag)::value, nt, decltype(r4_tag)::value>();
-    const float w = w_mine[nt];
-    return f32x4{v[0] * w, v[1] * w, v[2] * w, v[3] * w};
-  };
-  // (compile-time loops over head tile, channel tile and register quad: the register names are immediates)
-  auto for_each_quad = [&](auto&& fn) {
-    auto quads = [&](auto nt_tag, auto mt_tag) {
-      fn(nt_tag, mt_tag, std::integral_constant<int, 0>{});
-      fn(nt_tag, mt_tag, std::integral_constant<int, 1>{});
-      fn(nt_tag, mt_tag, std::integral_constant<int, 2>{});
-      fn(nt_tag, mt_tag, std::integral_constant<int, 3>{});
-    };
-    auto tiles = [&](auto nt_tag) {
-      quads(nt_tag, std::integral_constant<int, 0>{});
-      quads(nt_tag, std::integral_constant<int, 1>{});
-      quads(nt_tag, std::integral_constant<int, 2>{});
-      quads(nt_tag, std::integral_constant<int, 3>{});
-    };
-    tiles(std::integral_constant<int, 0>{});
-    tiles(std::integral_constant<int, 1>{});
-  };
-  auto zrow = [&](int nt, int mt, int r4) {
-    return zbuf + (hw * 64 + nt * 32 + c32) * kZPitch + mt * 32 + r4 * 8 + g * 4;
-  };
-  if (tw == 1) {
-    for_each_quad([&](auto nt_tag, auto mt_tag, auto r4_tag) {
-      *(f32x4*)zrow(decltype(nt_tag)::value, decltype(mt_tag)::value, decltype(r4_tag)::value) = z4(nt_tag, mt_tag, r4_tag);
-    });
-  }
-  __syncthreads();
-  if (tw == 0) {
-    for_each_quad([&](auto nt_tag, auto mt_tag, auto r4_tag) {
-      f32x4* const row = (f32x4*)zrow(decltype(nt_tag)::value, decltype(mt_tag)::value, decltype(r4_tag)::value);
-      const f32x4 own = z4(nt_tag, mt_tag, r4_tag);
-      f32x4 v = *row;
-      v[0] += own[0];
-      v[1] += own[1];
-      v[2] += own[2];
-      v[3] += own[3];
-      *row = v;
-    });
-    // (bf16 rows: 1 / l of the row's head goes into the padding behind its 128 channels)
-    if (p.rows_bf16 && g == 0) {
-#pragma unroll
-      for (int nt = 0; nt < 2; ++nt)
-        zbuf[(hw * 64 + nt * 32 + c32) * kZPitch + kDcb] = l_out[nt] > 0.f ? 1.f / l_out[nt] : 0.f;
-    }
-  }
-  __syncthreads();
-  // zbuf row hl = hw * 64 + (head inside the wave's 64): plain form, 128 heads of one block; PAIRED, 64
-  // heads of block blk0 then the same 64 heads of block blk0 + 1
-  // (GLA: rows 64..127 are channels 128..255 of the same 64 heads of the one block)
-  constexpr int kZRow = GLA ? 2 * kDcb : kDcb;   // channels of one partial row in the workspace
+  const size_t unit = ((size_t)seq * p.n_blocks + blk) * p.n_splits + split;
+  constexpr int kZRow = GLA ? 2 * kDcb : kDcb;   // channels of one partial row in the workspace (GLA: hw is the channel half)
   if (p.rows_bf16) {
     // The chunk's partial leaves normalised: z * (1 / l) rounded to bf16, with (m, l) beside it in fp32.  A
     // convex combination of cache rows is no larger than they are, so bf16 holds it as well as it holds
     // the cache; with one chunk per sequence the row is already what the up-projection consumes, with
     // several the merge weighs the rows by 2^(m_k - m*) l_k.  Half the bytes of fp32 partials.
-    bf16_t* zn = (bf16_t*)p.part_z;
-    for (int idx = tid; idx < kHeadsWG * (kDcb / 8); idx += 256) {
-      const int hl = idx / (kDcb / 8), f8 = idx % (kDcb / 8);
-      const int row_blk = (PAIRED && !GLA) ? blk0 + (hl >> 6) : blk0;
-      const int row_head = PAIRED ? hgrp * 64 + (hl & 63) : hgrp * kHeadsWG + hl;
-      const size_t row_unit = ((size_t)seq * p.n_blocks + row_blk) * p.n_splits + split;
-      if (row_head < p.h) {
-        const float inv = zbuf[hl * kZPitch + kDcb];
-        const f32x4 lo = *(const f32x4*)(zbuf + hl * kZPitch + f8 * 8), hi = *(const f32x4*)(zbuf + hl * kZPitch + f8 * 8 + 4);
-        bf16x8 packed;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          packed[e] = (__bf16)(inv * lo[e]);
-          packed[4 + e] = (__bf16)(inv * hi[e]);
-        }
-        *(bf16x8*)(zn + (row_unit * p.h + row_head) * kZRow + (GLA ? (hl >> 6) * kDcb : 0) + f8 * 8) = packed;
-      }
-    }
-  } else {
-    // (for the fp32 merge kernel, which takes the shapes that the bf16 epilogue does not: fp32, not normalised)
-    for (int idx = tid; idx < kHeadsWG * (kDcb / 4); idx += 256) {
-      const int hl = idx / (kDcb / 4), f4 = idx % (kDcb / 4);
-      const int row_blk = (PAIRED && !GLA) ? blk0 + (hl >> 6) : blk0;
-      const int row_head = PAIRED ? hgrp * 64 + (hl & 63) : hgrp * kHeadsWG + hl;
-      const size_t row_unit = ((size_t)seq * p.n_blocks + row_blk) * p.n_splits + split;
-      if (row_head < p.h)
-        *(f32x4*)(p.part_z + (row_unit * p.h + row_head) * kZRow + (GLA ? (hl >> 6) * kDcb : 0) + f4 * 4) =
-            *(const f32x4*)(zbuf + hl * kZPitch + f4 * 4);
+    for (int nt = 0; nt < 2; ++nt) {
+      const float inv = l_out[nt] > 0.f ? 1.f / l_out[nt] : 0.f;
+      w_own[nt] *= inv;
+      w_par[nt] *= inv;
     }
   }
-  const size_t unit = ((size_t)seq * p.n_blocks + blk) * p.n_splits + split;
+  auto finish = [&](auto nt_tag, auto mt_tag, auto pair_tag, auto at) {
+    constexpr int nt = decltype(nt_tag)::value, mt = decltype(mt_tag)::value, pr = decltype(pair_tag)::value,
+                  k = decltype(at)::value;
+    f32x4 v[2] = {acc_read4<mt, nt, 2 * pr>(), acc_read4<mt, nt, 2 * pr + 1>()};
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const f32x4 got = zbuf[((wave ^ 2) * 16 + 2 * k + i) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[i][e] = v[i][e] * w_own[nt] + got[e] * w_par[nt];
+    }
+    const int head = wave_head0 + nt * 32 + c32;
+    const size_t row = (unit * p.h + head) * kZRow + (GLA ? hw * kDcb : 0) + mt * 32 + pr * 16;
+    if (p.rows_bf16) {
+      // A lane holds channels 4 g .. + 3 and 8 + 4 g .. + 3 of sixteen; after the swap, 8 g .. + 7.
+      typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+      typedef __attribute__((ext_vector_type(2))) unsigned uint2v;
+      typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
+      uint2v x = __builtin_bit_cast(uint2v, bf16x4{(__bf16)v[0][0], (__bf16)v[0][1], (__bf16)v[0][2], (__bf16)v[0][3]});
+      uint2v y = __builtin_bit_cast(uint2v, bf16x4{(__bf16)v[1][0], (__bf16)v[1][1], (__bf16)v[1][2], (__bf16)v[1][3]});
+      unsigned x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];
+      asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %2\n\tv_permlane32_swap_b32 %1, %3\n\ts_nop 1"
+                   : "+v"(x0), "+v"(x1), "+v"(y0), "+v"(y1));
+      if (head < p.h) *(uint4v*)((bf16_t*)p.part_z + row + 8 * g) = uint4v{x0, x1, y0, y1};
+    } else if (head < p.h) {
+      // (for the fp32 merge kernel, which takes the shapes that the bf16 epilogue does not: fp32, not normalised)
+      *(f32x4*)(p.part_z + row + 4 * g) = v[0];
+      *(f32x4*)(p.part_z + row + 8 + 4 * g) = v[1];
+    }
+  };
+  if (tw == 0) for_each_pair(std::integral_constant<int, 0>{}, finish);
+  else for_each_pair(std::integral_constant<int, 2>{}, finish);
   if (tw == 0 && g == 0 && !(GLA && hw == 1)) {   // (GLA: both channel halves hold the same m and l)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt) {

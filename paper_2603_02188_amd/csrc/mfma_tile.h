@@ -20,7 +20,6 @@ constexpr int kLatBytes = kTile * kDcb * 2;   // 16 KiB
 constexpr int kRopeBytes = kTile * kDr * 2;   //  8 KiB
 constexpr int kStageBytes = kLatBytes + kRopeBytes;
 constexpr int kLoadsPerTile = 6;              // direct-to-LDS loads each thread issues per tile
-constexpr int kZPitch = kDcb + 4;             // floats per head row of the epilogue buffer
 constexpr float kNegBig = -1.0e30f;
 constexpr float kLazy = 8.0f;                 // log2 headroom before the running max is refreshed
 
