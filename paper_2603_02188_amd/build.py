@@ -72,10 +72,10 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         if bad:
             raise RuntimeError(f"{src}: compiler-generated code touches the reserved accumulation registers:\n" +
                                "\n".join(f"  {asm}:{ln}: {text}" for ln, text in bad[:20]))
-        # a spill inside the MLA kernel's tile loop would wait for the tile loads in flight
-        bad = find_scratch_in_loops(text, r"mla_mfma_kernel")
+        # a spill inside an MLA kernel's tile loop would wait for the tile loads in flight
+        bad = find_scratch_in_loops(text, r"mla_(mfma|pipe)_kernel")
         if bad:
-            raise RuntimeError(f"{src}: scratch accesses inside the loop of the MLA kernel:\n" +
+            raise RuntimeError(f"{src}: scratch accesses inside the loop of an MLA kernel:\n" +
                                "\n".join(f"  {asm}:{ln}: {text}" for ln, text in bad[:20]))
         return obj
 

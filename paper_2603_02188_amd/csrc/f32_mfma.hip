@@ -71,7 +71,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   // slowest index, so that the chunk slots that a ragged batch leaves empty are spread over the XCDs evenly.
   // (A grid that one dimension does not hold is cut into rows of a multiple of eight; the last one is padded.)
   int wg = blockIdx.y * gridDim.x + blockIdx.x, units = p.n_splits * p.batch * p.n_blocks, chunk = p.chunk, len = 0;
-  if (p.chunk_tab) {
+  if (__builtin_expect(p.chunk_tab != nullptr, 0)) {
     const int lane = threadIdx.x & 63;
     len = lane < p.batch ? max(0, min(p.seq_lens[lane], p.max_pages * p.page_size)) : 0;
     chunk = chunk_fit::fit_length(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.chunk / chunk_fit::kTokens, 1);
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   }
   const int b = u % p.n_blocks;
   int s = u / p.n_blocks % p.batch, split = u / p.n_blocks / p.batch;
-  if (p.chunk_tab) {
+  if (__builtin_expect(p.chunk_tab != nullptr, 0)) {
     const chunk_fit::Chunk c = chunk_fit::find(len, p.batch, chunk, u / p.n_blocks);
     s = c.seq;
     split = c.split;

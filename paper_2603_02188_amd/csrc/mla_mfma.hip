@@ -2,8 +2,9 @@
 // (Section 2.1, Steps 1-3 with d_c = 512; bf16 caches).
 //
 // One workgroup (4 wavefronts) owns one (sequence, context chunk, 64 query heads) and walks the
-// chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads, two stages deep with two
-// workgroups per CU or four stages deep with one.  The two products split the work differently:
+// chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads.  Most launches run on
+// mla_pipe_kernel, described there; mla_mfma_kernel, two stages deep with two workgroups per CU or four stages deep with
+// one, keeps the shapes named in launch_mla_mfma.  In the latter the two products split the work differently:
 //   * scores and softmax by heads: wave w owns heads [16 w, 16 w + 16) and computes their complete scores
 //     S^T = [C | K^R] [q~ | q^R]^T over all 576 channels with 16x16x32 MFMAs (tokens x heads), so the
 //     softmax of a head is computed once, by one wave, with its running maximum and sum in that wave;
@@ -23,12 +24,13 @@
 // sequences of 4352 (one workgroup per CU) 221 -> 212.  Measured and not kept: 16-token tiles in four stages
 // (198 / 237 / 250 us), two groups of four waves one barrier apart in one workgroup (223 / 260 / 215), 32 heads x 16
 // tokens per wave (216 / 264 / 214), the channels of the scores split over two waves (224 / 265 / 298).
-// With one workgroup per CU and no second head half beside it to share rows with in L2, two stages leave the loads too
-// little time: see the rule in launch_mla_mfma.
 // The two head halves of a sequence are placed on the same XCD (ids 8 apart), so the cache is fetched
 // from HBM once.  Partials go to the workspace in the layout of the MLRA path with n_blocks = 1,
 // d_cb = 512.
+#include "chunk_fit.h"
 #include "mfma_tile.h"
+
+#include <type_traits>
 
 namespace mlra {
 namespace {
@@ -46,6 +48,9 @@ constexpr int kMPBytes = 4 * 1024;                 // P^T: [2 head tiles][2 toke
 constexpr int mla_lds_bytes(int stages) { return stages * kMStage + kMPBytes + kMHeads * 4 + 4 * 4; }
 static_assert(2 * mla_lds_bytes(2) <= 160 * 1024 && mla_lds_bytes(4) <= 160 * 1024, "two workgroups per CU / one");
 constexpr int kMLoads = 9;                         // direct-to-LDS loads per wave and tile
+
+// start-up and write-out of a workgroup in the time of 64 tokens (15 us, 2.3 us)
+constexpr int kMFitOverhead = 6;
 
 typedef const __attribute__((address_space(3))) bf16x8* lds_bf16x8_ptr;
 typedef const __attribute__((address_space(3))) unsigned char* lds_byte_ptr;
@@ -77,16 +82,23 @@ __device__ __forceinline__ float head_sum(float v) {
   return a + b;
 }
 
-template <int STAGES>
-__global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(MfmaParams p) {
-  static_assert(STAGES == 2 || STAGES == 4, "a power of two, and the waits below");
-  constexpr int kMPOff = STAGES * kMStage, kMAOff = kMPOff + kMPBytes, kMFOff = kMAOff + kMHeads * 4;
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+
+// false: an empty slot
+__device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& seq, int& split, int& chunk_len) {
   // workgroup -> (sequence, chunk, head half); the halves of one (sequence, chunk) get ids 8 apart
   const int n_hg = (p.h + kMHeads - 1) / kMHeads;
-  const int n_units = p.n_splits * p.batch;
+  int n_units = p.n_splits * p.batch, fit_len = 0;
+  if (p.fit_min > 0) {         // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
+    const int i = threadIdx.x & 63;
+    fit_len = i < p.batch ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
+    chunk_len = chunk_fit::fit_length(fit_len, p.batch, n_hg, p.cus, p.fit_min, kMFitOverhead);
+    if (blockIdx.x == 0 && (int)threadIdx.x < p.batch) p.chunk_out[threadIdx.x] = chunk_len;
+    n_units = chunk_fit::count(fit_len, chunk_len);
+    if ((int)blockIdx.x >= n_units * n_hg) return false;
+  }
   const int full_units = n_units & ~7;
-  int wg = blockIdx.x, su, hgrp;
+  int wg = blockIdx.x, su;
   if (wg < full_units * n_hg) {
     const int r = wg >> 3;
     hgrp = r % n_hg;
@@ -96,10 +108,13 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(Mfma
     su = full_units + wg / n_hg;
     hgrp = wg % n_hg;
   }
-  int split, seq, chunk_len;
-  if (p.unit_tab) {            // chunk lengths follow the sequence lengths: active units listed first
+  if (p.fit_min > 0) {
+    const chunk_fit::Chunk c = chunk_fit::find(fit_len, p.batch, chunk_len, su);
+    seq = c.seq;
+    split = c.split;
+  } else if (p.unit_tab) {     // chunk lengths follow the sequence lengths: active units listed first
     const int code = p.unit_tab[su];
-    if (code < 0) return;
+    if (code < 0) return false;
     seq = code >> 10;
     split = code & 1023;
     chunk_len = p.chunk_tab[seq];
@@ -113,7 +128,25 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(Mfma
     seq = p.seq_order ? p.seq_order[slot] : slot;
     chunk_len = p.chunk;
   }
-  typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
+  return true;
+}
+
+__device__ __forceinline__ f32x16 opaque_zero16() {
+  float z = 0.f;
+  asm volatile("" : "+v"(z));
+  f32x16 v;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) v[i] = z;
+  return v;
+}
+
+template <int STAGES>
+__global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(MfmaParams p) {
+  static_assert(STAGES == 2 || STAGES == 4, "a power of two, and the waits below");
+  constexpr int kMPOff = STAGES * kMStage, kMAOff = kMPOff + kMPBytes, kMFOff = kMAOff + kMHeads * 4;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int hgrp, seq, split, chunk_len;
+  if (!mla_unit(p, hgrp, seq, split, chunk_len)) return;
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
   if (t0 >= n) return;
@@ -364,6 +397,396 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(Mfma
   }
 }
 
+// ------------------------------------------------------------------------------------------------
+// The pipelined form: one workgroup of four waves per CU, four stages, and in each step the scores of one tile and the value
+// product of the tile before it, so that a wave has matrix work while its softmax, its hand-overs and its LDS reads are on
+// their way.  Against the form above:
+//   * scores and softmax by 32 heads x 16 tokens per wave (two groups of 16 heads share an operand read, 18 reads a tile
+//     instead of 36); the two waves of a head exchange their maxima over LDS and refresh the reference alike;
+//   * P^T, maxima and factors in two copies, so that one barrier hands over maxima, tile and freed stage and a second
+//     one P^T; neither has a wait behind it that matters;
+//   * everything a lane keeps per head is held for both of its groups in one register, masks and row clamps are only in the
+//     copy of the step that meets the chunk's last tile, factors are stored only when a maximum moved: 287 instructions a tile,
+//     52 of them MFMAs (430 in a first version, 300 us against 238 of the whole step below).
+// Bound by instruction issue of the one wave per SIMD: 2250 cycles a tile with 1088 of matrix pipe in them; without the tile
+// loads, the score reads or the value reads it takes 5 to 10 % less each.  Per workgroup another 15 us of start-up and
+// write-out.  HBM traffic is that of the cache once (0.68 GB on 128 sequences of 512 to 8192, two-stage form 1.01).
+// Whole steps, against the better of the two older forms: 128 sequences of 512 to 8192 x 128 heads 247.4 -> 236.2 us, x 64
+// heads 222 -> 190, 128 of 4352 x 128 heads 262 -> 222, 64 of 6000 186 -> 158, one of 4000 41.3 -> 38.2.
+// Measured and not kept: eight waves, two per SIMD, with half of the scores and channels each (260 us on the first shape
+// against 238), P^T read behind the first barrier and no second one (238), all loads of a tile behind the value product (243).
+// ------------------------------------------------------------------------------------------------
+template <int N>
+__device__ __forceinline__ void wait_lgkm() { asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(N) : "memory"); }
+
+// LDS of the pipelined kernel: the stages and, twice (tiles of even and odd number), P^T, the rescale factors, the tile
+// maxima of the four waves and the number of the last tile in which a wave's maxima grew.
+constexpr int kPStages = 4;
+constexpr int kPPOff = kPStages * kMStage, kPAOff = kPPOff + 2 * kMPBytes, kPXOff = kPAOff + 2 * kMHeads * 4,
+              kPFOff = kPXOff + 2 * 4 * 32 * 4, kPLds = kPFOff + 2 * 4 * 4;
+static_assert(kPLds <= 160 * 1024, "one workgroup per CU");
+
+__global__ __launch_bounds__(256, 1) void mla_pipe_kernel(MfmaParams p) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  int hgrp, seq, split, chunk_len;
+  if (!mla_unit(p, hgrp, seq, split, chunk_len)) return;
+  const int n = ((const_i32_ptr)p.seq_lens)[seq];
+  const int t0 = split * chunk_len;
+  if (t0 >= n) return;
+  const int t1 = min(n, t0 + chunk_len);
+  const int ntiles = (t1 - t0 + kMTok - 1) / kMTok;
+  const int nvalid_last = t1 - t0 - (ntiles - 1) * kMTok;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int g = lane >> 5, c32 = lane & 31;         // 32x32 MFMA roles (values)
+  const int q4 = lane >> 4, c16 = lane & 15;        // 16x16 MFMA roles (scores)
+  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+  const int hg = wave & 1, th = wave >> 1;          // scores: heads [32 hg, + 32), tokens [16 th, + 16) of the tile
+  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  const float sc = p.scale_log2;
+  const int head_base = hgrp * kMHeads;
+
+  // ---- tile loads.  Latent rows are 1 KiB: one load moves one token row (lane i: 16-byte chunk i, i.e. 256-byte sub-row
+  // i / 16, stored at chunk position (i % 16) ^ lat_swz(token) inside the sub-row); wave w loads tokens 8 w .. + 7 (parts
+  // 0..7) and RoPE rows 8 w .. + 7 (part 8).  Tiles are issued in order, in parts that sit behind different MFMAs; the id of
+  // the page after the current one is always loaded already (pages hold whole tiles).
+  const const_i32_ptr pt_row = (const_i32_ptr)(p.page_table + (size_t)seq * p.max_pages);
+  const size_t lat_page_bytes = (size_t)p.page_size * (kMDc * 2);
+  const size_t rope_page_bytes = (size_t)p.page_size * (kDr * 2);
+  int iss_tok = t0, iss_page_at = t0 / p.page_size, iss_slot = t0 % p.page_size;
+  unsigned iss_page = (unsigned)pt_row[iss_page_at];
+  unsigned iss_page_next = (unsigned)pt_row[min(iss_page_at + 1, p.max_pages - 1)];
+  unsigned lat_voff[8], rope_voff;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) lat_voff[i] = ((lane * 16) ^ (unsigned)(lat_swz(8 * wave + i) << 4)) + (i & 4) * 1024;
+  rope_voff = (8 * wave + (lane >> 3)) * (kDr * 2) + (((lane * 16) & 0x70) ^ (rope_swz(8 * wave + (lane >> 3)) << 4));
+  const char* iss_lat = nullptr;
+  const char* iss_rope = nullptr;
+  unsigned iss_dst = lds_base;
+  auto issue_begin = [&]() {
+    iss_lat = (const char*)p.latent + iss_page * lat_page_bytes + (unsigned)(iss_slot + 8 * wave_u) * (unsigned)(kMDc * 2);
+    iss_rope = (const char*)p.rope + iss_page * rope_page_bytes + (unsigned)iss_slot * (unsigned)(kDr * 2);
+  };
+  auto issue_part = [&](int i) {       // of a full tile (the instruction offset moves both sides)
+    if (i == 0 || i == 4) set_m0(iss_dst + wave_u * 8192 + i * 1024);
+    if (i == 8) set_m0(iss_dst + kMLatBytes + wave_u * 1024);
+    if (i == 8) lds_dma16<0>(iss_rope, rope_voff);
+    else if ((i & 3) == 0) lds_dma16<0>(iss_lat, lat_voff[i]);
+    else if ((i & 3) == 1) lds_dma16<1024>(iss_lat, lat_voff[i]);
+    else if ((i & 3) == 2) lds_dma16<2048>(iss_lat, lat_voff[i]);
+    else lds_dma16<3072>(iss_lat, lat_voff[i]);
+  };
+  auto issue_part_any = [&](int i) {   // rows past the chunk's end re-read its last one (finite values, weight 0 later)
+    const int last = min(kMTok, t1 - iss_tok) - 1;
+    if (i < 8) {
+      const int t = 8 * wave_u + i;
+      set_m0(iss_dst + t * 1024);
+      lds_dma16<0>(iss_lat + (long)(min(t, last) - 8 * wave_u) * 1024, lat_voff[i] - (i & 4) * 1024);
+    } else {
+      const int t = 8 * wave + (lane >> 3);
+      set_m0(iss_dst + kMLatBytes + wave_u * 1024);
+      lds_dma16<0>(iss_rope, rope_voff - (unsigned)(t - min(t, last)) * (kDr * 2));
+    }
+  };
+  auto issue_end = [&]() {
+    iss_tok += kMTok;
+    iss_slot += kMTok;
+    iss_dst = iss_dst == lds_base + (kPStages - 1) * kMStage ? lds_base : iss_dst + kMStage;
+    if (iss_slot == p.page_size) {
+      iss_slot = 0;
+      ++iss_page_at;
+      iss_page = iss_page_next;
+      iss_page_next = (unsigned)pt_row[min(iss_page_at + 1, p.max_pages - 1)];
+    }
+  };
+
+  // ---- query operands of this wave's 32 heads, two groups of 16
+  bf16x8 qreg[2][18];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int head = min(head_base + 32 * hg + 16 * i + c16, p.h - 1);
+    const bf16_t* qa = p.q_abs + ((size_t)seq * p.h + head) * kMDc + q4 * 8;
+    const bf16_t* qr = p.q_rope + ((size_t)seq * p.h + head) * kDr + q4 * 8;
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) qreg[i][ks] = *(const bf16x8*)(qa + ks * 32);
+    qreg[i][16] = *(const bf16x8*)qr;
+    qreg[i][17] = *(const bf16x8*)(qr + 32);
+  }
+  auto issue_whole = [&]() {
+    issue_begin();
+#pragma unroll
+    for (int i = 0; i < kMLoads; ++i) issue_part_any(i);
+    issue_end();
+  };
+  // the first tile is requested behind the queries and waited for with them; they go into the accumulation file
+  issue_whole();
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int ks = 0; ks < 18; ++ks) asm volatile("" : "+a"(qreg[i][ks]));
+  __builtin_amdgcn_sched_barrier(0);
+  const int n_pro = min(ntiles, kPStages);
+  for (int jj = 1; jj < n_pro; ++jj) issue_whole();
+  if (tid < 8) ((int*)(smem + kPFOff))[tid] = -1;
+
+  // ---- per-lane LDS read offsets inside a stage (see mla_mfma_kernel; this wave's 16 tokens only)
+  const int k_tok = c16 ^ ((c16 & 4) << 1);
+  const int q4t = q4 ^ ((q4 & 1) << 1);
+  const unsigned k_lat_off = (16 * th + k_tok) * 1024 + ((q4 ^ lat_swz(k_tok)) << 4);                     // ^ ((ks % 4) << 6), + 256 (ks / 4)
+  const unsigned k_rope_off = kMLatBytes + (16 * th + k_tok) * (kDr * 2) + ((q4 ^ rope_swz(k_tok)) << 4); // ^ (kr << 6)
+  unsigned v_off;                                                             // ^ (mt << 6), + 16 KiB ss
+  {
+    const int k = (lane & 15) >> 2, seg = lane & 3, hb = (lane >> 4) & 1, ta = 4 * g + k;
+    v_off = ta * 1024 + wave * 256 + (((2 * hb + (seg >> 1)) ^ lat_swz(ta)) << 4) + ((seg & 1) << 3);
+  }
+  // this lane's four probabilities of head group i go to + 256 i
+  const unsigned p_wr_off = hg * 2048 + th * 1024 + (c16 + 32 * (q4t & 1)) * 16 + (q4t >> 1) * 8;
+
+  // Per-head values (16 lanes a group) are kept for both groups in one register: lanes with even q4 hold group 0, odd q4
+  // group 1.  both() spreads such a register.
+  float m_run = kNegBig, mx = 0.f;
+  float neg_m[2] = {-kNegBig, -kNegBig}, l_run[2] = {0.f, 0.f};
+  auto both = [&](float x, float& g0, float& g1) {
+    g0 = g1 = x;
+    row_pairs(g0, g1);
+  };
+  f32x16 zacc[4][2];
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+    for (int nt = 0; nt < 2; ++nt) zacc[mt][nt] = opaque_zero16();
+
+  constexpr int kAhead = 10;           // score operands read in the step before
+  bf16x8 ka[18];
+  short4v vlo[2][4], vhi[2][4];
+  f32x4 s[2];
+  auto k_read = [&](unsigned base, int ks) {
+    const unsigned addr = ks < 16 ? ((base + k_lat_off) ^ ((ks & 3) << 6)) + (ks >> 2) * 256
+                                  : ((base + k_rope_off) ^ ((ks - 16) << 6));
+    ka[ks] = *(lds_bf16x8_ptr)(size_t)addr;
+  };
+  auto v_read = [&](unsigned base, int i) {     // i = 8 ss + 2 mt + half
+    const int ss = i >> 3, mt = (i >> 1) & 3;
+    if ((i & 1) == 0) vlo[ss][mt] = lds_tr16((lds_byte_ptr)(size_t)((base + v_off) ^ (mt << 6)) + ss * 16 * 1024);
+    else vhi[ss][mt] = lds_tr16((lds_byte_ptr)(size_t)((base + v_off) ^ (mt << 6) ^ 32) + (ss * 16 + 8) * 1024);
+  };
+  bf16x8 pb[2][2];
+  auto p_read = [&](int par, int i) {           // i = 2 nt + ss
+    pb[i & 1][i >> 1] = *(const bf16x8*)(smem + kPPOff + par * kMPBytes + i * 1024 + lane * 16);
+  };
+  // scores of a tile (its first operands already read), with the operands of the value product of the tile before it and, ISSUE, the
+  // second half of the loads of the tile after next
+  auto scores = [&](unsigned kb, unsigned vb, int par, auto with_v, auto issue, bool rest) {
+    constexpr bool ISSUE = decltype(issue)::value;
+    s[0] = s[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int m = 0; m < 18; ++m) {
+      s[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m], qreg[0][m], s[0], 0, 0, 0);
+      s[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[m], qreg[1][m], s[1], 0, 0, 0);
+      if (m + kAhead < 18) k_read(kb, m + kAhead);
+      if (decltype(with_v)::value && m < 16) v_read(vb, m);
+      if (decltype(with_v)::value && m >= 10 && m < 14) p_read(par, m - 10);
+      if (m % 3 == 1 && m < 15) {
+        if (ISSUE) issue_part(4 + m / 3);
+        else if (rest) issue_part_any(4 + m / 3);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (ISSUE || rest) issue_end();
+  };
+  // the tile's maxima over this wave's 16 tokens, for the wave with the other 16 as well
+  auto publish_max = [&](int par) {
+    float a = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
+    float b = fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3]));
+    row_pairs(a, b);
+    a = fmaxf(a, b);
+    b = a;
+    half_pairs(a, b);
+    mx = fmaxf(a, b);
+    ((float*)(smem + kPXOff))[(par * 4 + wave) * 32 + c32] = mx;
+  };
+  // The reference maxima (refreshed lazily, see decode_mfma.hip) from both halves' maxima; when one moves, its factor is
+  // left for the waves that hold the head's history (both halves store the same).
+  auto refresh = [&](float partner, int par, int tile) {
+    const float cand = fmaxf(mx, partner) * sc;
+    const bool grow = cand > m_run + kLazy;
+    if (__builtin_expect(__any(grow), 0)) {
+      const float m_new = grow ? cand : m_run;
+      const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+      m_run = m_new;
+      float a0, a1;
+      both(alpha, a0, a1);
+      l_run[0] *= a0;
+      l_run[1] *= a1;
+      both(-m_new, neg_m[0], neg_m[1]);
+      ((float*)(smem + kPAOff))[par * kMHeads + 32 * hg + c32] = alpha;
+      ((int*)(smem + kPFOff))[par * 4 + wave] = tile;
+    }
+  };
+  float pe[2][4];
+  auto soften = [&](int e, int valid) {        // valid: tokens of the tile (kMTok: no mask)
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      pe[i][e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][e], sc, neg_m[i]));
+      if (valid < kMTok && 16 * th + 4 * q4t + e >= valid) pe[i][e] = 0.f;    // rows past a ragged end are copies of its last one
+      l_run[i] += pe[i][e];
+    }
+  };
+  auto store_p = [&](int par) {
+    typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const bf16x4 pk = {(__bf16)pe[i][0], (__bf16)pe[i][1], (__bf16)pe[i][2], (__bf16)pe[i][3]};
+      *(bf16x4*)(smem + kPPOff + par * kMPBytes + i * 256 + p_wr_off) = pk;
+    }
+  };
+  auto rescale = [&](int2 grown, int par, int tile) {      // a head's history loses weight when its maximum grew
+    const int g0 = __builtin_amdgcn_readfirstlane(grown.x), g1 = __builtin_amdgcn_readfirstlane(grown.y);
+    if (__builtin_expect(g0 == tile || g1 == tile, 0)) {
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        const float a_h = (nt == 0 ? g0 : g1) == tile ? ((const float*)(smem + kPAOff))[par * kMHeads + nt * 32 + c32] : 1.f;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) zacc[mt][nt][i] *= a_h;
+      }
+    }
+  };
+  auto pv = [&](int m) {             // m = 4 ss + mt
+    const int ss = m >> 2, mt = m & 3;
+    const bf16x8 va = __builtin_bit_cast(bf16x8, __builtin_shufflevector(vlo[ss][mt], vhi[ss][mt], 0, 1, 2, 3, 4, 5, 6, 7));
+    zacc[mt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ss][0], zacc[mt][0], 0, 0, 0);
+    zacc[mt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va, pb[ss][1], zacc[mt][1], 0, 0, 0);
+  };
+  auto hand_over = [&]() {
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto partner_max = [&](int par) { return ((const float*)(smem + kPXOff))[(par * 4 + (wave ^ 2)) * 32 + c32]; };
+  auto grown_at = [&](int par) { return *(const int2*)(smem + kPFOff + par * 16); };   // waves 0, 1: heads 0..31, 32..63
+  auto after = [&](unsigned st) { return st == lds_base + (kPStages - 1) * kMStage ? lds_base : st + kMStage; };
+
+  // ---- prologue: scores and probabilities of tile 0
+  if (ntiles > 3) wait_vm_lgkm<3 * kMLoads>();
+  else if (ntiles > 2) wait_vm_lgkm<2 * kMLoads>();
+  else if (ntiles > 1) wait_vm_lgkm<kMLoads>();
+  else wait_vm_lgkm<0>();
+  hand_over();
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) k_read(lds_base, i);
+  scores(lds_base, 0u, 0, std::false_type{}, std::false_type{}, false);
+  publish_max(0);
+  if (ntiles > 3) wait_vm_lgkm<2 * kMLoads>();
+  else if (ntiles > 2) wait_vm_lgkm<kMLoads>();
+  else wait_vm_lgkm<0>();
+  hand_over();                       // the maxima are visible, tile 1 has landed
+  refresh(partner_max(0), 0, 0);
+#pragma unroll
+  for (int e = 0; e < 4; ++e) soften(e, ntiles == 1 ? nvalid_last : kMTok);
+  store_p(0);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) k_read(lds_base + kMStage, i);   // (one tile: whatever the stage holds, unused)
+
+  // ---- step j: scores of tile j + 1 while the operands of tile j's value product are read; one barrier; the value product
+  // of tile j, with the softmax of tile j + 1 and the first operands of tile j + 2 between its MFMAs; one barrier, behind
+  // which P^T of tile j + 1 is there.  The loads of tile j + 4 are spread over the second half of the step and the first
+  // half of the next.
+  bool rest = false;                 // the second half of a tile's loads is due
+  unsigned st_cur = lds_base;
+  __builtin_amdgcn_sched_barrier(0);
+  wait_lgkm<kAhead>();
+  hand_over();                       // P^T of tile 0
+  auto step = [&](auto issue, int j) {
+    constexpr bool ISSUE = decltype(issue)::value;         // tiles j + 3 and j + 4 exist and are no last ones
+    const int par = j & 1, next = par ^ 1;
+    const unsigned st_next = after(st_cur), st_then = after(st_next);
+    __builtin_amdgcn_sched_barrier(0);
+    const int2 grown = grown_at(par);
+    scores(st_next, st_cur, par, std::true_type{}, issue, rest);
+    publish_max(next);
+    // tile j + 2 has landed in this wave's share, its reads of tile j are done, the maxima are stored
+    if (ISSUE || j + 3 < ntiles) wait_vm_lgkm<kMLoads>();
+    else wait_vm_lgkm<0>();
+    hand_over();
+    const float partner = partner_max(next);
+    rest = ISSUE || j + 4 < ntiles;
+    const int valid = !ISSUE && j + 2 == ntiles ? nvalid_last : kMTok;
+    rescale(grown, par, j);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) {
+      pv(m);
+      if (m == 0 && (ISSUE || rest)) issue_begin();
+      if (m == 1) refresh(partner, next, j + 1);
+      if (m >= 2 && m < 6) soften(m - 2, valid);
+      if (m == 5) store_p(next);
+      if ((m & 1) == 1) {
+        if (ISSUE) issue_part(m >> 1);
+        else if (rest) issue_part_any(m >> 1);
+      }
+      if (m >= 3) {
+        k_read(st_then, 2 * (m - 3));
+        k_read(st_then, 2 * (m - 3) + 1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    wait_lgkm<4>();                  // (all but the last two pieces' reads: P^T is stored)
+    hand_over();
+    st_cur = st_next;
+  };
+  {
+    int j = 0;
+    if (ntiles > 1) step(std::false_type{}, j++);
+    for (; j + 5 < ntiles; ++j) step(std::true_type{}, j);
+    for (; j + 1 < ntiles; ++j) step(std::false_type{}, j);
+  }
+  {
+    const int j = ntiles - 1, par = j & 1;
+    const int2 grown = grown_at(par);
+#pragma unroll
+    for (int i = 0; i < 16; ++i) v_read(st_cur, i);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) p_read(par, i);
+    rescale(grown, par, j);
+#pragma unroll
+    for (int m = 0; m < 8; ++m) pv(m);
+    hand_over();                     // (every wave is past the last maxima: their space is used below)
+  }
+
+  // ---- write the chunk's partial: every wave its 128 channels of all 64 heads, and (m, l) of the heads, whose sums over
+  // the two token halves meet in LDS
+  const size_t unit = (size_t)seq * p.n_splits + split;
+#pragma unroll
+  for (int nt = 0; nt < 2; ++nt) {
+    const int head = head_base + nt * 32 + c32;
+    if (head < p.h) {
+      float* dst = p.part_z + (unit * p.h + head) * kMDc + wave * 128 + g * 4;
+#pragma unroll
+      for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const f32x4 v = {zacc[mt][nt][r4 * 4], zacc[mt][nt][r4 * 4 + 1], zacc[mt][nt][r4 * 4 + 2],
+                           zacc[mt][nt][r4 * 4 + 3]};
+          *(f32x4*)(dst + mt * 32 + r4 * 8) = v;
+        }
+    }
+  }
+  float* const lbuf = (float*)(smem + kPXOff);       // (free since the barrier above)
+#pragma unroll
+  for (int i = 0; i < 2; ++i) l_run[i] = head_sum(l_run[i]);
+  if (th == 1 && lane < 32) lbuf[hg * 32 + lane] = lane < 16 ? l_run[0] : l_run[1];
+  __syncthreads();
+  if (th == 0 && lane < 32) {
+    const int head = head_base + 32 * hg + lane;
+    if (head < p.h) {
+      p.part_ml[(unit * p.h + head) * 2 + 0] = m_run;
+      p.part_ml[(unit * p.h + head) * 2 + 1] = (lane < 16 ? l_run[0] : l_run[1]) + lbuf[hg * 32 + lane];
+    }
+  }
+}
+
 }  // namespace
 
 bool mla_mfma_supported(const DecodeArgs& a) {
@@ -408,21 +831,44 @@ int launch_mla_mfma(const DecodeArgs& a) {
   p.batch = a.batch;
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
   p.rows_bf16 = 0;
+  if (a.fitted) {
+    p.fit_min = (a.max_pages * a.page_size + 64 * a.plan.n_splits - 1) / (64 * a.plan.n_splits);
+    p.cus = device_cu_count();
+    p.chunk_out = a.chunk_tab;
+  }
   const int n_hg = (a.h + kMHeads - 1) / kMHeads;
   const long long n_wg = (long long)a.plan.n_splits * n_hg * a.batch;
   if (n_wg <= 0 || n_wg > 0x7fffffffLL) return MLRA_ERR_SHAPE;
-  if (!a.balanced && (n_wg > device_cu_count() || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
+  if (!a.balanced && !a.fitted && (n_wg > device_cu_count() || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
   // (the query tokens of one sequence are kept side by side in the order)
   p.split_major = p.seq_order && a.q_group <= 1;
-  // Four stages where every CU has one workgroup at most, none of them shares its rows with another (one head group) and
-  // the chunks are long: 64 sequences of 6000 tokens x 64 heads in four chunks, whole step 124 us against 130 with two
-  // stages, 128 of 3000 in two 128 against 134.  Two stages otherwise: with two head groups 64 of 6000 take 181 us (182.7
-  // with four stages), in chunks below 1024 tokens 30 of 2500 53 (55), with more workgroups than CUs 140 of 2000 128 (155).
-  // (Planned chunks: a batch of nearly equal lengths is left uncut and has one workgroup per sequence; 256 of 2000 x 32
-  // heads 157 against 161, and 512 chunks of a ragged one take the same or less.)
-  const long long most = a.balanced ? a.batch : n_wg;
-  const bool four = n_hg == 1 && most <= device_cu_count() && a.plan.chunk_tokens >= 1024;
-  return four ? launch_mla_as<4>(a, p, (unsigned)n_wg) : launch_mla_as<2>(a, p, (unsigned)n_wg);
+  // The pipelined kernel has one workgroup per CU, 15 us of start-up and write-out each and 1.15 us per tile; the two-stage
+  // kernel overlaps the start-up of one workgroup with another's tiles, 1.5 us each.  So the latter keeps launches of more
+  // workgroups than CUs in short chunks, where these are not fitted (whole steps, two-stage against pipelined: 100 sequences of
+  // 300 to 900 x 128 heads in chunks of 512 87 against 91 us, 140 of 2000 x 64 heads in chunks of 1024 130 against 143; with
+  // long ones 256 of 2176 x 128 heads 265 against 257).  Planned chunks of one head group go to the four-stage kernel as long
+  // as the batch is no more than a round: a batch of nearly equal lengths is left uncut then, and with many CUs idle its
+  // three tiles in flight count.
+  const int cus = device_cu_count();
+  if (a.balanced && n_hg == 1 && a.batch <= cus && a.plan.chunk_tokens >= 1024) return launch_mla_as<4>(a, p, (unsigned)n_wg);
+  if (!a.balanced && !a.fitted && n_wg > cus && a.plan.chunk_tokens < 1280) return launch_mla_as<2>(a, p, (unsigned)n_wg);
+  static PerDeviceSetup setup;
+  int setup_dev = -1;
+  if (setup.needed(&setup_dev)) {
+    if (hipFuncSetAttribute((const void*)mla_pipe_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kPLds) != hipSuccess)
+      return MLRA_ERR_LAUNCH;
+    setup.done(setup_dev);
+  }
+  MLRA_LAUNCH_TIMED(a.t_main, mla_pipe_kernel, dim3((unsigned)n_wg), dim3(256), kPLds, a.stream, p);
+  return check_launch();
 }
 
+
+// Fitted chunk lengths where the slots are more than a round of workgroups: whole steps of 30 sequences of 2500 tokens x 128
+// heads 92.7 -> 72.7 us (300 slots for 256 CUs; 87.2 in the two-stage kernel), 59 of 2836 x 64 heads 103.0 -> 82.9 (99.4).
+bool mla_mfma_fits_chunks(const DecodeArgs& a) {
+  const long slots = (long)a.plan.n_splits * a.batch * ((a.h + kMHeads - 1) / kMHeads);
+  return a.batch > 1 && a.batch <= chunk_fit::kMaxSeqs && a.q_group == 1 && a.plan.n_splits > 1 && a.plan.target_chunks == 0 &&
+         slots > device_cu_count();
+}
 }  // namespace mlra

@@ -192,13 +192,15 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   a.t_epi = timing_pair(1);
   // Up to 64 sequences: the decode kernel finds its chunk from the lengths itself (chunk_fit.h), which saves the kernels in
   // front that would plan or order the chunks.  The MLRA kernel does so with long chunks and with several query tokens per
-  // sequence, else its uniform chunks are as good and their workgroups start a round trip earlier; the fp32 kernel by its own
-  // rule.
+  // sequence, else its uniform chunks are as good and their workgroups start a round trip earlier; the MLA and the
+  // fp32 kernels by rules of their own.
   // Other batches with a target: a kernel in front plans the chunks (both MFMA kernels read its table).
   const bool mfma = decode_mfma_supported(a), merge_mfma = merge_upproj_mfma_supported(a);
   const int n_seqs = batch / q_group;
   if (mfma && merge_mfma && n_seqs <= 64) a.fitted = q_group > 1 || (a.plan.target_chunks > 0 && !a.plan.single_if_uniform);
-  const bool runs_f32 = !mfma && !decode_gla_supported(a) && !mla_mfma_supported(a) && decode_f32_supported(a);
+  const bool runs_mla = !mfma && !decode_gla_supported(a) && mla_mfma_supported(a);
+  if (runs_mla) a.fitted = mla_mfma_fits_chunks(a);
+  const bool runs_f32 = !mfma && !decode_gla_supported(a) && !runs_mla && decode_f32_supported(a);
   if (runs_f32) a.fitted = decode_f32_fits_chunks(a);
   if (q_group > 1 && !a.fitted) {
     const int st = launch_expand_queries(c->seq_lens, c->page_table, n_seqs, q_group, c->max_pages_per_seq, lens_room,

@@ -138,6 +138,7 @@ int launch_merge_upproj_f32(const DecodeArgs& a);
 int launch_seq_order(const DecodeArgs& a);
 int launch_plan_chunks(const DecodeArgs& a);
 bool mla_mfma_supported(const DecodeArgs& a);
+bool mla_mfma_fits_chunks(const DecodeArgs& a);   // for `fitted`
 int launch_mla_mfma(const DecodeArgs& a);
 bool decode_mfma_supported(const DecodeArgs& a);
 bool decode_mfma_paired(int h, int n_blocks);

@@ -95,3 +95,24 @@ def test_mlra_kernel_long(batch, h, n_max):
     print(f"[case] fit MLRA B={batch} h={h} {info}", flush=True)
     assert info["target_chunks"] > 0 and not info["single_if_uniform"]
     _check(wl, lens)
+
+
+# the MLA kernel: more slots than CUs, one and two head groups
+@pytest.mark.parametrize("batch,h,n_max", [(30, 128, 640), (63, 70, 700), (11, 16, 6000)])
+def test_mla_kernel(batch, h, n_max):
+    wl = gen.WORKLOADS["C5"].scaled(name="fit-mla", batch=batch, n_min=0, n_max=n_max, h=h, index=4500 + batch)
+    info = mlra.mlra_decode_plan_info(batch, h, 128, 1, 1, 512, 64, 64, -(-n_max // 64) * 64, torch.bfloat16)
+    print(f"[case] fit MLA B={batch} h={h} {info}", flush=True)
+    assert info["kernel"] == "mfma-mla" and batch * info["chunk_slots"] * ((h + 63) // 64) > 256 and info["target_chunks"] == 0
+    inp = gen.make_decode_inputs(wl, poison=True, seq_lens=_ragged(batch, n_max, batch))
+    q_nope, q_rope, w_uk, w_uv = device_queries_weights(gen.as_single_latent(inp))
+    lse = torch.full((batch, 1, h), float("nan"), device="cuda")
+    out = mlra.mla_decode_attn(device_cache(gen.as_single_latent(inp)), mlra.mlra_absorb_q(q_nope, w_uk), q_rope, w_uv, wl.tau,
+                               out_dtype=torch.float32, lse=lse)
+    torch.cuda.synchronize()
+    v = oracle_views(gen.as_single_latent(inp))
+    ref, ref_lse = orc.mlra_decode_batch(v["latent_pool"], v["rope_pool"], v["page_table"], v["seq_lens"], v["q_nope"],
+                                         v["q_rope"], v["w_uk"], v["w_uv"], wl.tau, 1.0, return_lse=True)
+    assert max_rel_err(host(out), ref) <= TOL["bf16"]
+    got, live = host(lse), np.isfinite(ref_lse)
+    assert np.array_equal(np.isfinite(got), live) and np.max(np.abs(got[live] - ref_lse[live])) <= 2e-2
