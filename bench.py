@@ -87,7 +87,7 @@ def _cpu_baseline(inp, max_seconds=25.0):
                       f"{dt:.1f} s of fp64 numpy, scaled to the whole batch by token count"}, np.stack(outs)
 
 
-_DECODE_KERNEL_SOURCES = ("decode_mfma.hip", "mfma_tile.h", "proj_mfma.hip")
+_DECODE_KERNEL_SOURCES = ("decode_mfma.hip", "chunk_fit.h", "mfma_tile.h", "proj_mfma.hip")
 
 
 def _kernel_sources_digest():
@@ -208,7 +208,7 @@ def _baselines(inp, mlra_decode_us):
             "gqa_gbps": gqa_bytes["total"] / (gqa_us * 1e-6) / 1e9,
             "gqa_kernel": "MFMA streaming kernel",
             "mla_decode_us": mla_us, "mla_over_mlra4": mla_us / mlra_decode_us,
-            "mla_kernel": "MFMA kernel (32-token tiles; scores split by heads, values by channels; not pipelined across tiles)",
+            "mla_kernel": "MFMA kernel (32-token tiles; scores split by heads and tokens, values by channels; pipelined over two tiles)",
             "paper_context": "H100, Section 4.5: MLRA-4 1.05-1.26x faster than GQA, about 2.8x faster than MLA "
                              "(MLRA-4 measured as one 4-way-TP device's share)"}
 

@@ -23,12 +23,16 @@ struct Chunk {
 
 // The chunk length in tokens.  n: this lane's sequence length, 0 from n_seqs on.  Each chunk is the work of `wgs`
 // workgroups, `cus` of them run at a time, and a workgroup costs its tiles and `overhead` tiles more.  Lane k prices chunks
-// of c_min + k step tiles (c_min: what the workspace has slots for).  Workgroups go out longest first, so a launch takes
-// the longest of: the rounds of whole chunks; the longest chunk; the mean over the compute units; and, where some units
-// get a second, shorter chunk, the shortest of the first ones and the longest of the second ones in a row, both about as
-// long as the sequences' last pieces are there if these spread evenly over the lengths up to a whole chunk.  The cheapest
-// length wins, among equals the longest, for the fewest partials.  Every wavefront of a launch computes the same: it runs
-// the same instructions on the same lengths.
+// of c_min + k step tiles (c_min: what the workspace has slots for).  Workgroups go out longest first: rounds of whole
+// chunks, then the sequences' last pieces beside the whole chunks of the last round.  Pieces that find no room there come
+// second on the units with the shortest first ones; both are about as long as the pieces are at that place if these spread
+// evenly over the lengths up to a whole chunk.  No launch is shorter than the mean over the units.  The cheapest length
+// wins, among equals the longest, for the fewest partials.  Every wavefront of a launch computes the same: it runs the same
+// instructions on the same lengths.
+// SHARED: a compute unit runs several workgroups at a time, which share its matrix pipe: their start-ups overlap, and one
+// alone takes 8 % longer for its tiles (fp32 kernel, 8 sequences of 8192: 222 us in one round of long chunks, 213 in two of
+// half the length).
+template <bool SHARED>
 __device__ __forceinline__ int fit_length(int n, int n_seqs, int wgs, int cus, int c_min, int overhead) {
   const int lane = threadIdx.x & 63, tiles = (n + kTokens - 1) / kTokens;
   int longest = max(tiles, c_min);
@@ -45,11 +49,12 @@ __device__ __forceinline__ int fit_length(int n, int n_seqs, int wgs, int cus, i
     units += t > 0 ? (int)((x - 0.5f) * c_inv) + 1 : 0;
   }
   const float at_once = (float)cus / (float)wgs, cost = (float)overhead, w = (float)whole, u = (float)units;
-  float price = fmaxf(ceilf(w / at_once) * ((float)c + cost), (float)c + cost);
-  if (u > at_once) {
-    price = fmaxf(price, ((float)total + u * cost) / at_once);
-    if (w < at_once) price = fmaxf(price, 2.f * ((float)c * (1.f - (at_once - w) / (u - w)) + cost));
-  }
+  const float full = floorf(w / at_once), rests = u - w, per_round = SHARED ? 0.f : cost, one = (float)c + per_round;
+  const float room = (full + 1.f) * at_once - w;        // places beside the whole chunks of the last round
+  float last = room < at_once || rests > 0.f ? one : 0.f;
+  if (rests > room) last = fmaxf(last, 2.f * ((float)c * (1.f - room / rests) + per_round));
+  float price = fmaxf(full * one + last, u > at_once ? ((float)total + u * per_round) / at_once : 0.f);
+  if (SHARED) price = price * (full * one + last < 1.5f * one ? 1.08f : 1.f) + cost;
   unsigned best = (unsigned)fminf(8.f * price, 67000000.f) << 6 | (unsigned)(63 - lane);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) best = min(best, (unsigned)__shfl_xor((int)best, o));

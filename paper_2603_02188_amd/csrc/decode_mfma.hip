@@ -84,7 +84,7 @@ __global__ __launch_bounds__(256) void plan_chunks_kernel(const int32_t* __restr
                                                           int32_t* __restrict__ unit_tab, int batch, int target,
                                                           int max_slots, int min_chunk, int single_if_uniform) {
   __shared__ float part[4];
-  __shared__ int part_max[4], part_active[4];
+  __shared__ int part_max[4], part_count[3][4];
   __shared__ int wave_tot[4];
   extern __shared__ int32_t tab[];             // [batch] lengths, [batch] chunk lengths, [batch] dispatch order
   int32_t* lens = tab;
@@ -108,30 +108,30 @@ __global__ __launch_bounds__(256) void plan_chunks_kernel(const int32_t* __restr
   const float total = (part[0] + part[1]) + (part[2] + part[3]);
   longest = max(max(part_max[0], part_max[1]), max(part_max[2], part_max[3]));
   const bool single = single_if_uniform && (float)longest * (float)batch <= 1.25f * total;
-  // (rounding may leave more than `target` chunks, whose surplus would run alone at the end: 266 of 256 in 128 sequences of
-  // 512 to 8192 tokens.  Then the shares are made a little smaller, at most three times.)
+  // Rounding may leave more than `target` chunks, whose surplus would run alone at the end (266 of 256 in 128 sequences of
+  // 512 to 8192 tokens: GLA-2 162 -> 140 us, MLRA-2 141 -> 117).  Then the shares are made a little smaller, at most three
+  // times.  (Counted are the shares, no less than the chunks that come of them.)
+  auto share_of = [&](int n, int share) {
+    const int s_i = (total > 0.f && !single) ? (int)((float)share * (float)n / total + 0.5f) : 1;
+    return min(max(s_i, 1), max_slots);
+  };
   int share = target;
-  for (int attempt = 0;; ++attempt) {
-    int active = 0;
-    for (int i = threadIdx.x; i < batch; i += 256) {
-      const int n = lens[i];
-      int s_i = (total > 0.f && !single) ? (int)((float)share * (float)n / total + 0.5f) : 1;
-      s_i = min(max(s_i, 1), max_slots);
-      int chunk = (n + s_i - 1) / s_i;
-      chunk = max(min_chunk, (chunk + kTile - 1) / kTile * kTile);
-      chunks[i] = chunk;         // ceil(n / chunk) <= s_i <= max_slots
-      chunk_tab[i] = chunk;
-      active += (n + chunk - 1) / chunk;
-    }
-    if (single || attempt == 3) break;
-    for (int o = 32; o > 0; o >>= 1) active += __shfl_xor(active, o);
-    if (lane == 0) part_active[wave] = active;
+  for (int attempt = 0; single_if_uniform && !single && attempt < 3; ++attempt) {   // (targets that are whole rounds)
+    int count = 0;
+    for (int i = threadIdx.x; i < batch; i += 256) count += lens[i] > 0 ? share_of(lens[i], share) : 0;
+    for (int o = 32; o > 0; o >>= 1) count += __shfl_xor(count, o);
+    if (lane == 0) part_count[attempt][wave] = count;
     __syncthreads();
-    active = part_active[0] + part_active[1] + part_active[2] + part_active[3];
-    __syncthreads();
-    if (active <= target) break;
-    share -= active - target;
-    if (share < 1) break;
+    count = part_count[attempt][0] + part_count[attempt][1] + part_count[attempt][2] + part_count[attempt][3];
+    if (count <= target) break;
+    share = max(1, share - (count - target));
+  }
+  for (int i = threadIdx.x; i < batch; i += 256) {
+    const int n = lens[i], s_i = share_of(n, share);
+    int chunk = (n + s_i - 1) / s_i;
+    chunk = max(min_chunk, (chunk + kTile - 1) / kTile * kTile);
+    chunks[i] = chunk;         // ceil(n / chunk) <= s_i <= max_slots
+    chunk_tab[i] = chunk;
   }
   __syncthreads();
   // dispatch order: rank sort by chunk length, longest first (ties keep index order)
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
     const int n_seqs = p.batch / p.fit_group, i = threadIdx.x & 63;
     fit_len = i < n_seqs ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
     fit_chunk = p.n_splits == 1 ? p.fit_min * kTile   // (only the order is wanted)
-                                : chunk_fit::fit_length(fit_len, n_seqs, fam * p.fit_group, p.cus, p.fit_min, kFitOverhead);
+                                : chunk_fit::fit_length<false>(fit_len, n_seqs, fam * p.fit_group, p.cus, p.fit_min, kFitOverhead);
     if (blockIdx.x == 0)
       for (int e = threadIdx.x; e < p.batch; e += 256) p.chunk_out[e] = fit_chunk;
     fit_units = chunk_fit::count(fit_len, fit_chunk);

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   if (__builtin_expect(p.chunk_tab != nullptr, 0)) {
     const int lane = threadIdx.x & 63;
     len = lane < p.batch ? max(0, min(p.seq_lens[lane], p.max_pages * p.page_size)) : 0;
-    chunk = chunk_fit::fit_length(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.chunk / chunk_fit::kTokens, 1);
+    chunk = chunk_fit::fit_length<true>(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.chunk / chunk_fit::kTokens, 1);
     if (wg == 0 && (int)threadIdx.x < p.batch) p.chunk_tab[threadIdx.x] = chunk;
     units = chunk_fit::count(len, chunk) * p.n_blocks;
   }

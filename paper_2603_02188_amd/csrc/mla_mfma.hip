@@ -92,7 +92,7 @@ __device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& se
   if (p.fit_min > 0) {         // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
     const int i = threadIdx.x & 63;
     fit_len = i < p.batch ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
-    chunk_len = chunk_fit::fit_length(fit_len, p.batch, n_hg, p.cus, p.fit_min, kMFitOverhead);
+    chunk_len = chunk_fit::fit_length<false>(fit_len, p.batch, n_hg, p.cus, p.fit_min, kMFitOverhead);
     if (blockIdx.x == 0 && (int)threadIdx.x < p.batch) p.chunk_out[threadIdx.x] = chunk_len;
     n_units = chunk_fit::count(fit_len, chunk_len);
     if ((int)blockIdx.x >= n_units * n_hg) return false;
