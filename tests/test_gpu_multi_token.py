@@ -85,11 +85,13 @@ def test_multi_token_full_size_every_sequence():
 
 
 # the queries' dispatch order, found by the decode kernel itself up to 64 sequences: runs of eight full and not, sequences
-# shorter than the queries, none of them, equal lengths; chunks of long contexts; and 65 sequences, which take the expanded tables
-@pytest.mark.parametrize("batch,q_len,n_max", [(1, 3, 700), (8, 2, 130), (9, 4, 70), (17, 3, 200), (64, 2, 66), (65, 2, 66),
-                                               (3, 2, 9000)])
-def test_multi_token_order(batch, q_len, n_max):
-    wl = gen.WORKLOADS["C5"].scaled(name="mt-order", batch=batch, n_min=0, n_max=n_max, index=4300 + batch)
+# shorter than the queries, none of them, equal lengths; chunks of long contexts; two blocks per workgroup (16 heads), two head
+# groups; and 65 sequences, which take the expanded tables
+@pytest.mark.parametrize("batch,q_len,n_max,h", [(1, 3, 700, 128), (8, 2, 130, 128), (9, 4, 70, 128), (17, 3, 200, 128),
+                                                 (64, 2, 66, 128), (65, 2, 66, 128), (3, 2, 9000, 128), (9, 3, 300, 16),
+                                                 (10, 2, 200, 200)])
+def test_multi_token_order(batch, q_len, n_max, h):
+    wl = gen.WORKLOADS["C5"].scaled(name="mt-order", batch=batch, n_min=0, n_max=n_max, h=h, index=4300 + batch)
     lens = np.random.default_rng(batch).integers(0, n_max + 1, size=batch).astype(np.int32)
     lens[0] = n_max
     if batch > 4:
