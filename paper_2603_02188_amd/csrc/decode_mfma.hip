@@ -356,13 +356,13 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   // loads of each tile lie in one page: the page ids below are this wave's; with pages of 16 or 32 tokens
   // the four waves of a tile read different pages)
   int issue_page_idx = (t0 + 16 * (int)wave_u) / p.page_size;
-  int issue_page = pt_row[min(issue_page_idx, p.max_pages - 1)];
+  int issue_page = pt_row[min((unsigned)issue_page_idx, (unsigned)p.max_pages - 1u)];
   const int n = ((const_i32_ptr)p.seq_lens)[tab_row] - behind;
-  if (t0 >= n) {
+  if (n <= 0 || (unsigned)t0 >= (unsigned)n) {   // (slots of a plan without a target chunk reach to twice the capacity)
     wait_vmcnt<0>();   // the query loads target this workgroup's LDS: let them land before it is released
     return;
   }
-  const int t1 = min(n, t0 + chunk_len);
+  const int t1 = t0 + min(n - t0, chunk_len);
   const int ntiles = (t1 - t0 + kTile - 1) / kTile;
   const int nvalid_last = t1 - t0 - (ntiles - 1) * kTile;
 

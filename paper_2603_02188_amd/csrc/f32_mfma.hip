@@ -99,8 +99,8 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   }
   const int n = p.seq_lens[s];
   const int t0 = split * chunk;
-  if (t0 >= n) return;
-  const int t1 = min(n, t0 + chunk);
+  if (n <= 0 || (unsigned)t0 >= (unsigned)n) return;   // (slots beyond the capacity)
+  const int t1 = t0 + min(n - t0, chunk);
   const int ntiles = (t1 - t0 + TT - 1) / TT;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int q = lane >> 4, r16 = lane & 15;

@@ -168,7 +168,7 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
   if (fitted_chunk) chunk = *fitted_chunk;   // (the decode kernel's own choice)
   if (tid < 16) {
     const int n = tid < n_seq ? seq_lens[m0 + tid] : 0;
-    act[tid] = min(n_splits, (n + chunk - 1) / chunk);
+    act[tid] = min(n_splits, chunks_of(n, chunk));
   }
 
   for (int r0 = 0; r0 < R; r0 += slab) {
@@ -204,7 +204,7 @@ __global__ __launch_bounds__(256) void merge_upproj_f32_kernel(
       for (int pair = tid; pair < n_pairs; pair += 256) {
         const int sl = pair / nblk, bb = pair - sl * nblk;
         const float* ml = ml_of(sl, bb);
-        const int n_act = min(n_splits, (seq_lens[m0 + sl] + chunk - 1) / chunk);
+        const int n_act = min(n_splits, chunks_of(seq_lens[m0 + sl], chunk));
         float2 got[4];
 #pragma unroll
         for (int k = 0; k < 4; ++k) got[k] = *(const float2*)(ml + (size_t)min(k, n_splits - 1) * h * 2);

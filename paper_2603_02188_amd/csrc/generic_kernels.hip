@@ -360,7 +360,7 @@ __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict_
       row[k] = slot * stride;
     }
     const int n = seq_lens[s];
-    const int active = min(n_splits, (n + chunk - 1) / chunk);
+    const int active = min(n_splits, chunks_of(n, chunk));
     float m_star = kNegBig, L = 0.f;
 #pragma unroll
     for (int k = 0; k < kFewChunks; ++k)
@@ -397,7 +397,7 @@ __global__ __launch_bounds__(256) void gqa_merge_kernel(const float* __restrict_
     return;
   }
   const int n = seq_lens[s];
-  const int active = min(n_splits, (n + chunk - 1) / chunk);
+  const int active = min(n_splits, chunks_of(n, chunk));
   float* const w = wtab + wave * n_splits;
   float m_star = kNegBig;
   for (int k = lane; k < active; k += 64) m_star = fmaxf(m_star, ml[(size_t)k * h * 2]);

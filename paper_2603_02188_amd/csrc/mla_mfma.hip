@@ -150,7 +150,7 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(Mfma
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
   if (t0 >= n) return;
-  const int t1 = min(n, t0 + chunk_len);
+  const int t1 = t0 + min(n - t0, chunk_len);
   const int ntiles = (t1 - t0 + kMTok - 1) / kMTok;
   const int nvalid_last = t1 - t0 - (ntiles - 1) * kMTok;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
@@ -433,7 +433,7 @@ __global__ __launch_bounds__(256, 1) void mla_pipe_kernel(MfmaParams p) {
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
   if (t0 >= n) return;
-  const int t1 = min(n, t0 + chunk_len);
+  const int t1 = t0 + min(n - t0, chunk_len);
   const int ntiles = (t1 - t0 + kMTok - 1) / kMTok;
   const int nvalid_last = t1 - t0 - (ntiles - 1) * kMTok;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;

@@ -83,15 +83,17 @@ SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len) {
   const long units = (long)batch * n_blocks;
   const long target = 1L * device_cu_count();
   long want = (target + units - 1) / units;
-  const long max_splits = (max_seq_len + kMinChunk - 1) / kMinChunk;
+  const long len = max_seq_len, max_splits = (len + kMinChunk - 1) / kMinChunk;
   if (want > max_splits) want = max_splits;
   if (want < 1) want = 1;
-  long chunk = (max_seq_len + want - 1) / want;
+  long chunk = (len + want - 1) / want;
   chunk = (chunk + kTile - 1) / kTile * kTile;
   if (chunk < kMinChunk) chunk = kMinChunk;
+  // (chunk lengths are 32-bit on the device: a capacity within a tile of 2^31 takes a second chunk)
+  if (chunk > 0x7fffffffL) chunk = 0x7fffffffL / kTile * kTile;
   SplitPlan p;
   p.chunk_tokens = (int)chunk;
-  p.n_splits = (int)((max_seq_len + chunk - 1) / chunk);
+  p.n_splits = (int)((len + chunk - 1) / chunk);
   if (p.n_splits < 1) p.n_splits = 1;
   p.target_chunks = 0;
   return p;

@@ -39,6 +39,11 @@ struct SplitPlan {
   bool single_if_uniform = false;   // with target_chunks: a batch of nearly equal lengths is not cut at all
 };
 
+// Chunks of `chunk` tokens that a sequence of n has (a chunk may be as long as the longest cache, close to 2^31).
+__device__ __forceinline__ int chunks_of(int n, int chunk) {
+  return (int)(((unsigned)max(n, 0) + (unsigned)chunk - 1u) / (unsigned)chunk);
+}
+
 int device_cu_count();
 
 // Kernel attributes (the dynamic LDS limit) belong to a device: a launcher sets them the first time it

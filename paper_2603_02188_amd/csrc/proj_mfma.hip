@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256, 2) void merge_upproj_mfma_kernel(
   };
   auto active_chunks = [&](int seq) {
     const int ch = chunk_tab ? chunk_tab[seq] : chunk;
-    return min(n_splits, (len_of(seq) + ch - 1) / ch);
+    return min(n_splits, chunks_of(len_of(seq), ch));
   };
   bf16x8 zero8;
 #pragma unroll

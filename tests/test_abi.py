@@ -207,3 +207,18 @@ def test_plan_info_errors():
     assert lib.mlra_decode_plan_info(4, 127, 128, 2, 4, 128, 64, 64, 8192, 0, buf) == -2      # heads do not split into groups
     assert lib.mlra_decode_plan_info(4, 128, 128, 1, 4, 128, 64, 64, 8192, 7, buf) == -3
     assert mlra.mlra_decode_plan_info(4, 128, 128, 1, 4, 128, 64, 64, 8192, torch.bfloat16)["kernel"] == "mfma"
+
+
+def test_plans_cover_capacities_close_to_2_31():
+    """Chunk lengths and slots cover the longest sequence, in tiles of 64 tokens, up to the largest capacity that the entry
+    points accept."""
+    import torch
+    for page, pages in ((64, 1 << 24), (64, (1 << 25) - 3), (64, (1 << 25) - 1), (16, (1 << 27) - 1), (1, (1 << 31) - 1),
+                        (4096, (1 << 19) - 1)):
+        cap = page * pages
+        for batch, n_blocks, dtype in ((1, 4, torch.bfloat16), (3, 1, torch.float32), (64, 4, torch.float32)):
+            info = mlra.mlra_decode_plan_info(batch, 128, 128, 1, n_blocks, 64, 64, page, cap, dtype)
+            want = -(-256 // (batch * n_blocks))
+            assert info["chunk_tokens"] > 0 and info["chunk_tokens"] % 64 == 0, (cap, batch, info)
+            assert info["chunk_tokens"] * info["chunk_slots"] >= cap, (cap, batch, info)
+            assert want <= info["chunk_slots"] <= want + 1, (cap, batch, info)

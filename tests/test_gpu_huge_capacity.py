@@ -1,0 +1,65 @@
+"""Caches whose page tables are wide enough for close to 2^31 tokens (a few pages of many tokens, shared by the sequences): what
+the kernels compute from a capacity stays in range, and the short sequences in it come out as in a small cache."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2603_02188_amd import binding as mlra
+
+from gpu_util import host, max_rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def _table(batch, width, pages):
+    table = torch.zeros((batch, width), dtype=torch.int32)
+    table[:, :pages] = torch.arange(pages, dtype=torch.int32)
+    return table.cuda()
+
+
+def _attend(q, keys, values, scale):
+    return torch.softmax((q @ keys.T) * scale, dim=-1) @ values
+
+
+# one chunk per sequence, as long as the capacity; sequences of none, one and more than the 2^31 - capacity tokens
+def test_fp32_step_in_one_chunk():
+    batch, nb, h, d_cb, d_r, d_h, page, width = 64, 4, 4, 32, 16, 32, 16384, 131071
+    print("[case] huge capacity fp32", flush=True)
+    assert mlra.mlra_decode_plan_info(batch, h, d_h, 1, nb, d_cb, d_r, page, page * width, torch.float32)["chunk_slots"] == 1
+    g = torch.Generator().manual_seed(1)
+    latent, rope = torch.randn((2, nb, page, d_cb), generator=g), torch.randn((2, page, d_r), generator=g)
+    q_abs, q_rope = torch.randn((batch, nb, h, d_cb), generator=g), torch.randn((batch, h, d_r), generator=g)
+    w_uv = torch.randn((nb, d_cb, h * d_h), generator=g) / d_cb ** 0.5
+    lens = torch.zeros(batch, dtype=torch.int32)
+    lens[0], lens[1], lens[63] = 16500, 1, 300
+    cache = mlra.Cache(latent.cuda(), rope.cuda(), _table(batch, width, 2), lens.cuda())
+    out = mlra.mlra_decode_attn(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), 0.1, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = torch.zeros((batch, h, d_h), dtype=torch.float64)
+    for s in (0, 1, 63):
+        n = int(lens[s])
+        kr = rope.double().reshape(-1, d_r)[:n]
+        for b in range(nb):
+            c = latent[:, b].double().reshape(-1, d_cb)[:n]
+            z = _attend(torch.cat((q_abs[s, b], q_rope[s]), -1).double(), torch.cat((c, kr), -1), c, 0.1)
+            ref[s] += torch.einsum("hc,chd->hd", z, w_uv[b].double().view(d_cb, h, d_h))
+    assert max_rel_err(host(out), ref.numpy()) <= 1e-5
+
+
+def test_fp32_gqa_in_one_chunk():
+    batch, h, g_heads, d_h, page, width = 256, 4, 2, 8, 16384, 131071
+    print("[case] huge capacity gqa", flush=True)
+    g = torch.Generator().manual_seed(2)
+    k, v = (torch.randn((2, g_heads, page, d_h), generator=g) for _ in range(2))
+    q = torch.randn((batch, h, d_h), generator=g)
+    lens = torch.zeros(batch, dtype=torch.int32)
+    lens[0], lens[1], lens[255] = 16500, 1, 300
+    out = mlra.gqa_decode_attn(k.cuda(), v.cuda(), _table(batch, width, 2), lens.cuda(), q.cuda(), 0.3, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = np.zeros((batch, h, d_h))
+    for s in (0, 1, 255):
+        n = int(lens[s])
+        for i in range(h):
+            keys, values = (t[:, i // (h // g_heads)].double().reshape(-1, d_h)[:n] for t in (k, v))
+            ref[s, i] = _attend(q[s, i:i + 1].double(), keys, values, 0.3)[0].numpy()
+    assert max_rel_err(host(out), ref) <= 1e-5
