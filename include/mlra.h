@@ -294,6 +294,17 @@ MLRA_API int mlra_probe_shader_clock(long long* out, int32_t spin_us, void* stre
 MLRA_API int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks, int32_t d_cb,
                                    int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype, int32_t* info);
 
+/* What mlra_decode_plan_info leaves open, for q_len query tokens per sequence (1 for the entry points but
+ * mlra_decode_attn_multi, which takes groups = 1).  info is a HOST array of 4 values:
+ *   [0] chunk slots per (unit, block), a unit being one query token of one sequence
+ *   [1] > 0: the decode kernel fits the chunk length to the lengths, a multiple of 64 tokens and at least this one ([0]
+ *       chunks of which hold the capacity); 0: it does not
+ *   [2] 1: a planning kernel cuts the chunks
+ *   [3] MLA kernel: 0 the pipelined one, 2 or 4 the one with that many tiles in flight; -1 another decode kernel */
+MLRA_API int mlra_decode_route_info(int32_t batch, int32_t q_len, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks,
+                                    int32_t d_cb, int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype,
+                                    int32_t* info);
+
 #ifdef __cplusplus
 }
 #endif

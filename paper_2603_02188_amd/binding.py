@@ -25,7 +25,7 @@ EXPORTS = ("mlra_strerror", "mlra_append_kv", "mlra_absorb_q", "mlra_absorb_q_fo
            "mlra2_decode_attn", "mlra_decode_attn_gated", "mlra_decode_multi_workspace_bytes", "mlra_decode_attn_multi",
            "mlra_pre_attention_workspace_bytes", "mlra_pre_attention",
            "gqa_decode_workspace_bytes", "gqa_decode_attn", "mlra_kernel_timing_begin",
-           "mlra_kernel_timing_end", "mlra_decode_plan_info", "mlra_probe_stream_read", "mlra_probe_shader_clock")
+           "mlra_kernel_timing_end", "mlra_decode_plan_info", "mlra_decode_route_info", "mlra_probe_stream_read", "mlra_probe_shader_clock")
 
 
 class _CacheStruct(ctypes.Structure):
@@ -95,6 +95,8 @@ def load_library() -> ctypes.CDLL:
     lib.mla_decode_attn.argtypes = [cp, i32, i32, i32, vp, vp, vp, f32, vp, i32, vp, vp, sz, vp]
     lib.mlra_decode_plan_info.restype = ctypes.c_int
     lib.mlra_decode_plan_info.argtypes = [i32] * 10 + [ctypes.POINTER(ctypes.c_int32)]
+    lib.mlra_decode_route_info.restype = ctypes.c_int
+    lib.mlra_decode_route_info.argtypes = [i32] * 11 + [ctypes.POINTER(ctypes.c_int32)]
     lib.gqa_decode_workspace_bytes.restype = sz
     lib.gqa_decode_workspace_bytes.argtypes = [i32, i32, i32, i32]
     lib.gqa_decode_attn.restype = ctypes.c_int
@@ -476,6 +478,16 @@ def mlra_decode_plan_info(batch: int, h: int, d_h: int, groups: int, n_blocks: i
                                                 _dt(dtype), info), "mlra_decode_plan_info")
     return {"kernel": DECODE_KERNELS[info[0]], "chunk_slots": info[1], "chunk_tokens": info[2],
             "target_chunks": info[3], "single_if_uniform": bool(info[4]), "merge_mfma": bool(info[5])}
+
+
+def mlra_decode_route_info(batch: int, h: int, d_h: int, groups: int, n_blocks: int, d_cb: int, d_r: int, page_size: int,
+                           max_seq_len: int, dtype: torch.dtype, q_len: int = 1) -> dict:
+    """How a decode call of this shape cuts the contexts (host logic only); mla_stages is None where the MLA kernels do not run."""
+    info = (ctypes.c_int32 * 4)()
+    _check(load_library().mlra_decode_route_info(batch, q_len, h, d_h, groups, n_blocks, d_cb, d_r, page_size, max_seq_len,
+                                                 _dt(dtype), info), "mlra_decode_route_info")
+    return {"chunk_slots": info[0], "fitted_from": info[1], "planned": bool(info[2]),
+            "mla_stages": None if info[3] < 0 else info[3]}
 
 
 def mlra_kernel_timing_begin(max_calls: int) -> None:

@@ -34,17 +34,19 @@ struct Chunk {
 // half the length).
 template <bool SHARED>
 __device__ __forceinline__ int fit_length(int n, int n_seqs, int wgs, int cus, int c_min, int overhead) {
-  const int lane = threadIdx.x & 63, tiles = (n + kTokens - 1) / kTokens;
+  const int lane = threadIdx.x & 63, tiles = chunks_of(n, kTokens);
   int longest = max(tiles, c_min);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) longest = max(longest, __shfl_xor(longest, o));
+  longest = min(longest, 0x7fffffff / kTokens);          // (in tokens it fits an int; c_min is no more than this)
   const int c = min(c_min + lane * ((c_min + 31) / 32), longest);
   const float c_inv = 1.f / (float)c;
-  int total = 0, whole = 0, units = 0;
+  unsigned total = 0;
+  int whole = 0, units = 0;
   for (int i = 0; i < n_seqs; ++i) {
     const int t = __builtin_amdgcn_readlane(tiles, i);
     const float x = (float)t;
-    total += t;
+    total += (unsigned)t;
     whole += (int)((x + 0.5f) * c_inv);                  // (rounding may miss by one from 2^20 tiles on: a price only)
     units += t > 0 ? (int)((x - 0.5f) * c_inv) + 1 : 0;
   }
@@ -63,7 +65,7 @@ __device__ __forceinline__ int fit_length(int n, int n_seqs, int wgs, int cus, i
 
 // Chunks of `chunk` tokens in the whole batch.
 __device__ __forceinline__ int count(int n, int chunk) {
-  int units = (n + chunk - 1) / chunk;
+  int units = chunks_of(n, chunk);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) units += __shfl_xor(units, o);
   return __builtin_amdgcn_readfirstlane(units);

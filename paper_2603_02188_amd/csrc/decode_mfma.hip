@@ -256,7 +256,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   const int n_hg = (p.h + kHeadsPerWG - 1) / kHeadsPerWG;
   const int fam = (GLA ? p.n_blocks : p.n_blocks / kBlocksWG) * n_hg;
   int n_units = p.n_splits * p.batch, fit_chunk = 0, fit_len = 0, fit_units = 0;
-  if (p.fit_min > 0) {
+  if (p.chunk_out) {
     const int n_seqs = p.batch / p.fit_group, i = threadIdx.x & 63;
     fit_len = i < n_seqs ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
     fit_chunk = p.n_splits == 1 ? p.fit_min * kTile   // (only the order is wanted)
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
     member = wg % fam;
   }
   int split, seq, chunk_len, tab_row, behind = 0;   // tab_row: row of seq_lens and of the page table; behind: later queries
-  if (p.fit_min > 0) {
+  if (p.chunk_out) {
     // The queries of one (sequence, chunk) take slots 8 apart: same XCD, side by side in time (see seq_order_kernel).  Runs
     // of eight chunks go over the XCDs forwards and backwards in turn, so that the XCDs' loads stay alike.
     const int run = su / (8 * p.fit_group), rem = su % (8 * p.fit_group), query = rem >> 3;
@@ -1089,12 +1089,6 @@ int launch_seq_order(const DecodeArgs& a) {
   return check_launch();
 }
 
-// The shortest chunk that the workspace has slots for, in tiles.
-static int fit_min_tiles(const DecodeArgs& a) {
-  const int tiles = (a.max_pages * a.page_size + kTile - 1) / kTile;
-  return (tiles + a.plan.n_splits - 1) / a.plan.n_splits;
-}
-
 // (several query tokens per sequence: the order is what brings a sequence's queries together, so it is
 // wanted even when one round of workgroups covers the launch)
 static bool want_seq_order(const DecodeArgs& a, long long n_wg) {
@@ -1209,7 +1203,7 @@ int launch_decode_mfma(const DecodeArgs& a) {
   p.chunk_tab = a.balanced ? a.chunk_tab : nullptr;
   p.unit_tab = a.balanced ? a.unit_tab : nullptr;
   if (a.fitted) {
-    p.fit_min = fit_min_tiles(a);
+    p.fit_min = a.fit_tiles;
     p.fit_group = a.q_group;
     p.cus = device_cu_count();
     p.chunk_out = a.chunk_tab;

@@ -38,7 +38,7 @@ struct F32Params {
   float* part_z;
   float* part_ml;
   int32_t* chunk_tab;   // non-null: the chunk length is fitted to the lengths (chunk_fit.h) and left here for the merge
-  int page_size, max_pages, n_blocks, groups, d_cb, d_r, h, n_splits, chunk, n_hg, batch, cus;
+  int page_size, max_pages, n_blocks, groups, d_cb, d_r, h, n_splits, chunk, n_hg, batch, fit_min, cus;
   float scale_log2;
 };
 
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
   if (__builtin_expect(p.chunk_tab != nullptr, 0)) {
     const int lane = threadIdx.x & 63;
     len = lane < p.batch ? max(0, min(p.seq_lens[lane], p.max_pages * p.page_size)) : 0;
-    chunk = chunk_fit::fit_length<true>(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.chunk / chunk_fit::kTokens, 1);
+    chunk = chunk_fit::fit_length<true>(len, p.batch, p.n_blocks * p.n_hg, p.cus, p.fit_min, 1);
     if (wg == 0 && (int)threadIdx.x < p.batch) p.chunk_tab[threadIdx.x] = chunk;
     units = chunk_fit::count(len, chunk) * p.n_blocks;
   }
@@ -418,6 +418,7 @@ int launch_decode_f32(const DecodeArgs& a) {
   p.chunk = a.plan.chunk_tokens;
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
   p.chunk_tab = a.fitted ? a.chunk_tab : nullptr;
+  p.fit_min = a.fit_tiles;
   p.cus = device_cu_count();
   // four-element loads: every row and every head's query starts on a multiple of four elements, and so do the bases
   const uintptr_t bases = (uintptr_t)a.latent | (uintptr_t)a.rope | (uintptr_t)a.q_abs | (uintptr_t)a.q_rope;

@@ -39,13 +39,13 @@ struct MfmaParams {
   int groups;                 // head groups (Eq. (6)): block b serves the h heads of group b / (n_blocks / groups);
                               // q_rope holds groups * h heads.  1 = every block serves every head (Eq. (5))
   float scale_log2;
-  int fit_min = 0;            // > 0: the kernel fits one chunk length, of at least this many tiles, to the lengths
-                              // (chunk_fit.h) and leaves it in chunk_out[batch] for the merge
+  int32_t* chunk_out = nullptr;   // non-null: the kernel fits one chunk length to the lengths (chunk_fit.h) and leaves it
+                                  // in chunk_out[batch] for the merge
+  int fit_min = 0;            // ... of at least this many tiles of 64 tokens
   int fit_group = 1;          // ... entries [i fit_group, (i + 1) fit_group) of the batch are the queries of one sequence:
                               // seq_lens and page_table have one row for all of them, query j sees fit_group - 1 - j
                               // tokens less
   int cus = 0;
-  int32_t* chunk_out = nullptr;
   int split_major = 0;        // (MLA) dispatch order: all sequences' first chunks, then all second ones, ...
   int rows_bf16;              // 1: part_z receives each chunk's partial as z / l rounded to bf16, [..][chunk][head][channels]
                               // (what the MFMA epilogue merges); 0: fp32 partials, not normalised (fp32 merge, MLA)

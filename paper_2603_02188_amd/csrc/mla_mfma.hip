@@ -89,7 +89,7 @@ __device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& se
   // workgroup -> (sequence, chunk, head half); the halves of one (sequence, chunk) get ids 8 apart
   const int n_hg = (p.h + kMHeads - 1) / kMHeads;
   int n_units = p.n_splits * p.batch, fit_len = 0;
-  if (p.fit_min > 0) {         // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
+  if (p.chunk_out) {         // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
     const int i = threadIdx.x & 63;
     fit_len = i < p.batch ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
     chunk_len = chunk_fit::fit_length<false>(fit_len, p.batch, n_hg, p.cus, p.fit_min, kMFitOverhead);
@@ -108,7 +108,7 @@ __device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& se
     su = full_units + wg / n_hg;
     hgrp = wg % n_hg;
   }
-  if (p.fit_min > 0) {
+  if (p.chunk_out) {
     const chunk_fit::Chunk c = chunk_fit::find(fit_len, p.batch, chunk_len, su);
     seq = c.seq;
     split = c.split;
@@ -808,6 +808,19 @@ static int launch_mla_as(const DecodeArgs& a, const MfmaParams& p, unsigned n_wg
   return check_launch();
 }
 
+// The pipelined kernel has one workgroup per CU, 15 us of start-up and write-out each and 1.15 us per tile; the two-stage
+// kernel overlaps the start-up of one workgroup with another's tiles, 1.5 us each.  So the latter keeps launches of more
+// workgroups than CUs in short chunks, where these are not fitted (whole steps, two-stage against pipelined: 100 sequences of
+// 300 to 900 x 128 heads in chunks of 512 87 against 91 us, 140 of 2000 x 64 heads in chunks of 1024 130 against 143; with
+// long ones 256 of 2176 x 128 heads 265 against 257).  Planned chunks of one head group go to the four-stage kernel as long
+// as the batch is no more than a round: a batch of nearly equal lengths is left uncut then, and with many CUs idle its
+// three tiles in flight count.
+int mla_mfma_stages(const DecodeArgs& a) {
+  const int cus = device_cu_count(), n_hg = (a.h + kMHeads - 1) / kMHeads;
+  if (a.balanced && n_hg == 1 && a.batch <= cus && a.plan.chunk_tokens >= 1024) return 4;
+  return !a.balanced && !a.fitted && (long)a.plan.n_splits * n_hg * a.batch > cus && a.plan.chunk_tokens < 1280 ? 2 : 0;
+}
+
 int launch_mla_mfma(const DecodeArgs& a) {
   MfmaParams p;
   p.latent = (const bf16_t*)a.latent;
@@ -832,7 +845,7 @@ int launch_mla_mfma(const DecodeArgs& a) {
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
   p.rows_bf16 = 0;
   if (a.fitted) {
-    p.fit_min = (a.max_pages * a.page_size + 64 * a.plan.n_splits - 1) / (64 * a.plan.n_splits);
+    p.fit_min = a.fit_tiles;
     p.cus = device_cu_count();
     p.chunk_out = a.chunk_tab;
   }
@@ -842,16 +855,9 @@ int launch_mla_mfma(const DecodeArgs& a) {
   if (!a.balanced && !a.fitted && (n_wg > device_cu_count() || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
   // (the query tokens of one sequence are kept side by side in the order)
   p.split_major = p.seq_order && a.q_group <= 1;
-  // The pipelined kernel has one workgroup per CU, 15 us of start-up and write-out each and 1.15 us per tile; the two-stage
-  // kernel overlaps the start-up of one workgroup with another's tiles, 1.5 us each.  So the latter keeps launches of more
-  // workgroups than CUs in short chunks, where these are not fitted (whole steps, two-stage against pipelined: 100 sequences of
-  // 300 to 900 x 128 heads in chunks of 512 87 against 91 us, 140 of 2000 x 64 heads in chunks of 1024 130 against 143; with
-  // long ones 256 of 2176 x 128 heads 265 against 257).  Planned chunks of one head group go to the four-stage kernel as long
-  // as the batch is no more than a round: a batch of nearly equal lengths is left uncut then, and with many CUs idle its
-  // three tiles in flight count.
-  const int cus = device_cu_count();
-  if (a.balanced && n_hg == 1 && a.batch <= cus && a.plan.chunk_tokens >= 1024) return launch_mla_as<4>(a, p, (unsigned)n_wg);
-  if (!a.balanced && !a.fitted && n_wg > cus && a.plan.chunk_tokens < 1280) return launch_mla_as<2>(a, p, (unsigned)n_wg);
+  const int stages = mla_mfma_stages(a);
+  if (stages == 4) return launch_mla_as<4>(a, p, (unsigned)n_wg);
+  if (stages == 2) return launch_mla_as<2>(a, p, (unsigned)n_wg);
   static PerDeviceSetup setup;
   int setup_dev = -1;
   if (setup.needed(&setup_dev)) {

@@ -133,6 +133,39 @@ static size_t decode_ws_bytes(int batch, int h, int n_blocks, int d_cb, const Sp
          align_up((size_t)batch * p.n_splits * sizeof(int32_t), 256);
 }
 
+enum DecodeKernel { kPlain = 0, kMlra = 1, kGla = 3, kMla = 4, kF32 = 5 };   // (mlra_decode_plan_info [0]; 2: kMlra, paired)
+struct Route {
+  DecodeKernel kernel;
+  bool merge_mfma;   // the bf16 epilogue
+  bool planned;      // a kernel in front plans the chunks
+};
+
+// Which kernels a call takes, from its shape; sets a.fitted and a.fit_tiles.
+// Up to 64 sequences: the decode kernel finds its chunk from the lengths itself (chunk_fit.h), which saves the kernels in
+// front that would plan or order the chunks.  The MLRA kernel does so with long chunks and with several query tokens per
+// sequence, else its uniform chunks are as good and their workgroups start a round trip earlier; the MLA and the
+// fp32 kernels by rules of their own.
+// Other batches with a target: a kernel in front plans the chunks (both MFMA kernels read its table).
+static Route choose_route(DecodeArgs& a) {
+  Route r;
+  r.kernel = decode_mfma_supported(a) ? kMlra
+             : decode_gla_supported(a) ? kGla
+             : mla_mfma_supported(a)  ? kMla
+             : decode_f32_supported(a) ? kF32
+                                       : kPlain;
+  r.merge_mfma = merge_upproj_mfma_supported(a);
+  a.fitted = r.kernel == kMlra ? r.merge_mfma && a.batch / a.q_group <= 64 &&
+                                     (a.q_group > 1 || (a.plan.target_chunks > 0 && !a.plan.single_if_uniform))
+             : r.kernel == kMla ? mla_mfma_fits_chunks(a)
+             : r.kernel == kF32 ? decode_f32_fits_chunks(a)
+                                : false;
+  const long tiles = ((long)a.max_pages * a.page_size + 63) / 64;   // (a capacity is below 2^31, this sum need not be)
+  a.fit_tiles = r.kernel == kF32 ? a.plan.chunk_tokens / 64 : (int)((tiles + a.plan.n_splits - 1) / a.plan.n_splits);
+  r.planned = !a.fitted && a.plan.target_chunks > 0 && r.merge_mfma &&
+              (r.kernel == kMlra || r.kernel == kGla || r.kernel == kMla);
+  return r;
+}
+
 // h: heads served by one block (all heads when groups == 1, the heads of one group otherwise)
 // q_group > 1: the batch is batch / q_group sequences with q_group query tokens each; the rooms take a row of the lengths
 // and of the page table per query, for the kernels that want them
@@ -192,38 +225,25 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   a.stream = (hipStream_t)stream;
   a.t_main = timing_pair(0);
   a.t_epi = timing_pair(1);
-  // Up to 64 sequences: the decode kernel finds its chunk from the lengths itself (chunk_fit.h), which saves the kernels in
-  // front that would plan or order the chunks.  The MLRA kernel does so with long chunks and with several query tokens per
-  // sequence, else its uniform chunks are as good and their workgroups start a round trip earlier; the MLA and the
-  // fp32 kernels by rules of their own.
-  // Other batches with a target: a kernel in front plans the chunks (both MFMA kernels read its table).
-  const bool mfma = decode_mfma_supported(a), merge_mfma = merge_upproj_mfma_supported(a);
-  const int n_seqs = batch / q_group;
-  if (mfma && merge_mfma && n_seqs <= 64) a.fitted = q_group > 1 || (a.plan.target_chunks > 0 && !a.plan.single_if_uniform);
-  const bool runs_mla = !mfma && !decode_gla_supported(a) && mla_mfma_supported(a);
-  if (runs_mla) a.fitted = mla_mfma_fits_chunks(a);
-  const bool runs_f32 = !mfma && !decode_gla_supported(a) && !runs_mla && decode_f32_supported(a);
-  if (runs_f32) a.fitted = decode_f32_fits_chunks(a);
+  const Route r = choose_route(a);
   if (q_group > 1 && !a.fitted) {
-    const int st = launch_expand_queries(c->seq_lens, c->page_table, n_seqs, q_group, c->max_pages_per_seq, lens_room,
+    const int st = launch_expand_queries(c->seq_lens, c->page_table, batch / q_group, q_group, c->max_pages_per_seq, lens_room,
                                          table_room, a.stream);
     if (st != MLRA_OK) return st;
     a.seq_lens = lens_room;
     a.page_table = table_room;
   }
-  if (!a.fitted && a.plan.target_chunks > 0 && merge_mfma && (mfma || decode_gla_supported(a) || mla_mfma_supported(a)))
-    a.balanced = launch_plan_chunks(a) == MLRA_OK;
+  if (r.planned) a.balanced = launch_plan_chunks(a) == MLRA_OK;
   // the MLRA MFMA kernels hand the epilogue normalised bf16 rows (one per chunk) instead of fp32 partials
-  a.rows_bf16 = merge_upproj_mfma_supported(a) && (decode_mfma_supported(a) || decode_gla_supported(a));
+  a.rows_bf16 = r.merge_mfma && (r.kernel == kMlra || r.kernel == kGla);
   // the MFMA launchers record their kernel's own start and end; the others are bracketed by stream markers
-  const bool main_fast = decode_mfma_supported(a) || decode_gla_supported(a) || mla_mfma_supported(a);
-  const bool epi_fast = merge_upproj_mfma_supported(a);
+  const bool main_fast = r.kernel == kMlra || r.kernel == kGla || r.kernel == kMla, epi_fast = r.merge_mfma;
   if (a.t_main.on() && !main_fast) (void)hipEventRecord(a.t_main.start, a.stream);
-  int st = decode_mfma_supported(a) ? launch_decode_mfma(a)
-           : decode_gla_supported(a) ? launch_decode_gla(a)
-           : mla_mfma_supported(a)  ? launch_mla_mfma(a)
-           : decode_f32_supported(a) ? launch_decode_f32(a)
-                                     : launch_decode_generic(a);
+  int st = r.kernel == kMlra ? launch_decode_mfma(a)
+           : r.kernel == kGla ? launch_decode_gla(a)
+           : r.kernel == kMla ? launch_mla_mfma(a)
+           : r.kernel == kF32 ? launch_decode_f32(a)
+                              : launch_decode_generic(a);
   if (st != MLRA_OK) return st;
   if (a.t_main.on() && !main_fast) (void)hipEventRecord(a.t_main.stop, a.stream);
   if (a.t_epi.on() && !epi_fast) (void)hipEventRecord(a.t_epi.start, a.stream);
@@ -444,15 +464,18 @@ int mla_decode_attn(const mlra_cache* cache, int32_t batch, int32_t h, int32_t d
                        workspace, workspace_bytes, stream);
 }
 
-int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks, int32_t d_cb,
-                          int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype, int32_t* info) {
-  if (!info) return MLRA_ERR_NULL;
+// The arguments of a decode call as far as its route depends on them; q_len query tokens for each of batch sequences.
+static int shape_args(DecodeArgs& a, int batch, int q_len, int h, int d_h, int groups, int n_blocks, int d_cb, int d_r,
+                      int page_size, int max_seq_len, int dtype) {
   if (!valid_dtype(dtype)) return MLRA_ERR_DTYPE;
-  if (batch <= 0 || h <= 0 || d_h <= 0 || groups <= 0 || n_blocks <= 0 || d_cb <= 0 || d_r <= 0 || page_size <= 0 ||
-      max_seq_len <= 0 || h % groups != 0 || n_blocks % groups != 0)
+  if (batch <= 0 || q_len <= 0 || h <= 0 || d_h <= 0 || groups <= 0 || n_blocks <= 0 || d_cb <= 0 || d_r <= 0 ||
+      page_size <= 0 || max_seq_len <= 0 || h % groups != 0 || n_blocks % groups != 0)
     return MLRA_ERR_SHAPE;
-  DecodeArgs a = {};
-  a.batch = batch;
+  const long pages = ((long)max_seq_len + page_size - 1) / page_size;
+  if (pages * page_size > 0x7fffffffL || (q_len > 1 && (groups != 1 || (long)batch * q_len > 65535))) return MLRA_ERR_SHAPE;
+  a = DecodeArgs{};
+  a.batch = batch * q_len;
+  a.q_group = q_len;
   a.h = h / groups;          // heads served by one block
   a.groups = groups;
   a.d_h = d_h;
@@ -460,19 +483,41 @@ int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups,
   a.d_cb = d_cb;
   a.d_r = d_r;
   a.page_size = page_size;
-  a.max_pages = (max_seq_len + page_size - 1) / page_size;
+  a.max_pages = (int)pages;
   a.dtype = dtype;
-  a.plan = plan_decode(batch, a.h, n_blocks, d_cb, a.max_pages * page_size);
-  info[0] = decode_mfma_supported(a) ? (decode_mfma_paired(a.h, n_blocks) ? 2 : 1)
-            : decode_gla_supported(a) ? 3
-            : mla_mfma_supported(a)  ? 4
-            : decode_f32_supported(a) ? 5
-                                      : 0;
+  a.plan = plan_decode(a.batch, a.h, n_blocks, d_cb, a.max_pages * page_size);
+  return MLRA_OK;
+}
+
+int mlra_decode_plan_info(int32_t batch, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks, int32_t d_cb,
+                          int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype, int32_t* info) {
+  if (!info) return MLRA_ERR_NULL;
+  DecodeArgs a;
+  const int st = shape_args(a, batch, 1, h, d_h, groups, n_blocks, d_cb, d_r, page_size, max_seq_len, dtype);
+  if (st != MLRA_OK) return st;
+  const Route r = choose_route(a);
+  info[0] = r.kernel == kMlra && decode_mfma_paired(a.h, n_blocks) ? 2 : (int)r.kernel;
   info[1] = a.plan.n_splits;
   info[2] = a.plan.chunk_tokens;
   info[3] = a.plan.target_chunks;
   info[4] = a.plan.single_if_uniform ? 1 : 0;
-  info[5] = merge_upproj_mfma_supported(a) ? 1 : 0;
+  info[5] = r.merge_mfma ? 1 : 0;
+  return MLRA_OK;
+}
+
+int mlra_decode_route_info(int32_t batch, int32_t q_len, int32_t h, int32_t d_h, int32_t groups, int32_t n_blocks,
+                           int32_t d_cb, int32_t d_r, int32_t page_size, int32_t max_seq_len, int32_t dtype,
+                           int32_t* info) {
+  if (!info) return MLRA_ERR_NULL;
+  DecodeArgs a;
+  const int st = shape_args(a, batch, q_len, h, d_h, groups, n_blocks, d_cb, d_r, page_size, max_seq_len, dtype);
+  if (st != MLRA_OK) return st;
+  const Route r = choose_route(a);
+  a.balanced = r.planned;
+  info[0] = a.plan.n_splits;
+  info[1] = a.fitted ? a.fit_tiles * 64 : 0;
+  info[2] = r.planned ? 1 : 0;
+  info[3] = r.kernel == kMla ? mla_mfma_stages(a) : -1;
   return MLRA_OK;
 }
 

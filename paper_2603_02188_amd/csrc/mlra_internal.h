@@ -108,6 +108,7 @@ struct DecodeArgs {
   int32_t* unit_tab;   // [batch * n_splits] active (sequence, chunk) pairs, then -1 (workspace); same
   bool balanced;       // chunk lengths follow the sequence lengths (chunk_tab) instead of plan.chunk_tokens
   bool fitted;         // the decode kernel fits one chunk length to the lengths and leaves it in chunk_tab
+  int fit_tiles;       // ... of at least this many tiles of 64 tokens, >= 1: with them the slots hold the capacity
   bool rows_bf16;      // the decode kernel writes each chunk's partial as a normalised bf16 row z / l (the MLRA
                        // MFMA kernels); otherwise fp32 partials Z (the MLA and the fp32 kernels)
   SplitPlan plan;
@@ -144,6 +145,7 @@ int launch_seq_order(const DecodeArgs& a);
 int launch_plan_chunks(const DecodeArgs& a);
 bool mla_mfma_supported(const DecodeArgs& a);
 bool mla_mfma_fits_chunks(const DecodeArgs& a);   // for `fitted`
+int mla_mfma_stages(const DecodeArgs& a);         // which kernel: 0 the pipelined one, 2 or 4 the one with that many stages
 int launch_mla_mfma(const DecodeArgs& a);
 bool decode_mfma_supported(const DecodeArgs& a);
 bool decode_mfma_paired(int h, int n_blocks);

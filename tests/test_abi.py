@@ -222,3 +222,33 @@ def test_plans_cover_capacities_close_to_2_31():
             assert info["chunk_tokens"] > 0 and info["chunk_tokens"] % 64 == 0, (cap, batch, info)
             assert info["chunk_tokens"] * info["chunk_slots"] >= cap, (cap, batch, info)
             assert want <= info["chunk_slots"] <= want + 1, (cap, batch, info)
+
+
+def test_fitted_chunks_cover_capacities_close_to_2_31():
+    """Where the decode kernel fits the chunk length, the slots cover the capacity with the shortest one (the page table's width
+    sets it, however short the sequences are)."""
+    import torch
+    bf16, f32 = torch.bfloat16, torch.float32
+    # kernel's shape (h, n_blocks, d_cb, dtype), batch, q_len: MLA, MLRA with long chunks, several query tokens, fp32
+    for h, nb, d_cb, dtype, batch, q_len in ((64, 1, 512, bf16, 3, 1), (128, 1, 512, bf16, 3, 1), (128, 1, 512, bf16, 60, 1),
+                                             (128, 4, 128, bf16, 4, 1), (128, 4, 128, bf16, 16, 4), (128, 4, 128, bf16, 64, 4),
+                                             (16, 4, 128, bf16, 7, 3), (128, 4, 128, f32, 8, 1), (128, 2, 64, f32, 60, 1)):
+        for page, pages in ((4096, (1 << 19) - 1), (64, (1 << 25) - 1), (32, (1 << 26) - 1), (64, 3_000_001), (64, 1000)):
+            cap = page * pages
+            r = mlra.mlra_decode_route_info(batch, h, 128, 1, nb, d_cb, 64, page, cap, dtype, q_len)
+            case = (h, nb, d_cb, batch, q_len, cap, r)
+            assert r["fitted_from"] % 64 == 0 and not (r["planned"] and r["fitted_from"]), case
+            assert r["fitted_from"] > 0 if cap > 1 << 30 else r["fitted_from"] >= 0, case
+            assert not r["fitted_from"] or cap <= r["fitted_from"] * r["chunk_slots"] < 3 * cap, case
+
+
+def test_route_info_errors():
+    import torch
+    lib = mlra.load_library()
+    buf = (ctypes.c_int32 * 4)()
+    assert lib.mlra_decode_route_info(4, 1, 128, 128, 1, 4, 128, 64, 64, 8192, 0, None) == -1
+    for bad in ((4, 0, 128, 128, 1, 4, 128, 64, 64, 8192, 0), (4, 2, 128, 128, 2, 4, 128, 64, 64, 8192, 0),
+                (40000, 2, 128, 128, 1, 4, 128, 64, 64, 8192, 0), (4, 1, 128, 128, 1, 4, 128, 64, 64, 0x7fffffff, 0)):
+        assert lib.mlra_decode_route_info(*bad, buf) == -2, bad
+    assert lib.mlra_decode_route_info(4, 1, 128, 128, 1, 4, 128, 64, 64, 8192, 7, buf) == -3
+    assert mlra.mlra_decode_route_info(4, 128, 128, 1, 4, 128, 64, 64, 8192, torch.bfloat16)["mla_stages"] is None

@@ -63,3 +63,55 @@ def test_fp32_gqa_in_one_chunk():
             keys, values = (t[:, i // (h // g_heads)].double().reshape(-1, d_h)[:n] for t in (k, v))
             ref[s, i] = _attend(q[s, i:i + 1].double(), keys, values, 0.3)[0].numpy()
     assert max_rel_err(host(out), ref) <= 1e-5
+
+
+# chunk lengths fitted by the kernel: several query tokens in one chunk as long as the capacity, and the MLA kernel, whose
+# shortest chunk is 390,168 tiles of 64 tokens here
+def test_several_query_tokens_in_one_chunk():
+    batch, q_len, nb, h, d_cb, d_r, d_h, page, width = 64, 2, 4, 128, 128, 64, 128, 16384, 131071
+    print("[case] huge capacity several query tokens", flush=True)
+    route = mlra.mlra_decode_route_info(batch, h, d_h, 1, nb, d_cb, d_r, page, page * width, torch.bfloat16, q_len)
+    assert route["chunk_slots"] == 1 and route["fitted_from"] == page * width
+    g = torch.Generator().manual_seed(3)
+    bf = lambda *shape: torch.randn(shape, generator=g).bfloat16()
+    latent, rope = bf(2, nb, page, d_cb), bf(2, page, d_r)
+    q_abs, q_rope, w_uv = bf(batch, q_len, nb, h, d_cb), bf(batch, q_len, h, d_r), (bf(nb, d_cb, h * d_h) / 16).bfloat16()
+    lens = torch.zeros(batch, dtype=torch.int32)
+    lens[0], lens[1], lens[63] = 16500, 1, 300
+    cache = mlra.Cache(latent.cuda(), rope.cuda(), _table(batch, width, 2), lens.cuda())
+    out = mlra.mlra_decode_attn_multi(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), 0.05, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = torch.zeros((batch, q_len, h, d_h), dtype=torch.float64)
+    for s in (0, 1, 63):
+        for j in range(q_len):
+            n = int(lens[s]) - (q_len - 1 - j)
+            if n <= 0:
+                continue
+            kr = rope.double().reshape(-1, d_r)[:n]
+            for b in range(nb):
+                c = latent[:, b].double().reshape(-1, d_cb)[:n]
+                z = _attend(torch.cat((q_abs[s, j, b], q_rope[s, j]), -1).double(), torch.cat((c, kr), -1), c, 0.05)
+                ref[s, j] += (z[:, None, :] @ w_uv[b].double().view(d_cb, h, d_h).transpose(0, 1))[:, 0]
+    assert max_rel_err(host(out), ref.numpy()) <= 1e-2
+
+
+def test_mla_fitted():
+    batch, h, d_c, d_r, d_h, page, width = 3, 64, 512, 64, 128, 4096, (1 << 19) - 1
+    print("[case] huge capacity mla", flush=True)
+    route = mlra.mlra_decode_route_info(batch, h, d_h, 1, 1, d_c, d_r, page, page * width, torch.bfloat16)
+    assert route["chunk_slots"] == 86 and route["fitted_from"] == 390168 * 64
+    g = torch.Generator().manual_seed(4)
+    bf = lambda *shape: torch.randn(shape, generator=g).bfloat16()
+    latent, rope = bf(2, 1, page, d_c), bf(2, page, d_r)
+    q_abs, q_rope, w_uv = bf(batch, 1, h, d_c), bf(batch, h, d_r), (bf(1, d_c, h * d_h) / 16).bfloat16()
+    lens = torch.tensor([5000, 0, 77], dtype=torch.int32)
+    cache = mlra.Cache(latent.cuda(), rope.cuda(), _table(batch, width, 2), lens.cuda())
+    out = mlra.mla_decode_attn(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), 0.03, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = torch.zeros((batch, h, d_h), dtype=torch.float64)
+    for s in (0, 2):
+        n = int(lens[s])
+        c, kr = latent.double().reshape(-1, d_c)[:n], rope.double().reshape(-1, d_r)[:n]
+        z = _attend(torch.cat((q_abs[s, 0], q_rope[s]), -1).double(), torch.cat((c, kr), -1), c, 0.03)
+        ref[s] = (z[:, None, :] @ w_uv[0].double().view(d_c, h, d_h).transpose(0, 1))[:, 0]
+    assert max_rel_err(host(out), ref.numpy()) <= 1e-2
