@@ -228,34 +228,45 @@ __global__ __launch_bounds__(256) void decode_f32_kernel(F32Params p) {
         for (int tt = 0; tt < NTT; ++tt)
           sc[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[tt][e], qf[i][e], sc[tt], 0, 0, 0);
     }
-    float mx = -INFINITY;
+    float mx = -INFINITY, lowest = INFINITY;
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         const float x = sc[tt][i] * p.scale_log2;
+        lowest = fminf(lowest, x);
         sc[tt][i] = tok0 + tt * 16 + 4 * q + i < valid ? x : -INFINITY;
         mx = fmaxf(mx, sc[tt][i]);
       }
     mx = fmaxf(mx, __shfl_xor(mx, 16));
     mx = fmaxf(mx, __shfl_xor(mx, 32));
     const float m_new = fmaxf(m_run, mx);
-    // (the bare instruction, exact to one unit: exp2f spends a few more on results below 2^-126, which are weights of
-    // nothing here; 47.3 -> 45.8 us on 8 sequences of 300 to 2048)
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float alpha = exp2f(m_run - m_new);
     m_run = m_new;
     l_run *= alpha;
 #pragma unroll
     for (int m = 0; m < NCT; ++m)
 #pragma unroll
       for (int ct = 0; ct < 4; ++ct) z[m][ct] *= alpha;
+    // The exponential instruction returns zero below 2^-126; exp2f spends a few more on a denormal result, and the values can
+    // make such a weight count.  Only a tile that holds one pays for it, the bits of the others are the same either way.
+    // 8 sequences of 300 to 2048: kernel 47.3 us with exp2f throughout, 45.8 with the instruction throughout; the whole step
+    // takes as long with this test in it as with the latter (75.0 us).
+    if (__builtin_expect(__any(lowest - m_new < -126.f), 0)) {
+#pragma unroll
+      for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc[tt][i] = exp2f(sc[tt][i] - m_new);
+    } else {
+#pragma unroll
+      for (int tt = 0; tt < NTT; ++tt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sc[tt][i] = __builtin_amdgcn_exp2f(sc[tt][i] - m_new);   // masked rows: 2^(-inf) = 0
+    }
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sc[tt][i] = __builtin_amdgcn_exp2f(sc[tt][i] - m_new);   // masked rows: 2^(-inf) = 0
-        l_run += sc[tt][i];
-      }
+      for (int i = 0; i < 4; ++i) l_run += sc[tt][i];
     const float* vrow = tile + (tok0 + 4 * q) * P + 4 * r16;
 #pragma unroll
     for (int tt = 0; tt < NTT; ++tt)
