@@ -272,7 +272,7 @@ __global__ __launch_bounds__(kFinishThreads) void pre_finish_down_kernel(
     int page_size, T* __restrict__ c_q, TC* __restrict__ latent, TC* __restrict__ rope_pool,
     float* __restrict__ cs_tab) {
   typedef __attribute__((ext_vector_type(W == 1 ? 2 : W))) float vec_t;   // (W = 1 uses element 0)
-  extern __shared__ __attribute__((aligned(16))) float row[];   // this workgroup's summed columns, times their gains
+  extern __shared__ __attribute__((aligned(16))) float row[];   // this workgroup's summed columns
   __shared__ float red[kFinishThreads / 64];
   __shared__ float cs_sh[256];               // (cos, sin) per RoPE frequency of this sequence's position
   const int s = blockIdx.x, tid = threadIdx.x;
@@ -282,6 +282,16 @@ __global__ __launch_bounds__(kFinishThreads) void pre_finish_down_kernel(
   const T* const gain = kv ? gain_kv : gain_q;
   const int pos = positions[s];
   const int page = kv && pos >= 0 ? page_table[(size_t)s * max_pages + pos / page_size] : 0;
+  // gains of the columns that this thread finishes (the later ones of rows beyond four rounds are fetched when they are
+  // used); they go on last, so that a column times its gain stays in range where the result does
+  constexpr int kGains = 4;
+  float gn[kGains];
+#pragma unroll
+  for (int u = 0; u < kGains; ++u) gn[u] = 1.f;
+  if (gain) {
+#pragma unroll
+    for (int u = 0; u < kGains; ++u) gn[u] = load_f32(gain, min(tid + u * kFinishThreads, n_norm - 1));
+  }
   // cos / sin of position * theta_l.  Positions reach 10^5 and beyond, so the product and its reduction
   // to [-pi, pi] are done in double (a float angle would be off by ~1e-2 rad there); the reduced angle is
   // then accurate to ~1e-11 and float sine / cosine of it are good to a few ulp.
@@ -301,12 +311,9 @@ __global__ __launch_bounds__(kFinishThreads) void pre_finish_down_kernel(
   float ss = 0.f;
   constexpr int kKK = 16;
   for (int j = W * tid; j < nc; j += W * kFinishThreads) {
-    float v[W], gn[W];
+    float v[W];
 #pragma unroll
-    for (int e = 0; e < W; ++e) {
-      v[e] = 0.f;
-      gn[e] = gain && j < n_norm ? load_f32(gain, j + e) : 1.f;
-    }
+    for (int e = 0; e < W; ++e) v[e] = 0.f;
     for (int k = 0; k < n_slices; k += kKK) {
       vec_t t[kKK];
 #pragma unroll
@@ -323,22 +330,31 @@ __global__ __launch_bounds__(kFinishThreads) void pre_finish_down_kernel(
 #pragma unroll
     for (int e = 0; e < W; ++e) {
       if (j < n_norm) ss += v[e] * v[e];
-      row[j + e] = v[e] * gn[e];
+      row[j + e] = v[e];
     }
   }
   ss = block_sum(ss, red);                    // (its barrier completes row and cs_sh as well)
   const float r = (kv ? alpha_kv : alpha_q) * rsqrtf(ss / n_norm + eps);
+  auto each = [&](auto&& put) {       // put(column, its value)
+#pragma unroll
+    for (int u = 0; u < kGains; ++u) {
+      const int j = tid + u * kFinishThreads;
+      if (j < n_norm) put(j, row[j] * r * gn[u]);
+    }
+    for (int j = tid + kGains * kFinishThreads; j < n_norm; j += kFinishThreads)
+      put(j, row[j] * r * (gain ? load_f32(gain, j) : 1.f));
+  };
   if (!kv) {
-    for (int j = tid; j < d_cq; j += kFinishThreads) store_f32(c_q, (size_t)s * d_cq + j, row[j] * r);
+    each([&](int j, float v) { store_f32(c_q, (size_t)s * d_cq + j, v); });
     return;
   }
   if (pos < 0) return;                        // no cache row for this sequence (as in mlra_append_kv)
   const int slot = pos % page_size;
   const int d_cb = d_c / n_blocks;
-  for (int j = tid; j < d_c; j += kFinishThreads) {
+  each([&](int j, float v) {
     const int b = j / d_cb, c = j % d_cb;
-    store_f32(latent, (((size_t)page * n_blocks + b) * page_size + slot) * d_cb + c, row[j] * r);
-  }
+    store_f32(latent, (((size_t)page * n_blocks + b) * page_size + slot) * d_cb + c, v);
+  });
   for (int l = tid; l < d_r / 2; l += kFinishThreads) {
     const float c = cs_sh[2 * l], sn = cs_sh[2 * l + 1];
     float y0, y1;

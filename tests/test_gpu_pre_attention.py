@@ -26,11 +26,14 @@ def _say(msg):
     sys.stdout.flush()
 
 
-def _run_and_check(wl, d, d_cq, lens, unit_gains=False):
+def _run_and_check(wl, d, d_cq, lens, unit_gains=False, scales=None):
     _say(f"[case] pre-attention {wl.name} B={wl.batch} d={d} d_cq={d_cq} NB={wl.n_blocks} d_cb={wl.d_cb} "
          f"d_r={wl.d_r} h={wl.h} d_h={wl.d_h} {wl.dtype}")
     inp = gen.make_decode_inputs(wl, poison=True, hole=True, seq_lens=lens)
     pre = gen.make_pre_inputs(wl, d, d_cq, unit_gains=unit_gains)
+    if scales:                                   # (fp32) factors on the hidden states and on the gains
+        pre.hidden, pre.eps = pre.hidden * np.float32(scales[0]), 1e-6 * scales[0] ** 2
+        pre.gain_q, pre.gain_kv = pre.gain_q * np.float32(scales[1]), pre.gain_kv * np.float32(scales[1])
     tag = wl.dtype
     cache = device_cache(inp)
     lat_before, rope_before = cache.latent.clone(), cache.rope.clone()
@@ -128,3 +131,12 @@ def test_pre_attention_bf16_paper_shape_unit_gains():
 def test_pre_attention_finish_columns(key, d, d_cq, nb, d_cb, d_r):
     wl = gen.WORKLOADS[key].scaled(name="pre-finish", batch=3, h=4, n_blocks=nb, d_cb=d_cb, d_r=d_r, n_min=1, n_max=500)
     _run_and_check(wl, d=d, d_cq=d_cq, lens=np.array([500, 0, 65], dtype=np.int32))
+
+
+# columns and gains whose product leaves the range of fp32 while the normalised column times its gain does not (10^40, 10^-42),
+# in rows of up to four rounds of the finishing kernel's threads and of more
+@pytest.mark.parametrize("scales", [(1e15, 1e25), (1e-17, 1e-25)])
+@pytest.mark.parametrize("d_cq,d_cb", [(64, 34), (2100, 128)])
+def test_pre_attention_gains_far_from_the_columns(scales, d_cq, d_cb):
+    wl = gen.WORKLOADS["C1"].scaled(name="pre-range", batch=2, h=4, n_blocks=2, d_cb=d_cb, n_min=1, n_max=500)
+    _run_and_check(wl, d=64, d_cq=d_cq, lens=np.array([500, 65], dtype=np.int32), scales=scales)
