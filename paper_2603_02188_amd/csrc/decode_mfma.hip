@@ -1092,7 +1092,7 @@ int launch_seq_order(const DecodeArgs& a) {
 // (several query tokens per sequence: the order is what brings a sequence's queries together, so it is
 // wanted even when one round of workgroups covers the launch)
 static bool want_seq_order(const DecodeArgs& a, long long n_wg) {
-  return !a.balanced && !a.fitted && (n_wg > device_cu_count() || a.q_group > 1);
+  return !a.balanced && !a.fitted && (n_wg > a.cus || a.q_group > 1);
 }
 
 // Pages of 16 or 32 tokens (a wave's 16 rows of a tile never straddle a page), or whole tiles.
@@ -1205,7 +1205,7 @@ int launch_decode_mfma(const DecodeArgs& a) {
   if (a.fitted) {
     p.fit_min = a.fit_tiles;
     p.fit_group = a.q_group;
-    p.cus = device_cu_count();
+    p.cus = a.cus;
     p.chunk_out = a.chunk_tab;
   }
   if (want_seq_order(a, n_wg) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;

@@ -389,7 +389,7 @@ static int head_tiles(const DecodeArgs& a) {
   const int n_ht = (a.h + 15) / 16;
   const long units = (long)a.plan.n_splits * a.n_blocks * a.batch;
   int ht = n_ht >= 4 ? 4 : n_ht >= 2 ? 2 : 1;
-  while (ht > 1 && units * ((n_ht + ht - 1) / ht) < device_cu_count()) ht >>= 1;
+  while (ht > 1 && units * ((n_ht + ht - 1) / ht) < a.cus) ht >>= 1;
   return ht;
 }
 
@@ -404,7 +404,7 @@ bool decode_f32_fits_chunks(const DecodeArgs& a) {
   const long wgs = (long)a.plan.n_splits * a.n_blocks * a.batch * ((a.h + 16 * ht - 1) / (16 * ht));
   const int k16 = D <= 32 ? 2 : a.d_cb <= 64 && D <= 96 ? 6 : a.d_cb <= 128 && D <= 192 ? 12 : 20, v64 = (a.d_cb + 63) / 64;
   const long cycles = 32L * ht * (4 * k16 + 16 * v64) * (a.plan.chunk_tokens / chunk_fit::kTokens);   // matrix pipe, per chunk
-  return wgs > device_cu_count() && cycles >= 12000;
+  return wgs > a.cus && cycles >= 12000;
 }
 
 int launch_decode_f32(const DecodeArgs& a) {
@@ -430,7 +430,7 @@ int launch_decode_f32(const DecodeArgs& a) {
   p.scale_log2 = softmax_scale_log2(a.softmax_scale);
   p.chunk_tab = a.fitted ? a.chunk_tab : nullptr;
   p.fit_min = a.fit_tiles;
-  p.cus = device_cu_count();
+  p.cus = a.cus;
   // four-element loads: every row and every head's query starts on a multiple of four elements, and so do the bases
   const uintptr_t bases = (uintptr_t)a.latent | (uintptr_t)a.rope | (uintptr_t)a.q_abs | (uintptr_t)a.q_rope;
   const bool vec = a.d_cb % 4 == 0 && a.d_r % 4 == 0 && bases % (a.dtype == MLRA_BF16 ? 8 : 16) == 0;

@@ -816,9 +816,9 @@ static int launch_mla_as(const DecodeArgs& a, const MfmaParams& p, unsigned n_wg
 // as the batch is no more than a round: a batch of nearly equal lengths is left uncut then, and with many CUs idle its
 // three tiles in flight count.
 int mla_mfma_stages(const DecodeArgs& a) {
-  const int cus = device_cu_count(), n_hg = (a.h + kMHeads - 1) / kMHeads;
-  if (a.balanced && n_hg == 1 && a.batch <= cus && a.plan.chunk_tokens >= 1024) return 4;
-  return !a.balanced && !a.fitted && (long)a.plan.n_splits * n_hg * a.batch > cus && a.plan.chunk_tokens < 1280 ? 2 : 0;
+  const int n_hg = (a.h + kMHeads - 1) / kMHeads;
+  if (a.balanced && n_hg == 1 && a.batch <= a.cus && a.plan.chunk_tokens >= 1024) return 4;
+  return !a.balanced && !a.fitted && (long)a.plan.n_splits * n_hg * a.batch > a.cus && a.plan.chunk_tokens < 1280 ? 2 : 0;
 }
 
 int launch_mla_mfma(const DecodeArgs& a) {
@@ -846,13 +846,13 @@ int launch_mla_mfma(const DecodeArgs& a) {
   p.rows_bf16 = 0;
   if (a.fitted) {
     p.fit_min = a.fit_tiles;
-    p.cus = device_cu_count();
+    p.cus = a.cus;
     p.chunk_out = a.chunk_tab;
   }
   const int n_hg = (a.h + kMHeads - 1) / kMHeads;
   const long long n_wg = (long long)a.plan.n_splits * n_hg * a.batch;
   if (n_wg <= 0 || n_wg > 0x7fffffffLL) return MLRA_ERR_SHAPE;
-  if (!a.balanced && !a.fitted && (n_wg > device_cu_count() || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
+  if (!a.balanced && !a.fitted && (n_wg > a.cus || a.q_group > 1) && launch_seq_order(a) == MLRA_OK) p.seq_order = a.seq_order;
   // (the query tokens of one sequence are kept side by side in the order)
   p.split_major = p.seq_order && a.q_group <= 1;
   const int stages = mla_mfma_stages(a);
@@ -875,6 +875,6 @@ int launch_mla_mfma(const DecodeArgs& a) {
 bool mla_mfma_fits_chunks(const DecodeArgs& a) {
   const long slots = (long)a.plan.n_splits * a.batch * ((a.h + kMHeads - 1) / kMHeads);
   return a.batch > 1 && a.batch <= chunk_fit::kMaxSeqs && a.q_group == 1 && a.plan.n_splits > 1 && a.plan.target_chunks == 0 &&
-         slots > device_cu_count();
+         slots > a.cus;
 }
 }  // namespace mlra

@@ -42,14 +42,14 @@ int device_cu_count() {
 // Enough workgroups to cover every CU once when the batch alone cannot (the decode kernel runs one
 // workgroup per CU, and each workgroup pays a fixed start-up and write-out cost), never chunks shorter
 // than 128 tokens (a partial costs as much traffic as ~170 cached tokens of one block).
-SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len);
+SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len, int cus);
 
 // Workgroups per (sequence, chunk): the MLRA kernels run one per latent block, the MLA kernel (one
 // 512-dim latent) one per 64 heads.
-static SplitPlan plan_decode(int batch, int h, int n_blocks, int d_cb, int max_seq_len) {
+static SplitPlan plan_decode(int batch, int h, int n_blocks, int d_cb, int max_seq_len, int cus) {
   int groups = (n_blocks == 1 && d_cb == 512) ? (h + 63) / 64 : n_blocks;
   if (d_cb == 128 && decode_mfma_paired(h, n_blocks)) groups = n_blocks / 2;   // two blocks per workgroup
-  SplitPlan p = plan_splits(batch, groups, max_seq_len);
+  SplitPlan p = plan_splits(batch, groups, max_seq_len, cus);
   // Split mode on the MFMA MLRA shape with long chunks: twice the chunk slots, so that long sequences of
   // a ragged batch can take more chunks than short ones (the decode entry decides per call whether it
   // uses them).  The planning kernel and the round of idle slots cost 6-9 us whatever the batch looks
@@ -69,20 +69,19 @@ static SplitPlan plan_decode(int batch, int h, int n_blocks, int d_cb, int max_s
   const bool mla = n_blocks == 1 && d_cb == 512;
   const bool two_per_wg = (d_cb == 128 && decode_mfma_paired(h, n_blocks)) || d_cb == 256;
   const long wgs = (long)batch * groups;
-  if ((mla || two_per_wg) && p.n_splits == 1 && p.target_chunks == 0 && 2 * wgs > device_cu_count() &&
-      wgs < 2 * device_cu_count() && max_seq_len >= 2048 && batch <= 512) {
-    p.target_chunks = (int)std::max<long>(batch, 2L * device_cu_count() / groups);
+  if ((mla || two_per_wg) && p.n_splits == 1 && p.target_chunks == 0 && 2 * wgs > cus &&
+      wgs < 2 * cus && max_seq_len >= 2048 && batch <= 512) {
+    p.target_chunks = (int)std::max<long>(batch, 2L * cus / groups);
     p.n_splits = 4;
     p.single_if_uniform = true;
   }
   return p;
 }
 
-SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len) {
+SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len, int cus) {
   const int kMinChunk = 128, kTile = 64;
   const long units = (long)batch * n_blocks;
-  const long target = 1L * device_cu_count();
-  long want = (target + units - 1) / units;
+  long want = (cus + units - 1) / units;
   const long len = max_seq_len, max_splits = (len + kMinChunk - 1) / kMinChunk;
   if (want > max_splits) want = max_splits;
   if (want < 1) want = 1;
@@ -185,7 +184,8 @@ static int decode_common(const mlra_cache* c, int batch, int h, int groups, int 
   if (c->n_blocks % groups != 0) return MLRA_ERR_SHAPE;
   const int max_seq_len = c->max_pages_per_seq * c->page_size;
   DecodeArgs a;
-  a.plan = plan_decode(batch, h, c->n_blocks, c->d_cb, max_seq_len);
+  a.cus = device_cu_count();
+  a.plan = plan_decode(batch, h, c->n_blocks, c->d_cb, max_seq_len, a.cus);
   const size_t need = decode_ws_bytes(batch, h, c->n_blocks, c->d_cb, a.plan);
   if (!workspace || workspace_bytes < need) return MLRA_ERR_WORKSPACE;
   if (((uintptr_t)workspace) % 256 != 0) return MLRA_ERR_WORKSPACE;
@@ -320,7 +320,7 @@ int mlra_absorb_q_folded(int32_t batch, int32_t h, int32_t d_h, int32_t n_blocks
 
 size_t mlra_decode_workspace_bytes(int32_t batch, int32_t h, int32_t n_blocks, int32_t d_cb, int32_t max_seq_len) {
   if (batch <= 0 || h <= 0 || n_blocks <= 0 || d_cb <= 0 || max_seq_len <= 0) return 0;
-  return decode_ws_bytes(batch, h, n_blocks, d_cb, plan_decode(batch, h, n_blocks, d_cb, max_seq_len));
+  return decode_ws_bytes(batch, h, n_blocks, d_cb, plan_decode(batch, h, n_blocks, d_cb, max_seq_len, device_cu_count()));
 }
 
 int mlra_decode_attn(const mlra_cache* cache, int32_t batch, int32_t h, int32_t d_h, const void* q_abs,
@@ -418,7 +418,7 @@ int mlra2_absorb_q_folded(int32_t batch, int32_t h, int32_t d_h, int32_t n_block
 size_t mlra2_decode_workspace_bytes(int32_t batch, int32_t h, int32_t n_blocks, int32_t d_cb, int32_t max_seq_len) {
   if (batch <= 0 || h <= 0 || n_blocks <= 0 || d_cb <= 0 || max_seq_len <= 0) return 0;
   if (h % 2 != 0 || n_blocks % 2 != 0) return 0;
-  return decode_ws_bytes(batch, h / 2, n_blocks, d_cb, plan_decode(batch, h / 2, n_blocks, d_cb, max_seq_len));
+  return decode_ws_bytes(batch, h / 2, n_blocks, d_cb, plan_decode(batch, h / 2, n_blocks, d_cb, max_seq_len, device_cu_count()));
 }
 
 int mlra2_decode_attn(const mlra_cache* cache, int32_t batch, int32_t h, int32_t d_h, const void* q_abs,
@@ -485,7 +485,8 @@ static int shape_args(DecodeArgs& a, int batch, int q_len, int h, int d_h, int g
   a.page_size = page_size;
   a.max_pages = (int)pages;
   a.dtype = dtype;
-  a.plan = plan_decode(a.batch, a.h, n_blocks, d_cb, a.max_pages * page_size);
+  a.cus = device_cu_count();
+  a.plan = plan_decode(a.batch, a.h, n_blocks, d_cb, a.max_pages * page_size, a.cus);
   return MLRA_OK;
 }
 
@@ -558,7 +559,7 @@ int mlra_kernel_timing_end(double* main_kernel_ms, double* epilogue_kernel_ms, i
 
 size_t gqa_decode_workspace_bytes(int32_t batch, int32_t h, int32_t d_h, int32_t max_seq_len) {
   if (batch <= 0 || h <= 0 || d_h <= 0 || max_seq_len <= 0) return 0;
-  const SplitPlan p = plan_splits(batch, 1, max_seq_len);
+  const SplitPlan p = plan_splits(batch, 1, max_seq_len, device_cu_count());
   const size_t units = (size_t)batch * p.n_splits;
   return align_up(units * h * d_h * sizeof(float), 256) + align_up(units * h * 2 * sizeof(float), 256);
 }
@@ -580,9 +581,10 @@ int gqa_decode_attn(const void* k_pool, const void* v_pool, const int32_t* page_
   a.d_h = d_h;
   a.dtype = dtype;
   // the MFMA kernel runs one workgroup per (sequence, KV head, chunk), the generic one splits further
-  a.plan = plan_splits(batch, g, max_pages_per_seq * page_size);
+  const int cus = device_cu_count();
+  a.plan = plan_splits(batch, g, max_pages_per_seq * page_size, cus);
   const bool use_mfma = gqa_mfma_supported(a);
-  if (!use_mfma) a.plan = plan_splits(batch, 1, max_pages_per_seq * page_size);
+  if (!use_mfma) a.plan = plan_splits(batch, 1, max_pages_per_seq * page_size, cus);
   const size_t units = (size_t)batch * a.plan.n_splits;
   const size_t need = align_up(units * h * d_h * sizeof(float), 256) + align_up(units * h * 2 * sizeof(float), 256);
   if (!workspace || workspace_bytes < need || ((uintptr_t)workspace) % 256 != 0) return MLRA_ERR_WORKSPACE;

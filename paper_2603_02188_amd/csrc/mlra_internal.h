@@ -61,7 +61,7 @@ class PerDeviceSetup {
  private:
   std::atomic<unsigned long long> seen_{0};
 };
-SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len);
+SplitPlan plan_splits(int batch, int n_blocks, int max_seq_len, int cus);
 
 static inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -112,6 +112,7 @@ struct DecodeArgs {
   bool rows_bf16;      // the decode kernel writes each chunk's partial as a normalised bf16 row z / l (the MLRA
                        // MFMA kernels); otherwise fp32 partials Z (the MLA and the fp32 kernels)
   SplitPlan plan;
+  int cus;   // compute units (device_cu_count(), which asks the runtime for the current device)
   int dtype;
   hipStream_t stream;
   KernelTimer t_main, t_epi;   // set by mlra_kernel_timing_begin: the decode kernel and the merge / up-projection

@@ -552,7 +552,7 @@ int launch_merge_upproj_mfma(const DecodeArgs& a) {
   // small batches: fewer sequences per workgroup while that brings more workgroups onto idle CUs (not below 8: with 4 or
   // 2, 4 sequences of up to 128K took the same 17 us; two workgroups per CU instead of one cost 64 sequences 3 us)
   int spw = 32;
-  while (spw > 8 && (long)a.h * a.groups * ((a.batch + spw - 1) / spw) < device_cu_count()) spw /= 2;
+  while (spw > 8 && (long)a.h * a.groups * ((a.batch + spw - 1) / spw) < a.cus) spw /= 2;
   const dim3 grid(a.h, (a.batch + spw - 1) / spw, a.groups);
   return a.out_dtype == MLRA_BF16 ? launch_merge_typed<bf16_t>(a, grid, spw) : launch_merge_typed<float>(a, grid, spw);
 }
