@@ -463,8 +463,8 @@ __global__ __launch_bounds__(256, 1) void mla_pipe_kernel(MfmaParams p) {
   const char* iss_rope = nullptr;
   unsigned iss_dst = lds_base;
   auto issue_begin = [&]() {
-    iss_lat = (const char*)p.latent + iss_page * lat_page_bytes + (unsigned)(iss_slot + 8 * wave_u) * (unsigned)(kMDc * 2);
-    iss_rope = (const char*)p.rope + iss_page * rope_page_bytes + (unsigned)iss_slot * (unsigned)(kDr * 2);
+    iss_lat = (const char*)p.latent + iss_page * lat_page_bytes + (size_t)(iss_slot + 8 * wave_u) * (kMDc * 2);   // (pages of 4 GiB)
+    iss_rope = (const char*)p.rope + iss_page * rope_page_bytes + (size_t)iss_slot * (kDr * 2);
   };
   auto issue_part = [&](int i) {       // of a full tile (the instruction offset moves both sides)
     if (i == 0 || i == 4) set_m0(iss_dst + wave_u * 8192 + i * 1024);

@@ -115,3 +115,28 @@ def test_mla_fitted():
         z = _attend(torch.cat((q_abs[s, 0], q_rope[s]), -1).double(), torch.cat((c, kr), -1), c, 0.03)
         ref[s] = (z[:, None, :] @ w_uv[0].double().view(d_c, h, d_h).transpose(0, 1))[:, 0]
     assert max_rel_err(host(out), ref.numpy()) <= 1e-2
+
+
+# a cache that is one page of more than 4 GiB of latents: the heavy tokens (a RoPE channel makes the others' weights 0) are the last
+# ones, whose latents a 32-bit offset would take from the page's start
+def test_mla_page_beyond_32_bit_offsets():
+    h, d_c, d_r, d_h, page, heavy = 64, 512, 64, 128, (1 << 22) + 128, 100
+    n = page - 13
+    print("[case] huge page mla", flush=True)
+    assert mlra.mlra_decode_route_info(1, h, d_h, 1, 1, d_c, d_r, page, page, torch.bfloat16)["mla_stages"] == 0
+    g = torch.Generator().manual_seed(5)
+    bf = lambda *shape: torch.randn(shape, generator=g).bfloat16()
+    latent = torch.zeros((1, 1, page, d_c), dtype=torch.bfloat16, device="cuda")
+    rope = torch.zeros((1, page, d_r), dtype=torch.bfloat16, device="cuda")
+    c, kr, q_abs, q_rope = bf(heavy, d_c), bf(heavy, d_r), bf(1, 1, h, d_c), bf(1, h, d_r)
+    kr[:, 0], q_rope[:, :, 0] = 0.0, 64.0
+    w_uv = (bf(1, d_c, h * d_h) / 16).bfloat16()
+    latent[0, 0, n - heavy:n], rope[0, n - heavy:n] = c.cuda(), kr.cuda()
+    rope[0, :n - heavy, 0] = -1000.0                  # scores 0.03 x 64000 below: weights of 0
+    cache = mlra.Cache(latent, rope, torch.zeros((1, 1), dtype=torch.int32, device="cuda"),
+                       torch.tensor([n], dtype=torch.int32, device="cuda"))
+    out = mlra.mla_decode_attn(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), 0.03, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    z = _attend(torch.cat((q_abs[0, 0], q_rope[0]), -1).double(), torch.cat((c, kr), -1).double(), c.double(), 0.03)
+    ref = (z[:, None, :] @ w_uv[0].double().view(d_c, h, d_h).transpose(0, 1))[:, 0]
+    assert max_rel_err(host(out)[0], ref.numpy()) <= 1e-2
