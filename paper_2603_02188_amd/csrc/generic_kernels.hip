@@ -106,8 +106,8 @@ __global__ __launch_bounds__(256) void decode_generic_kernel(
   const int s = blockIdx.z;
   const int n = seq_lens[s];
   const int t0 = split * chunk;
-  if (t0 >= n) return;
-  const int t1 = min(n, t0 + chunk);
+  if (n <= 0 || (unsigned)t0 >= (unsigned)n) return;   // (slots beyond the capacity)
+  const int t1 = t0 + min(n - t0, chunk);
   const int head0 = hg * HG;
   const int nh = min(HG, h - head0);
   const int tid = threadIdx.x;
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(256) void gqa_generic_kernel(
   const int n = seq_lens[s];
   const int t0 = split * chunk;
   if (t0 >= n) return;
-  const int t1 = min(n, t0 + chunk);
+  const int t1 = t0 + min(n - t0, chunk);
   const int head0 = j * r + sub * HG;
   const int nh = min(HG, r - sub * HG);
   const int tid = threadIdx.x;

@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void gqa_mfma_kernel(GqaMfmaParams p) {
       }
     return;
   }
-  const int t1 = min(n, t0 + p.chunk);
+  const int t1 = t0 + min(n - t0, p.chunk);
   const int n_sub = (t1 - t0 + kGTok - 1) / kGTok;          // sub-tiles of this chunk
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int g = lane >> 5, c32 = lane & 31;

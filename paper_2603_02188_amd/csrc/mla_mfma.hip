@@ -432,7 +432,7 @@ __global__ __launch_bounds__(256, 1) void mla_pipe_kernel(MfmaParams p) {
   if (!mla_unit(p, hgrp, seq, split, chunk_len)) return;
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
-  if (t0 >= n) return;
+  if (n <= 0 || (unsigned)t0 >= (unsigned)n) return;   // (unplanned slots reach beyond 2^31 in the widest caches)
   const int t1 = t0 + min(n - t0, chunk_len);
   const int ntiles = (t1 - t0 + kMTok - 1) / kMTok;
   const int nvalid_last = t1 - t0 - (ntiles - 1) * kMTok;

@@ -140,3 +140,33 @@ def test_mla_page_beyond_32_bit_offsets():
     z = _attend(torch.cat((q_abs[0, 0], q_rope[0]), -1).double(), torch.cat((c, kr), -1).double(), c.double(), 0.03)
     ref = (z[:, None, :] @ w_uv[0].double().view(d_c, h, d_h).transpose(0, 1))[:, 0]
     assert max_rel_err(host(out)[0], ref.numpy()) <= 1e-2
+
+
+# four slots per sequence that no planning kernel cuts (the epilogue is the fp32 one): each chunk is as long as the capacity, and
+# the third and fourth start beyond 2^31
+@pytest.mark.parametrize("dtype,kernel", [(torch.bfloat16, "mfma-mla"), (torch.float32, "generic")])
+def test_slots_beyond_the_capacity(dtype, kernel):
+    batch, h, d_c, d_r, d_h, page, width = 256, 8, 512, 64, 64, 4096, (1 << 19) - 1
+    print(f"[case] slots beyond the capacity {kernel}", flush=True)
+    info = mlra.mlra_decode_plan_info(batch, h, d_h, 1, 1, d_c, d_r, page, page * width, dtype)
+    route = mlra.mlra_decode_route_info(batch, h, d_h, 1, 1, d_c, d_r, page, page * width, dtype)
+    assert info["kernel"] == kernel and info["chunk_slots"] == 4 and info["chunk_tokens"] == page * width
+    assert not route["planned"] and not route["fitted_from"]
+    g = torch.Generator().manual_seed(6)
+    draw = lambda *shape: torch.randn(shape, generator=g).to(dtype)
+    latent, rope = draw(2, 1, page, d_c), draw(2, page, d_r)
+    q_abs, q_rope, w_uv = draw(batch, 1, h, d_c), draw(batch, h, d_r), (draw(1, d_c, h * d_h) / 16).to(dtype)
+    lens = torch.zeros(batch, dtype=torch.int32)
+    lens[0], lens[1], lens[255] = 4200, 1, 300
+    table = torch.zeros((batch, width), dtype=torch.int32, device="cuda")
+    table[:, 1] = 1
+    cache = mlra.Cache(latent.cuda(), rope.cuda(), table, lens.cuda())
+    out = mlra.mla_decode_attn(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), 0.03, out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    ref = torch.zeros((batch, h, d_h), dtype=torch.float64)
+    for s in (0, 1, 255):
+        n = int(lens[s])
+        c, kr = latent.double().reshape(-1, d_c)[:n], rope.double().reshape(-1, d_r)[:n]
+        z = _attend(torch.cat((q_abs[s, 0], q_rope[s]), -1).double(), torch.cat((c, kr), -1), c, 0.03)
+        ref[s] = (z[:, None, :] @ w_uv[0].double().view(d_c, h, d_h).transpose(0, 1))[:, 0]
+    assert max_rel_err(host(out), ref.numpy()) <= (1e-2 if dtype == torch.bfloat16 else 1e-5)
