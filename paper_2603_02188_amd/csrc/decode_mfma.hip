@@ -1007,17 +1007,16 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
   }
   const size_t unit = ((size_t)seq * p.n_blocks + blk) * p.n_splits + split;
   constexpr int kZRow = GLA ? 2 * kDcb : kDcb;   // channels of one partial row in the workspace (GLA: hw is the channel half)
+  float inv_l[2] = {1.f, 1.f};
   if (p.rows_bf16) {
     // The chunk's partial leaves normalised: z * (1 / l) rounded to bf16, with (m, l) beside it in fp32.  A
     // convex combination of cache rows is no larger than they are, so bf16 holds it as well as it holds
     // the cache; with one chunk per sequence the row is already what the up-projection consumes, with
     // several the merge weighs the rows by 2^(m_k - m*) l_k.  Half the bytes of fp32 partials.
+    // (1 / l goes on behind the weights: their product would be a denormal number where a half of the tokens lies far below
+    // the other, however large its values)
 #pragma unroll
-    for (int nt = 0; nt < 2; ++nt) {
-      const float inv = l_out[nt] > 0.f ? 1.f / l_out[nt] : 0.f;
-      w_own[nt] *= inv;
-      w_par[nt] *= inv;
-    }
+    for (int nt = 0; nt < 2; ++nt) inv_l[nt] = l_out[nt] > 0.f ? 1.f / l_out[nt] : 0.f;
   }
   auto finish = [&](auto nt_tag, auto mt_tag, auto pair_tag, auto at) {
     constexpr int nt = decltype(nt_tag)::value, mt = decltype(mt_tag)::value, pr = decltype(pair_tag)::value,
@@ -1036,6 +1035,10 @@ __global__ __launch_bounds__(256) void decode_mfma_kernel(MfmaParams p) {
       typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
       typedef __attribute__((ext_vector_type(2))) unsigned uint2v;
       typedef __attribute__((ext_vector_type(4))) unsigned uint4v;
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] *= inv_l[nt];
       uint2v x = __builtin_bit_cast(uint2v, bf16x4{(__bf16)v[0][0], (__bf16)v[0][1], (__bf16)v[0][2], (__bf16)v[0][3]});
       uint2v y = __builtin_bit_cast(uint2v, bf16x4{(__bf16)v[1][0], (__bf16)v[1][1], (__bf16)v[1][2], (__bf16)v[1][3]});
       unsigned x0 = x[0], x1 = x[1], y0 = y[0], y1 = y[1];

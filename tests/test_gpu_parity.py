@@ -325,3 +325,33 @@ def test_workspace_too_small_is_refused_on_device_pointers():
     ws = torch.empty(256, dtype=torch.uint8, device="cuda")
     with pytest.raises(RuntimeError, match="workspace"):
         mlra.mlra_decode_attn(cache, q_abs, q_rope, w_uv, wl.tau, workspace=ws)
+
+
+# The halves of the MLRA kernel's tiles (32 tokens each) have maxima and sums of their own until the chunk is written.  Here one
+# token of a second half has a value of 2^120 and a score of 2^-125.5 of the first token's, all others of the second halves
+# weigh nothing and the first halves' values are 0: the result is the product of that value, that weight and 1 / l, in which
+# only weight times 1 / l (2^-145.4) is no normal number.  Exact up to the roundings of two probabilities, of the chunk's row and of
+# the sum to bf16: less than 4 x 2^-9.
+def test_decode_keeps_a_light_half():
+    batch, h, d_cb, d_r, d_h, page, n = 256, 128, 128, 64, 128, 64, 8192
+    print("[case] light half", flush=True)
+    info = mlra.mlra_decode_plan_info(batch, h, d_h, 1, 1, d_cb, d_r, page, n, torch.bfloat16)
+    assert info["kernel"] == "mfma" and info["chunk_slots"] == 1 and info["merge_mfma"]
+    tok = torch.arange(n)
+    score = torch.where(tok % 64 < 32, torch.where(tok >= n - 64, 0.0, 7.875), -1000.0)
+    light = n - 32                       # in the tile that is worked on first: its maxima stay the references
+    score[light] = -125.5
+    latent, rope = torch.zeros((n, d_cb)), torch.zeros((n, d_r))
+    latent[light, 3], rope[:, 0] = 2.0 ** 120, score
+    q_abs, q_rope = torch.zeros((batch, 1, h, d_cb), dtype=torch.bfloat16), torch.ones((batch, h, d_r), dtype=torch.bfloat16)
+    w_uv = torch.eye(d_cb, d_h).repeat(1, h).view(1, d_cb, h * d_h).bfloat16()
+    lens = torch.zeros(batch, dtype=torch.int32)
+    lens[5] = n
+    cache = mlra.Cache(latent.view(n // page, 1, page, d_cb).bfloat16().cuda(), rope.view(n // page, page, d_r).bfloat16().cuda(),
+                       torch.arange(n // page, dtype=torch.int32).repeat(batch, 1).cuda(), lens.cuda())
+    out = host(mlra.mlra_decode_attn(cache, q_abs.cuda(), q_rope.cuda(), w_uv.cuda(), mlra.SCALE_FOLDED,
+                                     out_dtype=torch.float32))[5]
+    weights = torch.exp2(score.double())
+    ref = 2.0 ** 120 * float(weights[light] / weights.sum())
+    assert np.all(out[:, [c for c in range(d_h) if c != 3]] == 0.0)
+    assert np.max(np.abs(out[:, 3] / ref - 1.0)) <= 4 * 2.0 ** -9
