@@ -4,7 +4,7 @@
 // One workgroup (4 wavefronts) owns one (sequence, context chunk, 64 query heads) and walks the
 // chunk in tiles of 32 tokens [C | K^RoPE] that stream HBM -> LDS with direct-to-LDS loads.  Most launches run on
 // mla_pipe_kernel, described there; mla_mfma_kernel, two stages deep with two workgroups per CU or four stages deep with
-// one, keeps the shapes named in launch_mla_mfma.  In the latter the two products split the work differently:
+// one, keeps the shapes named in mla_mfma_stages.  In the latter the two products split the work differently:
 //   * scores and softmax by heads: wave w owns heads [16 w, 16 w + 16) and computes their complete scores
 //     S^T = [C | K^R] [q~ | q^R]^T over all 576 channels with 16x16x32 MFMAs (tokens x heads), so the
 //     softmax of a head is computed once, by one wave, with its running maximum and sum in that wave;
@@ -84,12 +84,13 @@ __device__ __forceinline__ float head_sum(float v) {
 
 typedef const __attribute__((address_space(4))) int32_t* const_i32_ptr;
 
-// false: an empty slot
+// false: an empty slot.  FIT: the kernel takes fitted launches as well.
+template <bool FIT>
 __device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& seq, int& split, int& chunk_len) {
   // workgroup -> (sequence, chunk, head half); the halves of one (sequence, chunk) get ids 8 apart
   const int n_hg = (p.h + kMHeads - 1) / kMHeads;
   int n_units = p.n_splits * p.batch, fit_len = 0;
-  if (p.chunk_out) {         // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
+  if (FIT && p.chunk_out) {    // one chunk length fitted to the lengths (chunk_fit.h), left for the merge
     const int i = threadIdx.x & 63;
     fit_len = i < p.batch ? max(0, min(p.seq_lens[i], p.max_pages * p.page_size)) : 0;
     chunk_len = chunk_fit::fit_length<false>(fit_len, p.batch, n_hg, p.cus, p.fit_min, kMFitOverhead);
@@ -108,7 +109,7 @@ __device__ __forceinline__ bool mla_unit(const MfmaParams& p, int& hgrp, int& se
     su = full_units + wg / n_hg;
     hgrp = wg % n_hg;
   }
-  if (p.chunk_out) {
+  if (FIT && p.chunk_out) {
     const chunk_fit::Chunk c = chunk_fit::find(fit_len, p.batch, chunk_len, su);
     seq = c.seq;
     split = c.split;
@@ -146,7 +147,7 @@ __global__ __launch_bounds__(256, STAGES == 2 ? 2 : 1) void mla_mfma_kernel(Mfma
   constexpr int kMPOff = STAGES * kMStage, kMAOff = kMPOff + kMPBytes, kMFOff = kMAOff + kMHeads * 4;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int hgrp, seq, split, chunk_len;
-  if (!mla_unit(p, hgrp, seq, split, chunk_len)) return;
+  if (!mla_unit<false>(p, hgrp, seq, split, chunk_len)) return;
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
   if (t0 >= n) return;
@@ -429,7 +430,7 @@ static_assert(kPLds <= 160 * 1024, "one workgroup per CU");
 __global__ __launch_bounds__(256, 1) void mla_pipe_kernel(MfmaParams p) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   int hgrp, seq, split, chunk_len;
-  if (!mla_unit(p, hgrp, seq, split, chunk_len)) return;
+  if (!mla_unit<true>(p, hgrp, seq, split, chunk_len)) return;
   const int n = ((const_i32_ptr)p.seq_lens)[seq];
   const int t0 = split * chunk_len;
   if (n <= 0 || (unsigned)t0 >= (unsigned)n) return;   // (unplanned slots reach beyond 2^31 in the widest caches)
@@ -817,7 +818,7 @@ static int launch_mla_as(const DecodeArgs& a, const MfmaParams& p, unsigned n_wg
 // three tiles in flight count.
 int mla_mfma_stages(const DecodeArgs& a) {
   const int n_hg = (a.h + kMHeads - 1) / kMHeads;
-  if (a.balanced && n_hg == 1 && a.batch <= a.cus && a.plan.chunk_tokens >= 1024) return 4;
+  if (a.balanced && n_hg == 1 && a.batch <= a.cus) return 4;
   return !a.balanced && !a.fitted && (long)a.plan.n_splits * n_hg * a.batch > a.cus && a.plan.chunk_tokens < 1280 ? 2 : 0;
 }
 

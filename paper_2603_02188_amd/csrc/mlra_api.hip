@@ -65,7 +65,7 @@ static SplitPlan plan_decode(int batch, int h, int n_blocks, int d_cb, int max_s
   // CUs of its short sequences idle while the longest finishes.  Four chunk slots per sequence and a
   // target of two rounds let the planning kernel cut the long sequences and hand the chunks out longest
   // first; a batch of nearly equal lengths is left uncut.
-  // (The MLA kernel's two-stage form runs two workgroups per CU; its targets here are still those of one.)
+  // (The MLA kernels that take planned launches, the pipelined and the four-stage one, run one workgroup per CU as well.)
   const bool mla = n_blocks == 1 && d_cb == 512;
   const bool two_per_wg = (d_cb == 128 && decode_mfma_paired(h, n_blocks)) || d_cb == 256;
   const long wgs = (long)batch * groups;
