@@ -90,20 +90,22 @@ def test_mla_tiles_and_pages(h, page, lens):
     assert np.array_equal(np.isfinite(got), live) and np.max(np.abs(got[live] - ref_lse[live])) <= 2e-2
 
 
-# the four-stage form (one head group, at most one workgroup per CU, chunks from 1024 tokens on: 64 sequences in four slots)
-# and, one sequence more, the two-stage form with all first chunks dispatched before the second ones: chunks of no tile up
-# to a whole chunk and its ragged end, pages that end inside and at the chunks' ends
-@pytest.mark.parametrize("batch,h,page", [(64, 64, 32), (64, 17, 96), (64, 40, 64), (65, 64, 32), (70, 128, 64), (256, 16, 64)])
-def test_mla_long_chunks(batch, h, page):
+# whole chunks, none and ragged ends, pages that end inside and at the chunks' ends, in each MLA kernel: the pipelined one (0) on
+# uniform chunks, the two-stage one (2: a batch of more than 64 in chunks of little more than 1024 tokens, all first ones
+# dispatched before the second ones) and the four-stage one (4: planned chunks, one head group, as many sequences as CUs)
+@pytest.mark.parametrize("batch,h,page,stages", [(64, 64, 32, 0), (64, 17, 96, 0), (64, 40, 64, 0), (70, 128, 64, 0), (65, 64, 32, 2),
+                                                 (66, 17, 96, 2), (256, 16, 64, 4), (256, 64, 96, 4), (256, 17, 32, 4),
+                                                 (256, 40, 64, 4)])
+def test_mla_long_chunks(batch, h, page, stages):
     edges = [4090, 0, 1, 31, 32, 33, 64, 65, 96, 97, 127, 129, 160, 1023, 1024, 1025, 1056, 1057, 1088, 1089, 2047, 2049, 3071,
              3073, 3104]
     lens = (edges + [50] * batch)[:batch]
     wl = gen.WORKLOADS["C5"].scaled(name="mla-long", batch=batch, n_min=0, n_max=4090, h=h, page_size=page, index=3300 + h + batch)
     info = mlra.mlra_decode_plan_info(batch, h, 128, 1, 1, 512, 64, page, -(-4090 // page) * page, torch.bfloat16)
     print(f"[case] mla long chunks B={batch} h={h} page={page} {info}", flush=True)
-    planned = batch == 256               # one workgroup per sequence before the plan cuts: four stages as well
+    route = mlra.mlra_decode_route_info(batch, h, 128, 1, 1, 512, 64, page, -(-4090 // page) * page, torch.bfloat16)
     assert info["chunk_slots"] == (2 if batch == 70 else 4) and info["chunk_tokens"] >= 1024
-    assert (info["target_chunks"] > 0) == planned
+    assert route["mla_stages"] == stages and route["planned"] == (stages == 4) and not route["fitted_from"]
     one = gen.as_single_latent(gen.make_decode_inputs(wl, poison=True, seq_lens=np.array(lens, dtype=np.int32)))
     cache = device_cache(one)
     q_nope, q_rope, w_uk, w_uv = device_queries_weights(one)
