@@ -286,7 +286,8 @@ MLRA_API int mlra_probe_shader_clock(long long* out, int32_t spin_us, void* stre
  *       plain form, 2 MFMA PAIRED form (two blocks per workgroup), 3 MFMA GLA form (256-channel latent heads), 4 MFMA
  *       MLA kernel (one 512-channel latent), 5 fp32 matrix instructions (fp32 caches and every other bf16 shape)
  *   [1] chunk slots per (sequence, block)     [2] uniform chunk length in tokens (for up to 64 sequences the decode
- *       kernel may fit a longer one to the lengths, never more chunks than slots)
+ *       kernel may fit another one to the lengths, shorter or longer: a multiple of 64, at least
+ *       max_seq_len / slots, see mlra_decode_route_info)
  *   [3] > 0: chunk lengths may follow the sequence lengths (fitted, or by a planning kernel), with this many chunks per block
  *       as the target                          [4] 1: a batch of nearly equal lengths is then left uncut
  *   [5] 1: the merge + up-projection epilogue is the bf16 one, 0: the fp32 one

@@ -813,9 +813,11 @@ static int launch_mla_as(const DecodeArgs& a, const MfmaParams& p, unsigned n_wg
 // kernel overlaps the start-up of one workgroup with another's tiles, 1.5 us each.  So the latter keeps launches of more
 // workgroups than CUs in short chunks, where these are not fitted (whole steps, two-stage against pipelined: 100 sequences of
 // 300 to 900 x 128 heads in chunks of 512 87 against 91 us, 140 of 2000 x 64 heads in chunks of 1024 130 against 143; with
-// long ones 256 of 2176 x 128 heads 265 against 257).  Planned chunks of one head group go to the four-stage kernel as long
-// as the batch is no more than a round: a batch of nearly equal lengths is left uncut then, and with many CUs idle its
-// three tiles in flight count.
+// long ones 256 of 2176 x 128 heads 265 against 257).  Planned chunks of one head group go to the four-stage kernel where the
+// batch is no more than a round, which is as many sequences as CUs (smaller batches are cut without a plan): left uncut, equal
+// lengths of 2000 to 3000 tokens take 1 to 2 % less in it (256 of 2176 x 64 heads, whole call, four-stage against pipelined 159
+// against 162 us, of 2000 x 16 heads 129 against 130).  Elsewhere it is behind: 256 of 8000 x 64 heads 458 against 447, of 512 to
+// 4096 190 against 187, of 300 with 16 of 8192 among them 128 against 109.
 int mla_mfma_stages(const DecodeArgs& a) {
   const int n_hg = (a.h + kMHeads - 1) / kMHeads;
   if (a.balanced && n_hg == 1 && a.batch <= a.cus) return 4;
